@@ -35,16 +35,30 @@ struct Fit {
 };
 
 constexpr Fit kRingFit{0.07996214, 1.82930381, 1.78868403, 0.0};
-// the register-weight kernel per filter size (1x1, 3x3, 5x5: its only
-// ones), whose chain feature counts the rounds of resident workgroups
-constexpr Fit kRegFit1{0.020774588, 1.0001204, 0.45244511, 0.30880721};
-constexpr Fit kRegFit3{0.023252027, 1.112875, 0.44553699, 0.46230413};
-constexpr Fit kRegFit5{0.019268499, 2.1330448, 1.0296948, 0.91803993};
-// its workgroups per CU: eight wavefronts each, 60-66 VGPRs for 1x1 and 3x3
-// filters (eight wavefronts per SIMD, the 33 KB of reduction tiles four
-// times over), 80-98 for 5x5 (five per SIMD)
-inline int reg_workgroups_per_cu(int R) { return R == 5 ? 2 : 4; }
 constexpr Fit kResidentFit{0.01847326, 0.0, 1.77078063, 1.41836285};
+
+// Fixed part of the register-weight kernel's path (ms: the count and repack
+// launch, the gated launch of the dense path) and the count's reading rate
+// (ms per input element, 4 bytes at 4 TB/s).
+constexpr double kShortCall = 0.08;  // ms
+constexpr double kRegFixed = 0.0180, kCountPerInput = 1e-9;
+
+// The largest count whose density does not exceed dstar.
+long long limit_for(double dstar, int64_t total, double dense) {
+    // a crossover past 0.95 sparsity counts as none: keeping the choice open
+    // (the count, and the gated launch of the path not taken) costs more on
+    // every call than the sparse path could save on the rare inputs past it
+    // (Tab. 2's inception 4a.1 at batch 128: modelled crossover 0.97-0.99,
+    // measured none up to 0.99; AUTO 18 % over the dense path at 0.9 while
+    // it kept the choice)
+    if (dstar < 0.05) return -1;
+    // and on a short call one below 0.4 counts as every input being sparse:
+    // the dense path's gated launches are a fifth of such a call (inception
+    // 4e.3 at batch 1: 16 us without them, 20 with), a rectified input that
+    // dense is rare
+    if (dstar >= 1.0 || (dstar > 0.6 && dense < kShortCall)) return static_cast<long long>(total);
+    return static_cast<long long>(std::floor(dstar * static_cast<double>(total)));
+}
 
 }  // namespace
 
@@ -55,8 +69,25 @@ long long crossover_nnz_limit(const SparseShape &sh) {
         // kernels over compacted lists: no model, the paper's 0.9
         return static_cast<long long>(std::floor(0.1 * static_cast<double>(total)));
     }
-    const Fit &freg = sh.R == 1 ? kRegFit1 : (sh.R == 3 ? kRegFit3 : kRegFit5);
-    const Fit &f = p.kernel == ISC_KERNEL_FUSED_RING ? kRingFit : (p.kernel == ISC_KERNEL_FUSED_REG ? freg : kResidentFit);
+    const double dense = dense_time_model(sh.K, static_cast<int64_t>(sh.N) * sh.Ho * sh.Wo,
+                                          static_cast<int64_t>(sh.C) * sh.R * sh.S);
+    RegTime rt;
+    if (p.kernel == ISC_KERNEL_FUSED_REG && sparse_reg_time_model(sh, &rt)) {
+        // 1x1 filters, with one multiply-add per nonzero and map, are bound
+        // by reading x, once for the count and again per group of maps
+        const double reads = sh.R == 1 ? 3.0 : 1.0;
+        const double rest = dense - kRegFixed - static_cast<double>(total) * kCountPerInput * reads;
+        // a 1x1 layer's dense path is a plain GEMM: the choice stays open only
+        // where the sparse path would save an eighth of it on a 0.95 sparse
+        // input
+        const double at95 = std::max(rt.base[0] + 0.05 * rt.slope[0], rt.base[1] + 0.05 * rt.slope[1]);
+        if (sh.R == 1 && at95 > rest - 0.12 * dense) return -1;
+        // the density where the first of the kernel's two bounds meets the
+        // dense path
+        return limit_for(std::min((rest - rt.base[0]) / rt.slope[0], (rest - rt.base[1]) / rt.slope[1]), total,
+                         dense);
+    }
+    const Fit &f = p.kernel == ISC_KERNEL_FUSED_RING ? kRingFit : kResidentFit;
     const double wc = static_cast<double>(p.workgroups) * p.waves * sh.C / std::max(1, p.phases);
     const int wrows = (p.rows - 1) * sh.T + sh.R, wcols = (p.cols - 1) * sh.T + sh.S;
     const double pw = static_cast<double>(wrows) * wcols;
@@ -71,27 +102,13 @@ long long crossover_nnz_limit(const SparseShape &sh) {
     } else {
         scan = wc * pw * 1e-9;
     }
-    // channels each wavefront walks in sequence; for the register-weight
-    // kernel, whose wavefronts wait on their own chain of loads and scans,
-    // times the rounds of resident workgroups the grid takes
-    double chain = static_cast<double>(sh.C) / std::max(1, p.phases) * 1e-3;
-    if (p.kernel == ISC_KERNEL_FUSED_REG)
-        chain *= std::ceil(static_cast<double>(p.workgroups) / (256.0 * reg_workgroups_per_cu(sh.R)));
+    // channels each wavefront walks in sequence
+    const double chain = static_cast<double>(sh.C) / std::max(1, p.phases) * 1e-3;
     const double fixed = f.c0 + f.c_scan * scan + f.c_chain * chain;
     const double per_density = f.c_nz * wc * pin * (10.0 + taps * kpl) * 1e-9;
-    const double dense = dense_time_model(sh.K, static_cast<int64_t>(sh.N) * sh.Ho * sh.Wo,
-                                          static_cast<int64_t>(sh.C) * sh.R * sh.S);
     if (!(per_density > 0.0)) return dense >= fixed ? static_cast<long long>(total) : -1;
     const double dstar = (dense - fixed) / per_density;  // density at which the two meet
-    // a crossover past 0.95 sparsity counts as none: keeping the choice open
-    // (the count, and the gated launch of the path not taken) costs more on
-    // every call than the sparse path could save on the rare inputs past it
-    // (Tab. 2's inception 4a.1 at batch 128: modelled crossover 0.97-0.99,
-    // measured none up to 0.99; AUTO 18 % over the dense path at 0.9 while
-    // it kept the choice)
-    if (dstar < 0.05) return -1;
-    if (dstar >= 1.0) return static_cast<long long>(total);
-    return static_cast<long long>(std::floor(dstar * static_cast<double>(total)));
+    return limit_for(dstar, total, dense);
 }
 
 }  // namespace isc

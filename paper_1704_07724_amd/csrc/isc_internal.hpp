@@ -223,6 +223,13 @@ hipError_t launch_sparse_fring(const SparseShape &sh, const float *x, const floa
 bool sparse_fused_plan_info(const SparseShape &sh, isc_plan *out);
 bool sparse_fring_plan_info(const SparseShape &sh, isc_plan *out);
 int64_t sparse_fring_max_groups(const SparseShape &sh);
+// Expected time (ms) of the register-weight kernel's launch for a shape: the
+// larger of two lines base + slope * (input density); false where another
+// kernel takes the shape.
+struct RegTime {
+    double base[2], slope[2];
+};
+bool sparse_reg_time_model(const SparseShape &sh, RegTime *t);
 // Upper bound of the workgroups of the on-the-fly kernels' launch for a
 // shape (the census slots their epilogue may write).
 int64_t sparse_fused_max_groups(const SparseShape &sh);

@@ -3,7 +3,8 @@
 #include "sparse_fused.hpp"
 
 #include <algorithm>
-#include <cstdlib>
+#include <cmath>
+#include <cstring>
 
 namespace isc {
 namespace fused {
@@ -11,21 +12,85 @@ namespace {
 
 int fused_tw(int Wo) { return Wo <= 8 ? 8 : (Wo <= 16 ? 16 : 28); }
 
+// Whether the register-weight kernel is compiled for the tile (the walk of
+// every other tile exists for all three filter sizes).
+template <int R>
+bool reg_tile_compiled_r(RegTile t) {
+    bool ok = false;
+    tile::static_for<0, kRegTiles>([&](auto ic) {
+        constexpr RegTile c = kRegTile[decltype(ic)::value];
+        if (c.th == t.th && c.tw == t.tw && c.same == t.same) ok = tile::AsmWalk<R, c.th, c.tw, c.same>::kAvailable;
+    });
+    return ok;
+}
+bool reg_tile_compiled(int R, RegTile t) {
+    return R == 1 ? reg_tile_compiled_r<1>(t) : (R == 3 ? reg_tile_compiled_r<3>(t) : reg_tile_compiled_r<5>(t));
+}
+
+// Whether the register-weight kernel may run the shape on the tile: one
+// column tile holds the output, and the positions its walk leaves out are
+// padding.
+bool reg_tile_takes(const SparseShape &sh, RegTile t) {
+    if (sh.Wo > t.tw || !reg_tile_compiled(sh.R, t)) return false;
+    if (t.same >= 1 && (sh.P != sh.R / 2 || sh.W > t.tw)) return false;
+    return t.same < 2 || sh.H <= t.th;
+}
+
+// Modelled cycles of the register-weight kernel on a tile at an input
+// density, which choose the tile and stand for the kernel in AUTO's
+// crossover: reg_cost's lines.  The CU with most workgroups (w of them, two wavefronts per
+// SIMD each, `occ` resident) is bound either by issue -- per wavefront and
+// channel 150 cycles of loads, moves and ballots, and per nonzero its FMAs
+// at 4 cycles and 15 more -- or, with few wavefronts, by the latency of one
+// wavefront's jumps, 150 cycles a nonzero beside its FMAs.  Each round also
+// pays its start and its reduction.  The constants are those of AlexNet
+// conv3-5 at 0.5 and 0.95 (7 x 13 tiles: 44 cycles a nonzero and 150 a
+// channel, 8000 a round) and of inception 4e.3 at batch 1 over six tile
+// heights (180 cycles a nonzero).
+constexpr double kPlanDensity = 0.1;  // the paper's layers are 0.9 to 0.95 sparse
+
+struct RegCost {
+    // cycles at density d: max(issue0 + issue1 * d, chain0 + chain1 * d) + fixed
+    double issue0, issue1, chain0, chain1, fixed;
+    double at(double d) const { return std::max(issue0 + issue1 * d, chain0 + chain1 * d) + fixed; }
+};
+
+RegCost reg_cost(const SparseShape &sh, RegTile t) {
+    const int64_t bands = (sh.Ho + t.th - 1) / t.th;
+    // the tile's registers: accumulators, two sets of weights, addresses
+    const int vgprs = t.th * t.tw + 2 * sh.R * sh.R + 14;
+    const int occ = vgprs <= 64 ? 4 : (vgprs <= 80 ? 3 : 2);
+    const int64_t wgs = sh.N * bands * ((sh.K + kLanes - 1) / kLanes);
+    const int64_t w = (wgs + 255) / 256;
+    const double rounds = static_cast<double>((w + occ - 1) / occ);
+    const double cols = std::min(t.tw + sh.R - 1, sh.W);
+    // input rows a band's window holds on average: all but the padding above
+    // the first band and what the last one reaches past the map
+    const int64_t in = bands * (t.th + sh.R - 1) - sh.P - (bands * t.th - sh.Ho + sh.P);
+    const double rows = std::min<double>(sh.H, std::max(1.0, static_cast<double>(in) / bands));
+    const double fmas = static_cast<double>(std::min(t.th, sh.Ho)) * t.tw * sh.R * sh.R / (rows * cols);
+    const double chan = (sh.C + kWaves - 1) / kWaves;
+    return {2.0 * w * chan * 150.0, 2.0 * w * chan * rows * cols * std::max(28.0, 15.0 + 4.0 * fmas),
+            rounds * chan * 100.0,  rounds * chan * rows * cols * (150.0 + 4.0 * fmas),
+            8000.0 * rounds + 32.0 * w * t.th * t.tw};
+}
+
 size_t fused_lds(int crs, int th, int tw) {
     return std::max(sizeof(float) * crs * kWPitch, sizeof(float) * kWaves * th * tw * kRPad);
 }
 
 // Plans whose wavefronts share no channel (every wavefront its own phase)
 // gain nothing from the filter in LDS: with the weights streamed to
-// registers, LDS holds only the reduction's tiles, and 32-position tiles let
-// two workgroups share a CU (LeNet conv2: 13.2 -> 9.5 us), four since the
-// tiles are summed in pairs (AlexNet conv3-5 10-12 % faster).  The filter need not
-// fit in LDS at all, and one workgroup per group of 64 maps takes any K
-// (AlexNet-ImageNet conv4 of Tab. 2 at batch 128: 259 us on the
-// filter-ring kernel -> 113 us).  Taken wherever eligible: stride 1, square
-// 1x1, 3x3 and 5x5 filters, at most 16 output columns.  A caller's tuning
-// kernel FUSED or FUSED_RING keeps the filter in LDS, or in the ring beyond
-// 64 maps.
+// registers, LDS holds only the reduction's tiles (LeNet conv2: 13.2 -> 9.5
+// us).  The filter need not fit in LDS at all, and one workgroup per group of
+// 64 maps takes any K (AlexNet-ImageNet conv4 of Tab. 2 at batch 128: 259 us
+// on the filter-ring kernel, 43 here).  Taken wherever eligible: stride 1,
+// square 1x1, 3x3 and 5x5 filters, at most 16 output columns; the tile is the
+// cheapest by reg_cost's model (tall ones on full grids, short ones where a
+// small batch leaves CUs idle: inception 4e.3 at batch 1 takes 10.9 us on 1 x
+// 16 and 22.2 on 7 x 14, at batch 128 182 and 69).  A caller's tuning kernel
+// FUSED or FUSED_RING keeps the filter in LDS, or in the ring beyond 64 maps;
+// rows and cols name a tile.
 bool fused_wreg_plan(const SparseShape &sh, FusedPlan *plan) {
     if (sh.tu.kernel == ISC_KERNEL_FUSED || sh.tu.kernel == ISC_KERNEL_FUSED_RING) return false;
     if (sh.T != 1 || sh.Wo > 16) return false;
@@ -33,18 +98,22 @@ bool fused_wreg_plan(const SparseShape &sh, FusedPlan *plan) {
     const int64_t kp = (sh.K + kLanes - 1) / kLanes * kLanes;
     if (static_cast<int64_t>(sh.C) * sh.R * sh.S * kp * static_cast<int64_t>(sizeof(float)) >= (1ll << 31))
         return false;
-    // 4 x 8 or 2 x 16 tiles, 2 x 13 and 2 x 14 on maps of exactly that width
-    // (AlexNet conv3-5, the 14 x 14 inception layers: the window loses the
-    // columns past the map and fits one ballot; conv3-5 5 % faster); half as
-    // many rows when full ones leave CUs without a workgroup (LeNet conv2 at
-    // batch 8: 7.7 -> 6.4 us; at batch 256 they cost 44 %).  A caller's
-    // tuning rows fixes the rows.
-    const int tw = sh.Wo <= 8 ? 8 : (sh.Wo == 13 || sh.Wo == 14 ? sh.Wo : 16);
-    const int full = 32 / tw;
-    const int64_t kgroups = (sh.K + kLanes - 1) / kLanes;
-    int th = static_cast<int64_t>(sh.N) * ((sh.Ho + full - 1) / full) * kgroups < kMinGroups ? full / 2 : full;
-    if (sh.tu.rows == full || sh.tu.rows == full / 2) th = sh.tu.rows;
-    *plan = FusedPlan{th, tw, kWaves, sizeof(float) * kRegSlots * th * tw * kRPad, 1, true};
+    RegTile best{0, 0, 0};
+    double best_c = 0.0;
+    for (const RegTile &t : kRegTile) {
+        if (!reg_tile_takes(sh, t)) continue;
+        if (t.th == sh.tu.rows && (sh.tu.cols == 0 || sh.tu.cols == t.tw)) {
+            best = t;
+            break;
+        }
+        const double c = reg_cost(sh, t).at(kPlanDensity);
+        if (best.th == 0 || c < best_c) {
+            best = t;
+            best_c = c;
+        }
+    }
+    *plan = FusedPlan{best.th, best.tw, kWaves,
+                      sizeof(float) * kRegSlots * reg_chunk_rows(best.th, best.tw) * best.tw * kRPad, 1, true, best.same};
     return true;
 }
 
@@ -56,7 +125,7 @@ bool fused_wreg_plan(const SparseShape &sh, FusedPlan *plan) {
 // workgroups.  A caller's tuning rows caps the tile height and phases fixes
 // the phases; tuning kernel FUSED_RING leaves the shape to the filter-ring
 // kernel.
-bool fused_plan(const SparseShape &sh, FusedPlan *plan) {
+bool make_fused_plan(const SparseShape &sh, FusedPlan *plan) {
     if (sh.tu.kernel == ISC_KERNEL_FUSED_RING && sparse_fring_applies(sh)) return false;
     if (sh.R != sh.S || !(sh.R == 1 || sh.R == 3 || sh.R == 5)) return false;
     if (!(sh.T == 1 || (sh.T == 2 && sh.R > 1 && sh.Wo <= 8))) return false;
@@ -88,7 +157,7 @@ bool fused_plan(const SparseShape &sh, FusedPlan *plan) {
             const size_t lds = fused_lds(crs, th, tw);
             if (lds > kLdsMax) continue;
             if (!found || groups > best_groups) {
-                *plan = FusedPlan{th, tw, cs, lds, sh.T, false};
+                *plan = FusedPlan{th, tw, cs, lds, sh.T, false, 0};
                 best_groups = groups;
                 found = true;
             }
@@ -99,6 +168,25 @@ bool fused_plan(const SparseShape &sh, FusedPlan *plan) {
     }
     if (found && plan->cs == kWaves) fused_wreg_plan(sh, plan);
     return found;
+}
+
+// The plan of a shape, asked for several times in the course of one call
+// (workspace layout, crossover, launch): the calling thread's last answer is
+// kept beside the shape and the overrides it was computed from.
+bool fused_plan(const SparseShape &sh, FusedPlan *plan) {
+    struct Last {
+        SparseShape sh;
+        FusedPlan plan;
+        int ok = -1;
+    };
+    static_assert(sizeof(SparseShape) == 11 * sizeof(int) + sizeof(isc_tuning), "SparseShape has no padding");
+    static thread_local Last last;
+    if (last.ok < 0 || std::memcmp(&last.sh, &sh, sizeof sh) != 0) {
+        last.ok = make_fused_plan(sh, &last.plan);
+        last.sh = sh;
+    }
+    if (last.ok) *plan = last.plan;
+    return last.ok != 0;
 }
 
 }  // namespace
@@ -122,6 +210,16 @@ int sparse_fused_kernel(const SparseShape &sh) {
     fused::FusedPlan p;
     if (fused::fused_plan(sh, &p)) return p.wreg ? 6 : 1;
     return sparse_fring_applies(sh) ? 5 : 0;
+}
+
+bool sparse_reg_time_model(const SparseShape &sh, RegTime *t) {
+    using namespace fused;
+    FusedPlan p;
+    if (!fused_plan(sh, &p) || !p.wreg) return false;
+    const RegCost c = reg_cost(sh, RegTile{p.th, p.tw, p.same});
+    constexpr double kMs = 1.0 / 2.4e6;  // a cycle at 2.4 GHz
+    *t = RegTime{{(c.issue0 + c.fixed) * kMs, (c.chain0 + c.fixed) * kMs}, {c.issue1 * kMs, c.chain1 * kMs}};
+    return true;
 }
 
 bool sparse_fused_plan_info(const SparseShape &sh, isc_plan *out) {

@@ -42,6 +42,7 @@ constexpr int kMaxTile = 64;     // accumulators per lane
 constexpr int kRegSlots = kWaves / 2;  // phase-pair tiles of the register-weight kernel's reduction
 constexpr int kMinGroups = 256;  // workgroups that fill the CUs once
 constexpr int kWPitch = 64;      // maps per filter column in the repacked layout (K <= 64)
+constexpr int kPastPlane = static_cast<int>(0x80000000u);  // byte offset past any plane of the register-weight kernel
 // Word 3 of a raw buffer resource on gfx9-family chips (gfx950 included):
 // 32-bit data format, no swizzle, bounds checked against the record count.
 constexpr int kBufferFormat = 0x00020000;
@@ -67,7 +68,25 @@ struct FusedPlan {
     size_t lds;
     int st;       // stride (1, or 2 with 8-column tiles)
     bool wreg;    // weights streamed to registers (sparse_conv_fused_reg_kernel)
+    int same;     // its walk's window positions
 };
+
+// Tiles of the register-weight kernel (each compiled for the filter sizes
+// whose walk gen_dispatch.py generates).
+struct RegTile {
+    int th, tw, same;  // same: which window positions the walk visits (gen_dispatch.py)
+};
+constexpr RegTile kRegTile[] = {
+    {7, 7, 2},  {8, 8, 2},  {7, 8, 2},  {4, 8, 1},  {7, 13, 1}, {5, 13, 1}, {4, 13, 1}, {3, 13, 1},
+    {7, 14, 1}, {5, 14, 1}, {4, 14, 1}, {3, 14, 1}, {6, 16, 1}, {3, 16, 1}, {7, 7, 0},  {8, 8, 0},
+    {4, 8, 0},  {2, 8, 0},  {7, 14, 0}, {5, 14, 0}, {3, 14, 0}, {6, 16, 0}, {3, 16, 0}, {2, 16, 0},
+    {1, 16, 0}};
+constexpr int kRegTiles = sizeof(kRegTile) / sizeof(kRegTile[0]);
+
+// Rows of a register-weight tile summed per pass of its reduction: at most
+// 56 positions, so that the phase-pair tiles take at most 58 KB and two
+// workgroups share a CU's LDS.
+constexpr int reg_chunk_rows(int th, int tw) { return th * tw <= 56 ? th : (th + 1) / 2; }
 
 // Launchers of the kernels of one filter size (sparse_fused_r{1,3,5}.hip).
 hipError_t launch_r1(const FusedArgs &a, const FusedPlan &p, hipStream_t s);
@@ -253,16 +272,29 @@ void sparse_conv_fused_kernel(FusedArgs a) {
 // one row group, every wavefront its own channels): each wavefront streams
 // its channels' weights from the repacked filter (through L2) into
 // registers, one channel ahead of its walk, so LDS holds only the tiles of
-// the reduction -- one per pair of phases, for four-row tiles of 8 columns
-// little enough for four workgroups per CU.  One workgroup per group of
-// 64 output maps (kgroups), lanes over the maps of its group.  Stride 1;
+// the reduction, one per pair of phases.  One workgroup per group of 64
+// output maps (kgroups), lanes over the maps of its group.  Stride 1;
 // otherwise as the kernel above.
-template <int RS_, int TH, int TW, bool WIDE>
+//
+// What bounds it is instruction issue per nonzero and per channel, not the
+// multiply-adds: on AlexNet conv3 (0.95 sparse) a 2 x 13 tile with a static
+// scan of its window spent 20 scalar instructions a nonzero and loaded the
+// channel's nine weights, 3.2 GB over the launch, for 2.3 nonzeros.  So the
+// walk jumps from nonzero to nonzero (AsmWalk: one jump and five scalar
+// instructions each, the next leaf's address computed between the FMAs), and
+// tiles are as tall as the registers of four wavefronts per SIMD allow: 7 x
+// 13 meets 4.9 nonzeros per channel, 7.2 FMAs each, and loads 0.9 GB of
+// weights.  Kernel alone, batch 128: AlexNet conv3/4/5 179/261/178 -> 79/108/
+// 76 us (8.6 -> 21.8 TFLOP/s on nonzero MACs), inception 4e.3 108 -> 69,
+// 5b.3 46 -> 25, AlexNet-ImageNet conv4 88 -> 43, 5a.1 52 -> 40.
+// The leaves' alignment (4 to 128 bytes) made no difference.
+template <int RS_, int TH, int TW, int SAME, bool WIDE>
 __global__ __launch_bounds__(kWaves * kLanes, 4)
 void sparse_conv_fused_reg_kernel(FusedArgs a) {
-    using T = tile::Shape<RS_, RS_, 1, TH, TW>;
-    constexpr int RS2 = RS_ * RS_, EPL = T::EPL;
-    extern __shared__ float lds[];  // the phase-pair tiles [kRegSlots][TH*TW][kRPad]
+    using Walk = tile::AsmWalk<RS_, TH, TW, SAME>;
+    constexpr int RS2 = RS_ * RS_, TP = TH * TW, NQ = Walk::kPositions;
+    constexpr int EPL = Walk::kChunks, CH = tile::kWalkChunk;
+    extern __shared__ float lds[];  // the phase-pair tiles [kRegSlots][reg_chunk_rows(TH, TW) * TW][kRPad]
 
     const int tid = threadIdx.x;
     const int lane = tid & (kLanes - 1);
@@ -277,20 +309,23 @@ void sparse_conv_fused_reg_kernel(FusedArgs a) {
     const int kbase = kg * kLanes;
     const int kcnt = min(kLanes, a.K - kbase);
     const int C = a.C, H = a.H, W = a.W, P = a.P;
-    const bool rows_ok = oy0 < a.Ho;
     const size_t HW = static_cast<size_t>(H) * W;
+    const int plane_bytes = H * W * static_cast<int>(sizeof(float));
     const float *x_n = a.x + static_cast<size_t>(n) * C * HW;
     const int ncw = phase < C ? (C - 1 - phase) / cs + 1 : 0;
 
+    // byte offset in the channel's plane of position q * CH + lane of the
+    // walk; lanes without one (the padding, and lane CH of a ballot, whose
+    // bit is the walk's sentinel) an offset past the plane, which the
+    // hardware reads as zero
     int xoff[EPL];
-    bool inwin[EPL];
 #pragma unroll
     for (int q = 0; q < EPL; ++q) {
-        const int e = q * kLanes + lane;
-        const int wy = e / T::WCOLS;
-        const int y = oy0 - P + wy, xx = e - wy * T::WCOLS - P;
-        inwin[q] = rows_ok && e < T::WROWS * T::WCOLS && y >= 0 && y < H && xx >= 0 && xx < W;
-        xoff[q] = inwin[q] ? y * W + xx : 0;
+        const int e = q * CH + lane;
+        const int wy = e / Walk::kCols;
+        const int y = oy0 - P + Walk::kRow0 + wy, xx = e - wy * Walk::kCols - P + Walk::kCol0;
+        const bool in = lane < CH && e < NQ && y >= 0 && y < H && xx >= 0 && xx < W;
+        xoff[q] = in ? (y * W + xx) * static_cast<int>(sizeof(float)) : kPastPlane;
     }
 
     // the next channel's window and weights (loaded a channel ahead; the
@@ -309,9 +344,11 @@ void sparse_conv_fused_reg_kernel(FusedArgs a) {
     float wn[RS2];
     auto load_ch = [&](int i) {
         const int c = phase + min(i, ncw - 1) * cs;
-        const float *plane = x_n + static_cast<size_t>(c) * HW;
+        const __amdgpu_buffer_rsrc_t plane = __builtin_amdgcn_make_buffer_rsrc(
+            const_cast<float *>(x_n + static_cast<size_t>(c) * HW), 0, plane_bytes, kBufferFormat);
 #pragma unroll
-        for (int q = 0; q < EPL; ++q) xn[q] = plane[xoff[q]];
+        for (int q = 0; q < EPL; ++q)
+            xn[q] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(plane, xoff[q], 0, 0));
         if constexpr (WIDE) {
             const int voff = ((c * RS2 * a.Kp + kbase + lane) * static_cast<int>(sizeof(float)));
 #pragma unroll
@@ -331,11 +368,9 @@ void sparse_conv_fused_reg_kernel(FusedArgs a) {
         return;
     }
 
-    tile::Acc<T> acc;
+    float acc[TP];
 #pragma unroll
-    for (int y = 0; y < TH; ++y)
-#pragma unroll
-        for (int x = 0; x < TW; ++x) acc[y][x][0] = 0.0f;
+    for (int p = 0; p < TP; ++p) acc[p] = 0.0f;
 
 #pragma unroll 1
     for (int i = 0; i < ncw; ++i) {
@@ -344,76 +379,82 @@ void sparse_conv_fused_reg_kernel(FusedArgs a) {
         // channel's loads and need no copy at the back edge), then the next
         // channel's loads fly during this channel's walk
         float cur[EPL];
-        tile::Wts<T> w;
+        float w[RS2];
 #pragma unroll
         for (int q = 0; q < EPL; ++q) asm volatile("v_mov_b32 %0, %1" : "=v"(cur[q]) : "v"(xn[q]));
 #pragma unroll
-        for (int t = 0; t < RS2; ++t) asm volatile("v_mov_b32 %0, %1" : "=v"(w[t / RS_][t % RS_][0]) : "v"(wn[t]));
+        for (int t = 0; t < RS2; ++t) asm volatile("v_mov_b32 %0, %1" : "=v"(w[t]) : "v"(wn[t]));
         if (i + 1 < ncw) load_ch(i + 1);
         unsigned long long mask[EPL];
 #pragma unroll
-        for (int q = 0; q < EPL; ++q) mask[q] = __ballot(inwin[q] && (__float_as_uint(cur[q]) & 0x7fffffffu) != 0u);
-        tile::walk_scan<T>(mask, cur, acc, w);
+        for (int q = 0; q < EPL; ++q) {
+            constexpr int kLast = NQ - (EPL - 1) * CH;  // positions of the last ballot
+            mask[q] = __ballot((__float_as_uint(cur[q]) & 0x7fffffffu) != 0u) | (1ull << (q + 1 < EPL ? CH : kLast));
+        }
+        Walk::run(mask, cur, acc, w);
     }
 
     // step 3: the phase tiles summed through LDS and stored to NCHW, as in
     // the kernel above (one row group).  Half as many tiles as phases: the
     // upper phases write theirs, each lower phase p adds phase p + 4's to its
     // registers and writes the pair back into the same slot, and the store
-    // sums the four pairs in order -- a fixed order, so deterministic.  The
-    // smaller LDS footprint lets twice as many workgroups share a CU.
-    constexpr int TP = TH * TW;
+    // sums the four pairs in order -- a fixed order, so deterministic.  Tall
+    // tiles take several passes of RC rows each, so that LDS holds two
+    // workgroups per CU.
+    constexpr int RC = reg_chunk_rows(TH, TW), CP = RC * TW;
     constexpr int kSlots = kRegSlots;
     float *red = lds;
     const int slot = wave % kSlots;
-    if (wave >= kSlots) {
-#pragma unroll
-        for (int y = 0; y < TH; ++y)
-#pragma unroll
-            for (int x = 0; x < TW; ++x) red[(slot * TP + y * TW + x) * kRPad + lane] = acc[y][x][0];
-    }
-    __syncthreads();
-    if (wave < kSlots) {
-#pragma unroll
-        for (int y = 0; y < TH; ++y)
-#pragma unroll
-            for (int x = 0; x < TW; ++x) {
-                float *r = red + (slot * TP + y * TW + x) * kRPad + lane;
-                *r = acc[y][x][0] + *r;
-            }
-    }
-    __syncthreads();
     const int Wo = a.Wo;
-    const int rows = min(TH, a.Ho - oy0);
-    const int npos = rows * Wo;  // <= kMaxTile
-    const int ostep = (kWaves * kLanes) / npos;
-    const int k0 = tid / npos;
-    const int pos = tid - k0 * npos;
-    const int oyl = pos / Wo;
-    const int ox = pos - oyl * Wo;
     const size_t plane_out = static_cast<size_t>(a.Ho) * Wo;
-    const float *src = red + (oyl * TW + ox) * kRPad;
-    float *dst = a.y + (static_cast<size_t>(n) * a.K + kbase) * plane_out + static_cast<size_t>(oy0) * Wo + pos;
     const int relu = a.epi.relu;
     uint32_t cnt = 0;
-    // k: map within this workgroup's group of 64
-    for (int k = k0 < ostep ? k0 : kcnt; k < kcnt; k += ostep) {
-        float part[kSlots];
+    tile::static_for<0, (TH + RC - 1) / RC>([&](auto pc) {
+        constexpr int R0 = decltype(pc)::value * RC, R1 = R0 + RC < TH ? R0 + RC : TH;
+        if (oy0 + R0 >= a.Ho) return;
+        if constexpr (R0 > 0) __syncthreads();  // the previous pass's reads are done
+        if (wave >= kSlots) {
 #pragma unroll
-        for (int p = 0; p < kSlots; ++p) part[p] = src[p * TP * kRPad + k];
-        float sum = part[0];
+            for (int p = R0 * TW; p < R1 * TW; ++p) red[(slot * CP + p - R0 * TW) * kRPad + lane] = acc[p];
+        }
+        __syncthreads();
+        if (wave < kSlots) {
 #pragma unroll
-        for (int p = 1; p < kSlots; ++p) sum += part[p];
-        sum = epilogue_value(sum, relu);
-        cnt += nonzero_bit(sum);
-        dst[static_cast<size_t>(k) * plane_out] = sum;
-    }
+            for (int p = R0 * TW; p < R1 * TW; ++p) {
+                float *r = red + (slot * CP + p - R0 * TW) * kRPad + lane;
+                *r = acc[p] + *r;
+            }
+        }
+        __syncthreads();
+        const int rows = min(R1 - R0, a.Ho - oy0 - R0);
+        const int npos = rows * Wo;  // <= kWaves * kLanes
+        const int ostep = (kWaves * kLanes) / npos;
+        const int k0 = tid / npos;
+        const int pos = tid - k0 * npos;
+        const int oyl = pos / Wo;
+        const int ox = pos - oyl * Wo;
+        const float *src = red + (oyl * TW + ox) * kRPad;
+        float *dst =
+            a.y + (static_cast<size_t>(n) * a.K + kbase) * plane_out + static_cast<size_t>(oy0 + R0) * Wo + pos;
+        // k: map within this workgroup's group of 64
+        for (int k = k0 < ostep ? k0 : kcnt; k < kcnt; k += ostep) {
+            float part[kSlots];
+#pragma unroll
+            for (int p = 0; p < kSlots; ++p) part[p] = src[p * CP * kRPad + k];
+            float sum = part[0];
+#pragma unroll
+            for (int p = 1; p < kSlots; ++p) sum += part[p];
+            sum = epilogue_value(sum, relu);
+            cnt += nonzero_bit(sum);
+            dst[static_cast<size_t>(k) * plane_out] = sum;
+        }
+    });
     if (a.epi.census) census_commit(a.epi, cnt, reinterpret_cast<uint32_t *>(red + kLanes), kRPad);
 }
 
-template <int RS_, int TH, int TW, bool WIDE>
+template <int RS_, int TH, int TW, int SAME, bool WIDE>
 hipError_t launch_fused_reg_w(const FusedArgs &a, size_t lds, hipStream_t s) {
-    auto kern = sparse_conv_fused_reg_kernel<RS_, TH, TW, WIDE>;
+    auto kern = sparse_conv_fused_reg_kernel<RS_, TH, TW, SAME, WIDE>;
     if (lds > 64 * 1024) {
         hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(kern),
                                            hipFuncAttributeMaxDynamicSharedMemorySize, static_cast<int>(lds));
@@ -428,9 +469,9 @@ hipError_t launch_fused_reg_w(const FusedArgs &a, size_t lds, hipStream_t s) {
 // one group of 64 maps: filter taps at immediate offsets (kgroups == 1 and
 // Kp == 64); else, or when the caller asks (a.wide), through the buffer
 // resource.
-template <int RS_, int TH, int TW>
+template <int RS_, int TH, int TW, int SAME>
 hipError_t launch_fused_reg_t(const FusedArgs &a, size_t lds, hipStream_t s) {
-    return a.wide ? launch_fused_reg_w<RS_, TH, TW, true>(a, lds, s) : launch_fused_reg_w<RS_, TH, TW, false>(a, lds, s);
+    return a.wide ? launch_fused_reg_w<RS_, TH, TW, SAME, true>(a, lds, s) : launch_fused_reg_w<RS_, TH, TW, SAME, false>(a, lds, s);
 }
 
 template <int RS_, int TH, int TW, int ST>
@@ -466,26 +507,16 @@ hipError_t launch_fused_th(const FusedArgs &a, int th, size_t lds, hipStream_t s
 template <int RS_>
 hipError_t launch_fused_rs(const FusedArgs &a, const FusedPlan &p, hipStream_t s) {
     if (p.wreg) {
-        // 4 x 8, 2 x 8, 2 x 16, 1 x 16 and the exact 13- and 14-column
-        // tiles, stride 1
         if (p.st != 1) return hipErrorInvalidValue;
-        if (p.tw == 8) {
-            return p.th == 4 ? launch_fused_reg_t<RS_, 4, 8>(a, p.lds, s)
-                             : (p.th == 2 ? launch_fused_reg_t<RS_, 2, 8>(a, p.lds, s) : hipErrorInvalidValue);
-        }
-        if (p.tw == 16) {
-            return p.th == 2 ? launch_fused_reg_t<RS_, 2, 16>(a, p.lds, s)
-                             : (p.th == 1 ? launch_fused_reg_t<RS_, 1, 16>(a, p.lds, s) : hipErrorInvalidValue);
-        }
-        if (p.tw == 13) {
-            return p.th == 2 ? launch_fused_reg_t<RS_, 2, 13>(a, p.lds, s)
-                             : (p.th == 1 ? launch_fused_reg_t<RS_, 1, 13>(a, p.lds, s) : hipErrorInvalidValue);
-        }
-        if (p.tw == 14) {
-            return p.th == 2 ? launch_fused_reg_t<RS_, 2, 14>(a, p.lds, s)
-                             : (p.th == 1 ? launch_fused_reg_t<RS_, 1, 14>(a, p.lds, s) : hipErrorInvalidValue);
-        }
-        return hipErrorInvalidValue;
+        hipError_t e = hipErrorInvalidValue;
+        tile::static_for<0, kRegTiles>([&](auto ic) {
+            constexpr RegTile t = kRegTile[decltype(ic)::value];
+            if constexpr (tile::AsmWalk<RS_, t.th, t.tw, t.same>::kAvailable) {
+                if (p.th == t.th && p.tw == t.tw && p.same == t.same)
+                    e = launch_fused_reg_t<RS_, t.th, t.tw, t.same>(a, p.lds, s);
+            }
+        });
+        return e;
     }
     if (p.st == 2) {
         if constexpr (RS_ == 1) {

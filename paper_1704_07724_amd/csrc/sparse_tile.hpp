@@ -24,6 +24,7 @@ namespace isc {
 namespace tile {
 
 constexpr int kLanes = 64;
+constexpr int kWalkChunk = 63;  // window positions per ballot of AsmWalk (the next bit is its sentinel)
 
 // T_: the convolution's stride (output row oy reads input rows oy*T + r).
 template <int R_, int S_, int KPL_, int TH_, int TW_, int T_ = 1>
@@ -37,7 +38,7 @@ struct Shape {
 };
 
 template <int B, int E, typename F>
-__device__ __forceinline__ void static_for(F &&f) {
+__host__ __device__ __forceinline__ void static_for(F &&f) {
     if constexpr (B < E) {
         f(std::integral_constant<int, B>{});
         static_for<B + 1, E>(f);
