@@ -8,17 +8,14 @@
 // sparsity).
 //
 // Both paths' times are modelled from the plan the launch would run.  The
-// sparse path's time is linear in the input's density d = 1 - sparsity:
-//   t_sparse(d) = c0 + c1 * F_scan + c2 * d * F_nz + c3 * F_chain
-// with, per wavefront-channel of the plan (Wc of them), the window's
-// positions (F_scan: the scan's tests, the ring's LDS traffic), the window's
-// nonzeros times their work (F_nz: scalar dispatch plus taps times maps per
-// lane in multiply-adds), and the channels each wavefront walks in sequence
-// (F_chain: memory latency per channel on small grids; for the
-// register-weight kernel times the rounds of resident workgroups).  The coefficients
-// of each kernel family (the register-weight kernel's per filter size) were
-// fitted to the sparse path measured on every workload and Tab. 2 shape at
-// sparsities 0.5 to 0.99 (5-9 % rms); the
+// register-weight and filter-ring kernels' models, which also choose their
+// tiles, are the larger of two lines in the input's density (sparse_fused.hip,
+// sparse_fring.hip); the filter-resident kernel's is one line,
+//   t_sparse(d) = c0 + c2 * d * F_nz + c3 * F_chain
+// with F_nz the nonzeros of its wavefronts' windows times their work (scalar
+// dispatch plus taps in multiply-adds) and F_chain the channels each
+// wavefront walks in sequence, fitted to the sparse path measured at
+// sparsities 0.5 to 0.99.  The
 // dense path's model is in dense_conv.hip.  The limit handed to the device
 // is the largest nonzero count whose modelled sparse time does not exceed
 // the modelled dense time; the device compares integers only.
@@ -31,17 +28,16 @@ namespace isc {
 namespace {
 
 struct Fit {
-    double c0, c_scan, c_nz, c_chain;  // ms; features scaled by 1e-9 (1e-3 for the chain)
+    double c0, c_nz, c_chain;  // ms; features scaled by 1e-9 (1e-3 for the chain)
 };
 
-constexpr Fit kRingFit{0.07996214, 1.82930381, 1.78868403, 0.0};
-constexpr Fit kResidentFit{0.01847326, 0.0, 1.77078063, 1.41836285};
+constexpr Fit kResidentFit{0.01847326, 1.77078063, 1.41836285};
 
-// Fixed part of the register-weight kernel's path (ms: the count and repack
+// Fixed part of the other on-the-fly kernels' path (ms: the count and repack
 // launch, the gated launch of the dense path) and the count's reading rate
 // (ms per input element, 4 bytes at 4 TB/s).
 constexpr double kShortCall = 0.08;  // ms
-constexpr double kRegFixed = 0.0180, kCountPerInput = 1e-9;
+constexpr double kWalkFixed = 0.0180, kCountPerInput = 1e-9;
 
 // The largest count whose density does not exceed dstar.
 long long limit_for(double dstar, int64_t total, double dense) {
@@ -57,7 +53,9 @@ long long limit_for(double dstar, int64_t total, double dense) {
     // 4e.3 at batch 1: 16 us without them, 20 with), a rectified input that
     // dense is rare
     if (dstar >= 1.0 || (dstar > 0.6 && dense < kShortCall)) return static_cast<long long>(total);
-    return static_cast<long long>(std::floor(dstar * static_cast<double>(total)));
+    // the kernels' models are those of rectified inputs: past a density of
+    // 0.69 the two paths are within a tenth of each other where they cross
+    return static_cast<long long>(std::floor(std::min(dstar, 0.69) * static_cast<double>(total)));
 }
 
 }  // namespace
@@ -71,12 +69,13 @@ long long crossover_nnz_limit(const SparseShape &sh) {
     }
     const double dense = dense_time_model(sh.K, static_cast<int64_t>(sh.N) * sh.Ho * sh.Wo,
                                           static_cast<int64_t>(sh.C) * sh.R * sh.S);
-    RegTime rt;
-    if (p.kernel == ISC_KERNEL_FUSED_REG && sparse_reg_time_model(sh, &rt)) {
+    KernelTime rt;
+    if (p.kernel == ISC_KERNEL_FUSED_REG ? sparse_reg_time_model(sh, &rt)
+                                         : p.kernel == ISC_KERNEL_FUSED_RING && sparse_ring_time_model(sh, &rt)) {
         // 1x1 filters, with one multiply-add per nonzero and map, are bound
         // by reading x, once for the count and again per group of maps
         const double reads = sh.R == 1 ? 3.0 : 1.0;
-        const double rest = dense - kRegFixed - static_cast<double>(total) * kCountPerInput * reads;
+        const double rest = dense - kWalkFixed - static_cast<double>(total) * kCountPerInput * reads;
         // a 1x1 layer's dense path is a plain GEMM: the choice stays open only
         // where the sparse path would save an eighth of it on a 0.95 sparse
         // input
@@ -87,25 +86,16 @@ long long crossover_nnz_limit(const SparseShape &sh) {
         return limit_for(std::min((rest - rt.base[0]) / rt.slope[0], (rest - rt.base[1]) / rt.slope[1]), total,
                          dense);
     }
-    const Fit &f = p.kernel == ISC_KERNEL_FUSED_RING ? kRingFit : kResidentFit;
     const double wc = static_cast<double>(p.workgroups) * p.waves * sh.C / std::max(1, p.phases);
     const int wrows = (p.rows - 1) * sh.T + sh.R, wcols = (p.cols - 1) * sh.T + sh.S;
-    const double pw = static_cast<double>(wrows) * wcols;
     const double pin = static_cast<double>(std::min(wrows, sh.H)) * std::min(wcols, sh.W);
     const double useful = static_cast<double>(std::min(p.rows, sh.Ho)) * std::min(p.cols, sh.Wo);
     const double taps = std::min<double>(sh.R * sh.S, useful * sh.R * sh.S / pin);
-    const int kpl = std::max(1, p.maps_per_lane);
-    double scan;
-    if (p.kernel == ISC_KERNEL_FUSED_RING) {
-        const double wbytes = 4.0 * sh.R * sh.S * 64 * kpl;
-        scan = wc * (pw * 1.65 + wbytes / 128.0 * (1.0 + 1.0 / std::max(1, p.waves))) * 1e-9;
-    } else {
-        scan = wc * pw * 1e-9;
-    }
     // channels each wavefront walks in sequence
     const double chain = static_cast<double>(sh.C) / std::max(1, p.phases) * 1e-3;
-    const double fixed = f.c0 + f.c_scan * scan + f.c_chain * chain;
-    const double per_density = f.c_nz * wc * pin * (10.0 + taps * kpl) * 1e-9;
+    const Fit &f = kResidentFit;
+    const double fixed = f.c0 + f.c_chain * chain;
+    const double per_density = f.c_nz * wc * pin * (10.0 + taps * std::max(1, p.maps_per_lane)) * 1e-9;
     if (!(per_density > 0.0)) return dense >= fixed ? static_cast<long long>(total) : -1;
     const double dstar = (dense - fixed) / per_density;  // density at which the two meet
     return limit_for(dstar, total, dense);

@@ -89,7 +89,11 @@ WALK_TILES += [(R, TH, TW, 0) for R in (1, 3) for TH, TW in ((8, 8), (6, 16))]
 WALK_TILES += [(1, TH, TW, 0) for TH, TW in ((7, 7), (7, 14), (5, 14), (3, 14))]
 WALK_TILES += [(R, TH, TW, 1) for R in (3, 5) for TH, TW in ((4, 8), (4, 13), (4, 14), (3, 14), (3, 16))]
 WALK_TILES += [(3, TH, TW, 1) for TH, TW in ((7, 13), (5, 13), (3, 13), (7, 14), (5, 14), (6, 16))]
-WALK_TILES += [(R, 7, 7, 2) for R in (3, 5)] + [(3, 8, 8, 2), (5, 7, 8, 2)]
+WALK_TILES += [(R, 7, 7, 2) for R in (3, 5)] + [(3, 8, 8, 2)]
+# Tiles of the filter-ring kernel: (R, TH, TW, 0, KPL).
+RING_TILES = [(5, TH, TW, 0, 1) for TH, TW in ((9, 9), (7, 14), (5, 14), (3, 14))] + [(5, 1, 28, 0, 2)]
+RING_TILES += [(3, TH, 14, 0, 1) for TH in (7, 4, 2)] + [(3, 4, 14, 0, 2)]
+RING_TILES += [(1, TH, 14, 0, 1) for TH in (4, 2)] + [(1, 4, 14, 0, 2)]  # 7 x 14: WALK_TILES
 WALK_CHUNK = 63  # window positions per ballot; the next bit is the sentinel
 WALK_HEAD = 32   # bytes of a leaf besides its FMAs: lane read (8), five scalar instructions (20), the jump (4)
 
@@ -101,8 +105,8 @@ def walk_positions(R, TH, TW, same):
     return [(wy, xp) for wy in rows for xp in cols]
 
 
-def walk_specialisation(R, TH, TW, same):
-    """AsmWalk<R, TH, TW, SAME>: every set bit of the window's ballots, in order.
+def walk_specialisation(R, TH, TW, same, kpl=1):
+    """AsmWalk<R, TH, TW, SAME, KPL>: every set bit of the window's ballots, in order.
 
     Leaf q (chunk q / 64, lane q % 64 of that ballot) reads its nonzero's
     value from its lane, finds the next set bit, computes that bit's leaf
@@ -114,26 +118,27 @@ def walk_specialisation(R, TH, TW, same):
     pos = walk_positions(R, TH, TW, same)
     nq = len(pos)
     epl = -(-nq // WALK_CHUNK)
-    maxf = max(len(leaf_fmas(R, TH, TW, wy, xp)) for wy, xp in pos)
+    maxf = kpl * max(len(leaf_fmas(R, TH, TW, wy, xp)) for wy, xp in pos)
     stride = max(WALK_HEAD + 4 * maxf, 36 if epl > 1 else 0)
 
     def find_next(e):
-        return [" s_ff1_i32_b64 s72, %[m{}]".format(e), " s_bitset0_b64 %[m{}], s72".format(e),
-                " s_mulk_i32 s72, {}".format(stride), " s_add_u32 s74, s70, s72", " s_addc_u32 s75, s71, 0"]
+        return [" s_ff1_i32_b64 s46, %[m{}]".format(e), " s_bitset0_b64 %[m{}], s46".format(e),
+                " s_mulk_i32 s46, {}".format(stride), " s_add_u32 s48, s44, s46", " s_addc_u32 s49, s45, 0"]
 
-    jump = [" s_setpc_b64 s[74:75]"]
-    lines = [" s_getpc_b64 s[70:71]", "W%=_base:", " s_add_u32 s70, s70, W%=_q0-W%=_base", " s_addc_u32 s71, s71, 0"]
+    jump = [" s_setpc_b64 s[48:49]"]
+    lines = [" s_getpc_b64 s[44:45]", "W%=_base:", " s_add_u32 s44, s44, W%=_q0-W%=_base", " s_addc_u32 s45, s45, 0"]
     lines += find_next(0) + jump
     for e in range(epl):
         last = e == epl - 1
         n = min(WALK_CHUNK, nq - e * WALK_CHUNK)
         for l in range(n):
             wy, xp = pos[e * WALK_CHUNK + l]
-            fmas = [" v_fmac_f32_e32 %[a{}], s73, %[w{}]".format(a, w) for a, w in leaf_fmas(R, TH, TW, wy, xp)]
+            fmas = [" v_fmac_f32_e32 %[a{}], s47, %[w{}]".format(a * kpl + j, w * kpl + j)
+                    for a, w in leaf_fmas(R, TH, TW, wy, xp) for j in range(kpl)]
             nx = find_next(e)
             # the scalar chain between the FMAs; two instructions between the
             # lane read and the first use of its scalar
-            body = [" v_readlane_b32 s73, %[x{}], {}".format(e, l)] + nx[:2]
+            body = [" v_readlane_b32 s47, %[x{}], {}".format(e, l)] + nx[:2]
             for i in range(2, 5):
                 body += fmas[i - 2:i - 1] + [nx[i]]
             body += fmas[3:] + jump
@@ -145,19 +150,19 @@ def walk_specialisation(R, TH, TW, same):
         lines.append("W%=_q{}:".format(e * 64 + n))
         if not last:  # the sentinel: the next chunk's table and first bit
             assert n == WALK_CHUNK
-            lines += [" s_add_u32 s70, s70, {}".format(64 * stride), " s_addc_u32 s71, s71, 0"]
+            lines += [" s_add_u32 s44, s44, {}".format(64 * stride), " s_addc_u32 s45, s45, 0"]
             lines += find_next(e + 1) + jump
             if stride > 36:
                 lines.append(" .fill {}, 4, 0xbf800000".format((stride - 36) // 4))
-    na, nw = TH * TW, R * R
+    na, nw = TH * TW * kpl, R * R * kpl
     asm = "\n            ".join('"%s\\n"' % l for l in lines)
     outs = ", ".join(['[a{0}] "+v"(acc[{0}])'.format(i) for i in range(na)] +
                      ['[m{0}] "+s"(mask[{0}])'.format(e) for e in range(epl)])
     ins = ", ".join(['[w{0}] "v"(w[{0}])'.format(i) for i in range(nw)] +
                     ['[x{0}] "v"(x[{0}])'.format(e) for e in range(epl)])
     return '''template <>
-struct AsmWalk<{R}, {TH}, {TW}, {same}> {{
-    static constexpr bool kAvailable = true;
+struct AsmWalk<{R}, {TH}, {TW}, {same}, {kpl}> {{
+    static constexpr bool kReg = {reg};  // a tile of the register-weight kernel
     // {nq} positions: {nr} window rows from {r0}, {nc} columns from {c0}
     static constexpr int kRow0 = {r0}, kCol0 = {c0}, kRows = {nr}, kCols = {nc}, kPositions = {nq}, kChunks = {epl};
     // leaves of at most {maxf} FMAs, stride {stride} bytes
@@ -167,11 +172,12 @@ struct AsmWalk<{R}, {TH}, {TW}, {same}> {{
             {asm}
             : {outs}
             : {ins}
-            : "s70", "s71", "s72", "s73", "s74", "s75", "scc");
+            : "s44", "s45", "s46", "s47", "s48", "s49", "scc");
     }}
 }};
 '''.format(R=R, TH=TH, TW=TW, same=same, epl=epl, nq=nq, maxf=maxf, stride=stride, na=na, nw=nw, asm=asm, outs=outs,
-           ins=ins, r0=pos[0][0], c0=pos[0][1], nr=pos[-1][0] - pos[0][0] + 1, nc=pos[-1][1] - pos[0][1] + 1)
+           ins=ins, kpl=kpl,
+           reg="true" if kpl == 1 and (R, TH, TW, same) in WALK_TILES else "false", r0=pos[0][0], c0=pos[0][1], nr=pos[-1][0] - pos[0][0] + 1, nc=pos[-1][1] - pos[0][1] + 1)
 
 
 
@@ -191,13 +197,13 @@ struct AsmDispatch {
 ''']
     for R, TH, TW in SHAPES:
         parts.append(specialisation(R, TH, TW))
-    parts.append('''template <int R, int TH, int TW, int SAME>
+    parts.append('''template <int R, int TH, int TW, int SAME, int KPL = 1>
 struct AsmWalk {
-    static constexpr bool kAvailable = false;
+    static constexpr bool kReg = false;
 };
 
 ''')
-    for tile in WALK_TILES:
+    for tile in WALK_TILES + RING_TILES:
         parts.append(walk_specialisation(*tile))
     parts.append('''}  // namespace tile
 }  // namespace isc

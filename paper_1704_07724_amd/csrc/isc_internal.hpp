@@ -226,10 +226,12 @@ int64_t sparse_fring_max_groups(const SparseShape &sh);
 // Expected time (ms) of the register-weight kernel's launch for a shape: the
 // larger of two lines base + slope * (input density); false where another
 // kernel takes the shape.
-struct RegTime {
+struct KernelTime {
     double base[2], slope[2];
 };
-bool sparse_reg_time_model(const SparseShape &sh, RegTime *t);
+bool sparse_reg_time_model(const SparseShape &sh, KernelTime *t);
+// The same for the filter-ring kernel.
+bool sparse_ring_time_model(const SparseShape &sh, KernelTime *t);
 // Upper bound of the workgroups of the on-the-fly kernels' launch for a
 // shape (the census slots their epilogue may write).
 int64_t sparse_fused_max_groups(const SparseShape &sh);

@@ -2,7 +2,7 @@
 #include "sparse_fring.hpp"
 
 #include <algorithm>
-#include <cstdlib>
+#include <cstring>
 
 namespace isc {
 namespace fring {
@@ -22,68 +22,83 @@ void tiles_for(int R, const TileChoice **t, int *n) {
     }
 }
 
-// Relative cost of a tile on a shape, with the input assumed 90 % zero (the
-// regime the sparse path is for).  Per channel and wavefront: the
-// multiply-adds (taps per nonzero times maps per lane), the bytes the CU's
-// LDS moves (the wavefront's weight reads and its share of the stage's
-// direct loads) at 128 bytes a clock, the scan's scalar work per window
-// position and per nonzero, and a fixed part (wait, barrier, ballot);
-// windows are counted inside the map only.  Summed over the launch's
-// wavefronts and divided over the CUs, less 15 % for every wavefront a SIMD
-// holds beyond two (more latency hidden), and rounded up to whole
-// rounds of resident workgroups.  The weights are those that ranked the
-// compiled tiles on AlexNet conv2-5 and the inception 3x3 branch as measured.
-double tile_cost(const SparseShape &sh, const TileChoice &t) {
-    const double density = 0.1;
+// Modelled cycles of the kernel on a tile with its channels over `phases`
+// wavefronts, at an input density: the larger of two lines, plus a fixed
+// part.  A CU's w workgroups put a wavefront on each SIMD.  They are bound by
+// issue (per wavefront and channel 100 cycles, 50 a ballot, 3 a weight; per
+// nonzero its FMAs at 4 cycles and 15 more) or by one wavefront's chain of
+// jumps (150 cycles a nonzero beside its FMAs), and a third of a workgroup's
+// duration passes at the end with CUs running dry, which is what more
+// phases, hence more and shorter workgroups, are for: AlexNet conv2 on 9 x 9
+// tiles takes 286 / 250 / 243 us on 1 / 2 / 4 phases (the model 283 / 250 /
+// 240), the inception 3x3 branch on 7 x 14 117 / 93 / 99 (130 / 98 / 93), at
+// batch 1 on 2 x 14 48 / 28 / 17.
+struct RingCost {
+    double issue0, issue1, chain0, chain1;  // issue0 + issue1 * density, chain0 + chain1 * density
+    double at(double d) const { return std::max(issue0 + issue1 * d, chain0 + chain1 * d); }
+};
+
+RingCost ring_cost(const SparseShape &sh, const TileChoice &t, int phases) {
+    const int64_t bands = (sh.Ho + t.th - 1) / t.th, ctiles = (sh.Wo + t.tw - 1) / t.tw;
     const int64_t kw = static_cast<int64_t>(kLanes) * t.kpl;
-    const int64_t kgroups = (sh.K + kw - 1) / kw;
-    const int64_t ntiles = static_cast<int64_t>(sh.N) * ((sh.Ho + t.th - 1) / t.th) * ((sh.Wo + t.tw - 1) / t.tw);
-    const int64_t wgs = (ntiles + t.nw - 1) / t.nw * kgroups;
-    const int wrows = t.th + sh.R - 1, wcols = t.tw + sh.S - 1;
-    const double win_in = static_cast<double>(std::min(wrows, sh.H)) * std::min(wcols, sh.W);
-    const double useful = static_cast<double>(std::min(t.th, sh.Ho)) * std::min(t.tw, sh.Wo);
-    const double taps = std::min<double>(sh.R * sh.S, useful * sh.R * sh.S / win_in);
-    const double nz = density * win_in;
-    const double fma = nz * taps * t.kpl;
-    const double scan = 0.55 * wrows * wcols + 10.0 * nz;
-    const double wbytes = 4.0 * sh.R * sh.S * kw;
-    const int epl = (wrows * wcols + kLanes - 1) / kLanes;
-    const double slot = wbytes + 256.0 * t.nw * epl;
-    const double lds = (wbytes + slot / t.nw) / 128.0;
-    const double per = fma + lds + scan + 60.0;
-    const int regs = t.th * t.tw * t.kpl + sh.R * sh.S * t.kpl + 30;
-    const int wps = std::min(8, 512 / ((regs + 7) / 8 * 8));  // wavefronts per SIMD
-    const int64_t per_cu =
-        std::max<int64_t>(1, std::min<int64_t>(4 * wps / t.nw, static_cast<int64_t>(2 * kLdsMax / (2.0 * slot))));
-    const double rounds = static_cast<double>(wgs) / (256.0 * per_cu);
-    const double fill = rounds / std::ceil(rounds);
-    return static_cast<double>(wgs) * t.nw * sh.C * per / (1.0 + 0.15 * std::max(0, wps - 2)) / fill;
+    const int64_t per = t.nw / phases;
+    const int64_t wgs = (sh.N * bands * ctiles + per - 1) / per * ((sh.K + kw - 1) / kw);
+    const double w = std::max(1.0, static_cast<double>(wgs) / 256.0);
+    const int occ = fring_waves_per_simd(sh.R, t.kpl, t.th, t.tw);
+    const double resident = std::min<double>(occ, std::ceil(w));
+    // input rows and columns a tile's window holds on average: all but the
+    // padding and what the last tile reaches past the map
+    const int64_t inr = bands * (t.th + sh.R - 1) - sh.P - (bands * t.th - sh.Ho + sh.P);
+    const int64_t inc = ctiles * (t.tw + sh.R - 1) - sh.P - (ctiles * t.tw - sh.Wo + sh.P);
+    const double rows = std::min<double>(sh.H, std::max(1.0, static_cast<double>(inr) / bands));
+    const double cols = std::min<double>(sh.W, std::max(1.0, static_cast<double>(inc) / ctiles));
+    const double fmas =
+        t.kpl * static_cast<double>(std::min(t.th, sh.Ho)) * std::min(t.tw, sh.Wo) * sh.R * sh.R / (rows * cols);
+    const int chunks = ((t.th + sh.R - 1) * (t.tw + sh.R - 1) + tile::kWalkChunk - 1) / tile::kWalkChunk;
+    const double chan = (sh.C + phases - 1) / phases;
+    const double i0 = 100.0 + 50.0 * chunks + 3.0 * sh.R * sh.R * t.kpl;
+    const double i1 = rows * cols * std::max(28.0, 15.0 + 4.0 * fmas);
+    const double c0 = 300.0 + 50.0 * chunks, c1 = rows * cols * (150.0 + 4.0 * fmas);
+    const double fixed = 3000.0 + 40.0 * w * t.th * t.tw * t.kpl;
+    const double iw = chan * (w + (w > 1.0 ? 0.35 * resident : 0.0)), cw = chan * std::max(1.0, w / occ);
+    return {iw * i0 + fixed, iw * i1, cw * c0 + fixed, cw * c1};
 }
 
-// The cheapest compiled tile that fits the register budget, restricted to a
-// caller's maps_per_lane / rows / cols when those name a compiled tile.
-bool fring_choose(const SparseShape &sh, TileChoice *tc) {
+constexpr double kPlanDensity = 0.1;  // the paper's layers are 0.9 to 0.95 sparse
+
+// The cheapest compiled tile and number of phases, restricted to a caller's
+// maps_per_lane / rows / cols / waves when those name a compiled tile, and
+// to a caller's phases (1, 2 or 4; 1 where only the tile is named).
+bool choose(const SparseShape &sh, TileChoice *tc, int *phases) {
+    if (sh.T != 1 || sh.R != sh.S || !(sh.R == 1 || sh.R == 3 || sh.R == 5)) return false;
+    // the kernel addresses a plane and a channel's weights by 31-bit byte offsets
+    const int64_t kp = (sh.K + kLanes - 1) / kLanes * static_cast<int64_t>(kLanes);
+    if (static_cast<int64_t>(sh.H) * sh.W * 4 >= (1ll << 31) || kp * sh.R * sh.S * 4 >= (1ll << 31)) return false;
     const TileChoice *tiles;
     int n;
     tiles_for(sh.R, &tiles, &n);
     for (int pass = 0; pass < 2; ++pass) {
         const bool forced = pass == 0;
         if (forced && sh.tu.maps_per_lane <= 0 && sh.tu.rows <= 0 && sh.tu.cols <= 0 && sh.tu.waves <= 0) continue;
+        const bool named = sh.tu.phases == 1 || sh.tu.phases == 2 || sh.tu.phases == 4;
+        const int fix = named ? sh.tu.phases : (forced ? 1 : 0);
         bool found = false;
         double best = 0.0;
         for (int i = 0; i < n; ++i) {
             const TileChoice &t = tiles[i];
-            if (t.nw != 4 && !(forced && sh.tu.waves == t.nw)) continue;  // eight only when asked for
             if (forced && ((sh.tu.maps_per_lane > 0 && t.kpl != sh.tu.maps_per_lane) ||
                            (sh.tu.rows > 0 && t.th != sh.tu.rows) || (sh.tu.cols > 0 && t.tw != sh.tu.cols) ||
                            (sh.tu.waves > 0 && t.nw != sh.tu.waves)))
                 continue;
-            if (!fring_fits(sh.R, t.kpl, t.th, t.tw)) continue;
-            const double c = tile_cost(sh, t);
-            if (!found || c < best) {
-                *tc = t;
-                best = c;
-                found = true;
+            for (int ph : {1, 2, 4}) {
+                if (fix > 0 && fix != ph) continue;
+                const double c = ring_cost(sh, t, ph).at(kPlanDensity);
+                if (!found || c < best) {
+                    *tc = t;
+                    *phases = ph;
+                    best = c;
+                    found = true;
+                }
             }
         }
         if (found) return true;
@@ -91,13 +106,41 @@ bool fring_choose(const SparseShape &sh, TileChoice *tc) {
     return false;
 }
 
+// The choice of a shape, asked for several times in the course of one call:
+// the calling thread's last answer is kept beside the shape and the
+// overrides it was computed from.
+bool fring_choose(const SparseShape &sh, TileChoice *tc, int *phases) {
+    struct Last {
+        SparseShape sh;
+        TileChoice tc;
+        int phases;
+        int ok = -1;
+    };
+    static thread_local Last last;
+    if (last.ok < 0 || std::memcmp(&last.sh, &sh, sizeof sh) != 0) {
+        last.ok = choose(sh, &last.tc, &last.phases);
+        last.sh = sh;
+    }
+    if (last.ok) {
+        *tc = last.tc;
+        *phases = last.phases;
+    }
+    return last.ok != 0;
+}
+
+int64_t ring_groups(const SparseShape &sh, const TileChoice &t, int phases) {
+    const int64_t ntiles = static_cast<int64_t>(sh.N) * ((sh.Ho + t.th - 1) / t.th) * ((sh.Wo + t.tw - 1) / t.tw);
+    const int per = t.nw / phases;
+    return (ntiles + per - 1) / per * ((sh.K + kLanes * t.kpl - 1) / (kLanes * t.kpl));
+}
+
 }  // namespace
 }  // namespace fring
 
 bool sparse_fring_applies(const SparseShape &sh) {
-    if (sh.T != 1 || sh.R != sh.S || !(sh.R == 1 || sh.R == 3 || sh.R == 5)) return false;
     fring::TileChoice tc;
-    return fring::fring_choose(sh, &tc);
+    int phases;
+    return fring::fring_choose(sh, &tc, &phases);
 }
 
 int64_t sparse_fring_max_groups(const SparseShape &sh) {
@@ -106,22 +149,27 @@ int64_t sparse_fring_max_groups(const SparseShape &sh) {
     int n;
     tiles_for(sh.R, &tiles, &n);
     int64_t most = 0;
-    for (int i = 0; i < n; ++i) {
-        const TileChoice &t = tiles[i];
-        const int64_t ntiles =
-            static_cast<int64_t>(sh.N) * ((sh.Ho + t.th - 1) / t.th) * ((sh.Wo + t.tw - 1) / t.tw);
-        most = std::max(most, (ntiles + t.nw - 1) / t.nw * ((sh.K + kLanes * t.kpl - 1) / (kLanes * t.kpl)));
-    }
+    for (int i = 0; i < n; ++i) most = std::max(most, ring_groups(sh, tiles[i], 4));
     return most;
+}
+
+bool sparse_ring_time_model(const SparseShape &sh, KernelTime *t) {
+    using namespace fring;
+    TileChoice tc;
+    int phases;
+    if (!fring_choose(sh, &tc, &phases)) return false;
+    const RingCost c = ring_cost(sh, tc, phases);
+    constexpr double kMs = 1.0 / 2.4e6;  // a cycle at 2.4 GHz
+    *t = KernelTime{{c.issue0 * kMs, c.chain0 * kMs}, {c.issue1 * kMs, c.chain1 * kMs}};
+    return true;
 }
 
 bool sparse_fring_plan_info(const SparseShape &sh, isc_plan *out) {
     using namespace fring;
     TileChoice tc;
-    if (!sparse_fring_applies(sh) || !fring_choose(sh, &tc)) return false;
-    const int64_t ntiles = static_cast<int64_t>(sh.N) * ((sh.Ho + tc.th - 1) / tc.th) * ((sh.Wo + tc.tw - 1) / tc.tw);
-    const int64_t groups = (ntiles + tc.nw - 1) / tc.nw * ((sh.K + kLanes * tc.kpl - 1) / (kLanes * tc.kpl));
-    *out = isc_plan{ISC_KERNEL_FUSED_RING, tc.th, tc.tw, tc.kpl, 1, tc.nw, groups};
+    int phases;
+    if (!fring_choose(sh, &tc, &phases)) return false;
+    *out = isc_plan{ISC_KERNEL_FUSED_RING, tc.th, tc.tw, tc.kpl, phases, tc.nw, ring_groups(sh, tc, phases)};
     return true;
 }
 
@@ -129,7 +177,8 @@ hipError_t launch_sparse_fring(const SparseShape &sh, const float *x, const floa
                                hipStream_t s, const Epilogue &epi) {
     using namespace fring;
     TileChoice tc;
-    if (sh.T != 1 || sh.R != sh.S || !fring_choose(sh, &tc)) return hipErrorInvalidValue;
+    int phases;
+    if (!fring_choose(sh, &tc, &phases)) return hipErrorInvalidValue;
     FringArgs a{};
     a.x = x;
     a.wt = wt;
@@ -143,6 +192,7 @@ hipError_t launch_sparse_fring(const SparseShape &sh, const float *x, const floa
     if (ntiles >= (1ll << 31) - tc.nw) return hipErrorInvalidValue;
     a.ntiles = static_cast<int>(ntiles);
     a.kgroups = (sh.K + kLanes * tc.kpl - 1) / (kLanes * tc.kpl);
+    a.phases = phases;
     a.dec = dec;
     a.epi = epi;
     switch (sh.R) {

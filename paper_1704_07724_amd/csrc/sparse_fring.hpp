@@ -2,29 +2,38 @@
 // units that define ISC_FRING_INSTANTIATE, the kernel and its launchers).
 //
 // ISC steps 1-3 (Sec. "Sparse Convolution") in one launch for stride-1
-// convolutions with square 1x1, 3x3 or 5x5 filters whose filter does not fit
-// in LDS (many input or output maps: AlexNet conv2-5, an inception 3x3
-// branch): the input is compacted on the fly as in the filter-resident kernel
-// (sparse_fused.hip), and the filter is streamed through LDS.
+// convolutions with square 1x1, 3x3 or 5x5 filters whose output is wider than
+// 16 columns or whose filter does not fit in LDS (AlexNet conv2, an
+// inception 3x3 branch): the input is compacted on the fly as in the
+// register-weight kernel (sparse_fused.hpp), and the filter is streamed
+// through LDS.
 //
 // The output of every image is cut into TH x TW tiles, numbered image by
-// image, row band by row band; wavefront w of workgroup b owns tile 4b + w
-// (any image: the four wavefronts share only the channel's weights), with
-// 64*KPL output maps in registers (tile machinery in sparse_tile.hpp).  The
-// flat tile list leaves no wavefront idle on a ragged last band, except in
-// the launch's last workgroup.  Input channels go in order through a ring
-// of NBUF stages: stage c holds channel c's R*S*64*KPL weights (from the
-// K-contiguous repacked filter) and each wavefront's input window of the
-// channel -- (TH+R-1) rows x (TW+S-1) columns in leaf-key order, padding
-// read as zero -- all brought in by direct global->LDS loads.  No register
-// is the target of a load in flight, so the only waits are the kernel's own:
-// stages are issued NBUF-1 channels ahead and each channel waits for exactly
-// the stage it consumes, then one barrier.  Per channel a
-// wavefront reads the weights into registers, takes a ballot of the zero test
-// over its window and scans the window statically (walk_scan): every set
-// position runs the straight-line block of its (row, column).  Each lane
-// finally stores its accumulators to NCHW (step 3).  Summation order per
-// output is fixed (channels in order, window order within a channel), so
+// image, row band by row band, and each tile's input channels are dealt to
+// `phases` wavefronts of one workgroup.  A wavefront holds 64*KPL output maps
+// of its tile in registers and is on its own until the end: its LDS slot
+// takes the next channel's R*S*64*KPL weights (from the K-contiguous repacked
+// filter) and its window of that channel by direct global->LDS loads while
+// it walks the current channel, whose weights and window it has read into
+// registers; no barrier per channel, so a wavefront with many nonzeros
+// delays nobody.  The walk is AsmWalk's: from nonzero to nonzero by computed
+// jumps.  At the end the phases' tiles are summed through LDS in order and
+// stored to NCHW (step 3) a few rows at a time, consecutive lanes on
+// consecutive columns.
+//
+// Before, the four wavefronts of a workgroup shared each channel's stage of
+// an LDS ring behind a barrier and scanned their windows statically, at two
+// wavefronts per SIMD (100 weights and 108 accumulators): AlexNet conv2, 510
+// us, spent most of them waiting for the slowest wavefront of each channel
+// and for the weights' LDS reads.  One map per lane on a large tile reads a
+// quarter of the weights per nonzero (9 x 9: 16 nonzeros a channel, 15 FMAs
+// each) at four wavefronts per SIMD, and the workgroup's L1 serves the
+// wavefronts' separate reads.  Kernel alone: AlexNet conv2 at batch 128 510 ->
+// 243 us (43 TFLOP/s on nonzero MACs of 78.6), batch 1 163 -> 28; the
+// inception 3x3 branch 204 -> 93, batch 1 114 -> 17; 64 -> 192 maps of 56 x 56,
+// 3x3, batch 32 260 -> 102.
+// Summation order per output is fixed (channels in
+// order within a phase, window order within a channel, phases in order), so
 // results are deterministic.
 #pragma once
 
@@ -45,37 +54,28 @@ struct FringArgs {
     int rtiles;       // row bands per image, ceil(Ho / TH)
     int ntiles;       // N * rtiles * ctiles
     int kgroups;      // groups of 64 * KPL output maps
+    int phases;       // wavefronts that share a tile's channels (1, 2 or 4)
     Decision dec;
     Epilogue epi;     // rectifier and census of y
 };
 
 // A register tile: KPL maps per lane, TH x TW outputs, so TH * TW * KPL
-// accumulators and R*S*KPL weights per lane; NW wavefronts per workgroup
-// share each stage of the ring (4: two workgroups per CU, each with half
-// of the LDS; 8: one workgroup per CU with all of it, so a deeper ring and
-// half the weight traffic per wavefront).
+// accumulators and R*S*KPL weights per lane; NW wavefronts per workgroup.
 struct TileChoice {
     int kpl, th, tw, nw;
 };
 
-constexpr int kMaxAcc = 160;      // accumulators per lane
-constexpr int kMaxRegs = 216;     // accumulators + weights per lane
-
-constexpr bool fring_fits(int RS, int KPL, int TH, int TW) {
-    return TH * TW * KPL <= kMaxAcc && TH * TW * KPL + RS * RS * KPL <= kMaxRegs;
+// Wavefronts a SIMD holds of a tile's kernel: accumulators, weights and about
+// 18 registers of window values, offsets and addresses, of 512.
+constexpr int fring_waves_per_simd(int RS, int KPL, int TH, int TW) {
+    const int regs = TH * TW * KPL + RS * RS * KPL + 18;
+    return regs <= 64 ? 8 : (regs <= 80 ? 6 : (regs <= 96 ? 5 : (regs <= 128 ? 4 : (regs <= 170 ? 3 : 2))));
 }
 
-// The tiles compiled for each filter size, the choice's candidates.  Tall
-// tiles feed every scanned nonzero to more outputs (R x S filters: up to
-// TH*TW*R*S / ((TH+R-1)(TW+S-1)) taps, times KPL maps per lane), which is
-// what the scan's scalar work per nonzero is paid against; narrow ones fit
-// the 13-, 14-, 27- and 28-column maps without ragged edges.
-constexpr TileChoice kTiles5[] = {{4, 4, 7, 4}, {4, 3, 9, 4}, {4, 1, 28, 4}, {2, 2, 28, 4}, {2, 1, 28, 4},
-                                  {1, 2, 28, 4}, {4, 1, 16, 4}, {2, 2, 16, 4}, {1, 2, 16, 4}, {4, 4, 7, 8}};
-constexpr TileChoice kTiles3[] = {{6, 2, 13, 4}, {4, 2, 16, 4}, {6, 1, 16, 4}, {2, 2, 28, 4}, {2, 1, 28, 4},
-                                  {4, 1, 28, 4}, {1, 2, 28, 4}, {1, 2, 16, 4}, {2, 4, 16, 4}, {2, 2, 28, 8}};
-constexpr TileChoice kTiles1[] = {{6, 2, 13, 4}, {6, 1, 16, 4}, {4, 2, 16, 4}, {4, 1, 28, 4}, {2, 2, 28, 4},
-                                  {1, 2, 16, 4}};
+// The tiles compiled for each filter size, the choice's candidates.
+constexpr TileChoice kTiles5[] = {{1, 9, 9, 4}, {1, 7, 14, 4}, {1, 5, 14, 4}, {1, 3, 14, 4}, {2, 1, 28, 4}};
+constexpr TileChoice kTiles3[] = {{1, 7, 14, 4}, {1, 4, 14, 4}, {1, 2, 14, 4}, {2, 4, 14, 4}};
+constexpr TileChoice kTiles1[] = {{1, 7, 14, 4}, {1, 4, 14, 4}, {1, 2, 14, 4}, {2, 4, 14, 4}};
 
 // Launchers of the kernels of one filter size (sparse_fring_r{1,3,5}.hip).
 hipError_t launch_r1(const FringArgs &a, const TileChoice &tc, hipStream_t s);
@@ -92,57 +92,39 @@ namespace {
 
 template <int RS_, int KPL, int TH, int TW, int NW>
 struct FringShape {
-    using T = tile::Shape<RS_, RS_, KPL, TH, TW>;
-    static constexpr int kWaves = NW;
-    static constexpr int RS2 = RS_ * RS_;
-    static constexpr int CHF = RS2 * T::KW;                  // floats of one channel's weights
-    static constexpr int NDW = (CHF + 255) / 256;            // 1 KB direct-to-LDS blocks
-    static constexpr int SLOT4 = NDW * kLanes;               // float4 per ring slot
-    static constexpr size_t SLOTB = sizeof(float4) * SLOT4;  // bytes of one stage's weights
-    static constexpr int WIN4 = NW * T::EPL * kLanes / 4;    // float4 of its windows
-    static constexpr size_t WINB = sizeof(float4) * WIN4;
-    static constexpr int DPW = (NDW + NW - 1) / NW;          // weight blocks per wavefront per stage
-    static constexpr int VPS = DPW + T::EPL;                 // vector-memory operations per stage
-    // stages: up to 4 for slots of <= 16 KB, 3 for <= 32 KB, else 2, within
-    // the workgroup's share of LDS (half of it for four wavefronts, so that
-    // two workgroups share a CU) and few enough that the wait for the stage
-    // consumed fits the vmcnt field.  Deeper rings measured slower: the LDS
-    // they take costs resident workgroups (six stages for the inception 3x3
-    // branch on 1 x 28 tiles: 0.205 -> 0.284 ms)
-    static constexpr size_t BUDGET = NW == 4 ? kLdsMax / 2 : kLdsMax;
-    static constexpr int NPREF = SLOTB <= 16384 ? 4 : (SLOTB <= 32768 ? 3 : 2);
-    static constexpr int NFIT = static_cast<int>(BUDGET / (SLOTB + WINB));
-    static constexpr int NVM = 63 / VPS + 2;
-    static constexpr int NCAP = NFIT < NVM ? NFIT : NVM;
-    static constexpr int NBUF = NPREF < NCAP ? NPREF : NCAP;
-    static_assert(NBUF >= 2, "ring needs two stages");
-    static constexpr size_t lds = NBUF * (SLOTB + WINB);
+    using Walk = tile::AsmWalk<RS_, TH, TW, 0, KPL>;
+    static constexpr int RS2 = RS_ * RS_, KW = kLanes * KPL;
+    static constexpr int CHF = RS2 * KW;           // floats of one channel's weights
+    static constexpr int NDW = (CHF + 255) / 256;  // 1 KB direct-to-LDS blocks
+    static constexpr int EPL = Walk::kChunks;
+    // a wavefront's slot (floats): the channel's weights [R*S][KW] padded to
+    // whole blocks, then its window, one word per lane and ballot; at the end
+    // RC rows of its tile, [position][map] with a padded pitch
+    static constexpr int PITCH = KW + 1;
+    static constexpr int LOADF = NDW * 256 + EPL * kLanes;
+    static constexpr int RFIT = LOADF / (TW * PITCH) < kLanes / TW ? LOADF / (TW * PITCH) : kLanes / TW;
+    static constexpr int RC = RFIT < 1 ? 1 : (RFIT < TH ? RFIT : TH);
+    static constexpr int SLOTF = ((LOADF > RC * TW * PITCH ? LOADF : RC * TW * PITCH) + 3) / 4 * 4;
+    static constexpr size_t lds = sizeof(float) * SLOTF * NW;
 };
 
 template <int RS_, int KPL, int TH, int TW, int NW>
-__global__ __launch_bounds__(NW * kLanes)
+__global__ __launch_bounds__(NW * kLanes, fring_waves_per_simd(RS_, KPL, TH, TW))
 void sparse_conv_fring_kernel(FringArgs a) {
     using SH = FringShape<RS_, KPL, TH, TW, NW>;
-    constexpr int kWaves = NW;
-    using T = typename SH::T;
-    constexpr int KW = T::KW, NDW = SH::NDW, NBUF = SH::NBUF, DPW = SH::DPW, EPL = T::EPL;
-
-    // ring of NBUF slots, each one channel's weights [R*S][KW] (k = kbase +
-    // lane*KPL + j) padded to whole 1 KB blocks, then the wavefronts' input
-    // windows [wavefront][q][lane].  Static, so that the compiler can tell
-    // the slot being read from the slots being filled, and the kernel's only
-    // LDS variable: with a second one the compiler makes every read of the
-    // ring wait for all loads into LDS in flight, prefetched stages included.
-    __shared__ float4 wring[NBUF][SH::SLOT4 + SH::WIN4];
+    using Walk = typename SH::Walk;
+    constexpr int RS2 = SH::RS2, KW = SH::KW, NDW = SH::NDW, EPL = SH::EPL, TP = TH * TW;
+    constexpr int CH = tile::kWalkChunk, NQ = Walk::kPositions;
+    __shared__ __align__(16) float slots[NW][SH::SLOTF];
 
     const int lane = threadIdx.x & (kLanes - 1);
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kLanes);
     const int kg = blockIdx.x % a.kgroups;
-    // this wavefront's tile (past the last tile: the last tile's addresses,
-    // nothing counted, nothing stored)
-    const int tile = (blockIdx.x / a.kgroups) * kWaves + wave;
-    const bool rows_ok = tile < a.ntiles;
-    int t = rows_ok ? tile : a.ntiles - 1;
+    const int phase = wave % a.phases;
+    // this wavefront's tile (past the last one: nothing walked, nothing stored)
+    const int tile = static_cast<int>(blockIdx.x / a.kgroups) * (NW / a.phases) + wave / a.phases;
+    const bool has = tile < a.ntiles;
+    int t = has ? tile : 0;
     const int ct = t % a.ctiles;
     t /= a.ctiles;
     const int band = t % a.rtiles;
@@ -150,121 +132,140 @@ void sparse_conv_fring_kernel(FringArgs a) {
     const int oy0 = band * TH;
     const int ox0 = ct * TW;
     const int kbase = kg * KW;
-    const int C = a.C, H = a.H, W = a.W, P = a.P, Kp = a.Kp;
-    const int tw = min(TW, a.Wo - ox0);
+    const int C = a.C, H = a.H, W = a.W, P = a.P;
     const size_t HW = static_cast<size_t>(H) * W;
     const float *x_n = a.x + static_cast<size_t>(n) * C * HW;
+    const int ncw = has && phase < C ? (C - 1 - phase) / a.phases + 1 : 0;
+    float *slot = slots[wave];
 
-    // lane l of register q holds window element e = q*64 + l in leaf-key
-    // order, e = wy * WCOLS + xp: input row oy0 - P + wy, column ox0 - P + xp.
-    // Elements outside the map (padding) or past the window read the plane's
-    // first element and never count as nonzero.
+    // byte offset in the channel's plane of position q * CH + lane of the
+    // walk; lanes without one (padding, and lane CH of a ballot, whose bit is
+    // the walk's sentinel) an offset past the plane, which reads as zero
     int xoff[EPL];
-    bool inwin[EPL];
 #pragma unroll
     for (int q = 0; q < EPL; ++q) {
-        const int e = q * kLanes + lane;
-        const int wy = e / T::WCOLS;
-        const int y = oy0 - P + wy, xx = ox0 - P + (e - wy * T::WCOLS);
-        inwin[q] = rows_ok && e < T::WROWS * T::WCOLS && y >= 0 && y < H && xx >= 0 && xx < W;
-        xoff[q] = inwin[q] ? y * W + xx : 0;
+        const int e = q * CH + lane;
+        const int wy = e / Walk::kCols;
+        const int y = oy0 - P + wy, xx = ox0 - P + (e - wy * Walk::kCols);
+        const bool in = lane < CH && e < NQ && y >= 0 && y < H && xx >= 0 && xx < W;
+        xoff[q] = in ? (y * W + xx) * static_cast<int>(sizeof(float)) : tile::kPastPlane;
     }
+    // byte offset in a channel's weights of this lane's 16 bytes of block d
+    // (blocks past the last tap repeat it)
+    int woff[NDW];
+#pragma unroll
+    for (int d = 0; d < NDW; ++d) {
+        const int f = d * 256 + lane * 4;
+        const int tap = min(f / KW, RS2 - 1);
+        woff[d] = (tap * a.Kp + min(kbase + f % KW, a.Kp - 4)) * static_cast<int>(sizeof(float));
+    }
+    const int plane_bytes = H * W * static_cast<int>(sizeof(float));
+    const int chan_bytes = RS2 * a.Kp * static_cast<int>(sizeof(float));
 
-    // stage c -> slot SLOT: weights by direct global->LDS loads (every
-    // wavefront issues exactly DPW blocks and EPL window loads, so the number
-    // of vector-memory operations per stage is the same everywhere)
-    auto issue = [&](auto slot_c, int c) {
-        constexpr int SLOT = decltype(slot_c)::value;
+    // channel i of this wavefront into its slot
+    auto issue = [&](int i) {
+        const int c = phase + i * a.phases;
+        const __amdgpu_buffer_rsrc_t wres = __builtin_amdgcn_make_buffer_rsrc(
+            const_cast<float *>(a.wt) + static_cast<size_t>(c) * RS2 * a.Kp, 0, chan_bytes, tile::kBufferFormat);
 #pragma unroll
-        for (int i = 0; i < DPW; ++i) {
-            const int d = min(wave + i * kWaves, NDW - 1);
-            const int f = d * 256 + lane * 4;  // float offset in the slot
-            int tap = f / KW;
-            const int koff = f - tap * KW;
-            tap = min(tap, SH::RS2 - 1);       // padding of the last block
-            const int k = min(kbase + koff, Kp - 4);
-            const float *src = a.wt + (static_cast<size_t>(c) * SH::RS2 + tap) * Kp + k;
-            tile::load_lds16(src, &wring[SLOT][d * kLanes]);
-        }
-        const float *plane = x_n + static_cast<size_t>(c) * HW;
+        for (int d = 0; d < NDW; ++d) tile::buffer_lds16(wres, slot + d * 256, woff[d]);
+        const __amdgpu_buffer_rsrc_t xres = __builtin_amdgcn_make_buffer_rsrc(
+            const_cast<float *>(x_n) + static_cast<size_t>(c) * HW, 0, plane_bytes, tile::kBufferFormat);
 #pragma unroll
-        for (int q = 0; q < EPL; ++q)
-            tile::load_lds4(plane + xoff[q], reinterpret_cast<float *>(&wring[SLOT][SH::SLOT4]) + (wave * EPL + q) * kLanes);
+        for (int q = 0; q < EPL; ++q) tile::buffer_lds4(xres, slot + NDW * 256 + q * kLanes, xoff[q]);
     };
-
-    // prologue: stages 0 .. NBUF-2 in flight before the decision is read
-    // (past the last channel the last channel is loaded again, keeping the
-    // per-stage operation count fixed)
-    tile::static_for<0, NBUF - 1>([&](auto sl) { issue(sl, min(decltype(sl)::value, C - 1)); });
+    if (ncw > 0) issue(0);
     const bool run = decision_gate(a.dec, 1u);
     if (!run) {
         __builtin_amdgcn_s_waitcnt(0);  // no load into LDS may outlive the workgroup
         return;
     }
 
-    tile::Acc<T> acc;
+    float acc[TP * KPL];
 #pragma unroll
-    for (int y = 0; y < TH; ++y)
-#pragma unroll
-        for (int x = 0; x < TW; ++x)
-#pragma unroll
-            for (int j = 0; j < KPL; ++j) acc[y][x][j] = 0.0f;
+    for (int p = 0; p < TP * KPL; ++p) acc[p] = 0.0f;
 
-    // per channel: wait for its stage and the barrier, issue the stage NBUF-1
-    // channels ahead, then read the channel's weights and window (LDS ->
-    // registers) into one set of registers, so that the scan (most of the
-    // code) is inlined once
-    float cur[EPL];
-    tile::Wts<T> w;
 #pragma unroll 1
-    for (int c = 0; c < C; ++c) {
-        tile::static_for<0, NBUF>([&](auto sl) {
-            constexpr int B = decltype(sl)::value;
-            if (c % NBUF == B) {
-                // stage c complete for every wavefront; everyone is done with
-                // stage c - 1, whose slot is refilled next
-                tile::wait_vm_and_barrier<(NBUF - 2) * SH::VPS>();
-                issue(std::integral_constant<int, (B + NBUF - 1) % NBUF>{}, min(c + NBUF - 1, C - 1));
-                tile::load_weights<T>(reinterpret_cast<const float *>(&wring[B][0]), lane, w);
-                const float *win = reinterpret_cast<const float *>(&wring[B][SH::SLOT4]) + wave * EPL * kLanes + lane;
+    for (int i = 0; i < ncw; ++i) {
+        float cur[EPL], w[RS2 * KPL];
+        tile::wait_vm<0, true>();  // this channel's loads into the slot have landed
+        asm volatile("" ::: "memory");
 #pragma unroll
-                for (int q = 0; q < EPL; ++q) cur[q] = win[q * kLanes];
-                tile::wait_lgkm0();
-            }
-        });
+        for (int q = 0; q < EPL; ++q) cur[q] = slot[NDW * 256 + q * kLanes + lane];
+#pragma unroll
+        for (int r = 0; r < RS2; ++r)
+#pragma unroll
+            for (int j = 0; j < KPL; ++j) w[r * KPL + j] = slot[r * KW + lane * KPL + j];
+        // read into registers before the next channel's loads overwrite them
+        asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+        if (i + 1 < ncw) issue(i + 1);
         unsigned long long mask[EPL];
 #pragma unroll
-        for (int q = 0; q < EPL; ++q) mask[q] = __ballot(inwin[q] && (__float_as_uint(cur[q]) & 0x7fffffffu) != 0u);
-        tile::walk_scan<T>(mask, cur, acc, w);
+        for (int q = 0; q < EPL; ++q) {
+            constexpr int kLast = NQ - (EPL - 1) * CH;  // positions of the last ballot
+            mask[q] = __ballot((__float_as_uint(cur[q]) & 0x7fffffffu) != 0u) | (1ull << (q + 1 < EPL ? CH : kLast));
+        }
+        Walk::run(mask, cur, acc, w);
     }
-    __builtin_amdgcn_s_waitcnt(0);  // no load into LDS may outlive the workgroup
 
-    // step 3: each lane stores its accumulators to NCHW
+    // step 3: RC rows at a time, every wavefront writes them to its slot as
+    // [position][map] and the tile's wavefronts share the sums and stores:
+    // consecutive lanes on consecutive positions of one map
+    constexpr int RC = SH::RC, PITCH = SH::PITCH;
+    const size_t plane_out = static_cast<size_t>(a.Ho) * a.Wo;
+    const int cols = min(TW, a.Wo - ox0);
+    const int kcnt = min(KW, a.K - kbase);
+    const int w0 = wave - phase;  // the tile's first wavefront
+    const int relu = a.epi.relu;
     uint32_t cnt = 0;
-    if (rows_ok) {
-        const size_t plane_out = static_cast<size_t>(a.Ho) * a.Wo;
-        float *yrow = a.y + static_cast<size_t>(n) * a.K * plane_out + static_cast<size_t>(oy0) * a.Wo + ox0;
-        cnt = tile::store_tile<T>(acc, yrow, plane_out, a.Wo, kbase, lane, a.K, a.Ho - oy0, tw, a.epi.relu);
-    }
+    tile::static_for<0, (TH + RC - 1) / RC>([&](auto pc) {
+        constexpr int R0 = decltype(pc)::value * RC, R1 = R0 + RC < TH ? R0 + RC : TH;
+        if (a.phases > 1) {
+            if constexpr (R0 > 0) __syncthreads();  // the previous rows are read
+        } else {
+            asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+        }
+#pragma unroll
+        for (int p = R0 * TW; p < R1 * TW; ++p)
+#pragma unroll
+            for (int j = 0; j < KPL; ++j) slot[(p - R0 * TW) * PITCH + lane * KPL + j] = acc[p * KPL + j];
+        if (a.phases > 1) __syncthreads();
+        else asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+        const int rows = min(R1 - R0, a.Ho - oy0 - R0);
+        if (!has || rows <= 0) return;
+        // lane i of the tile's phases * 64: position i % npos of the rows,
+        // every ostep-th map from i / npos
+        const int npos = rows * cols;
+        const int id = phase * kLanes + lane;
+        const int ostep = a.phases * kLanes / npos;
+        const int k0 = id / npos;
+        const int pos = id - k0 * npos;
+        const int oy = pos / cols, ox = pos - oy * cols;
+        const float *src = slots[w0] + (oy * TW + ox) * PITCH;
+        float *dst = a.y + (static_cast<size_t>(n) * a.K + kbase) * plane_out +
+                     static_cast<size_t>(oy0 + R0 + oy) * a.Wo + ox0 + ox;
+        for (int k = k0 < ostep ? k0 : kcnt; k < kcnt; k += ostep) {
+            float sum = src[k];
+            for (int p = 1; p < a.phases; ++p) sum += src[p * SH::SLOTF + k];
+            sum = epilogue_value(sum, relu);
+            cnt += nonzero_bit(sum);
+            dst[static_cast<size_t>(k) * plane_out] = sum;
+        }
+    });
     if (a.epi.census) {
-        __syncthreads();  // every wavefront is done with the ring
-        census_commit(a.epi, cnt, reinterpret_cast<uint32_t *>(&wring[0][0]));
+        __syncthreads();  // every wavefront is done with the slots
+        census_commit(a.epi, cnt, reinterpret_cast<uint32_t *>(&slots[0][0]));
     }
 }
 
 template <int RS_, int KPL, int TH, int TW, int NW>
 hipError_t launch_fring_t(const FringArgs &a, hipStream_t s) {
-    if constexpr (!fring_fits(RS_, KPL, TH, TW)) {
-        return hipErrorInvalidValue;
-    } else {
-        using SH = FringShape<RS_, KPL, TH, TW, NW>;
-        constexpr int kWaves = NW;
-        static_assert(SH::lds <= kLdsMax, "weight ring exceeds LDS");
-        const int64_t grid = static_cast<int64_t>((a.ntiles + kWaves - 1) / kWaves) * a.kgroups;
-        if (a.epi.census && census_slots_for(grid) > a.epi.cap) return hipErrorInvalidValue;
-        sparse_conv_fring_kernel<RS_, KPL, TH, TW, NW><<<static_cast<unsigned>(grid), kWaves * kLanes, 0, s>>>(a);
-        return hipGetLastError();
-    }
+    using SH = FringShape<RS_, KPL, TH, TW, NW>;
+    static_assert(SH::lds <= 64 * 1024, "static LDS of a workgroup");
+    const int64_t grid = static_cast<int64_t>((a.ntiles + NW / a.phases - 1) / (NW / a.phases)) * a.kgroups;
+    if (a.epi.census && census_slots_for(grid) > a.epi.cap) return hipErrorInvalidValue;
+    sparse_conv_fring_kernel<RS_, KPL, TH, TW, NW><<<static_cast<unsigned>(grid), NW * kLanes, 0, s>>>(a);
+    return hipGetLastError();
 }
 
 // The launcher of table entry I of TILES when it is the chosen tile, else

@@ -12,14 +12,13 @@ namespace {
 
 int fused_tw(int Wo) { return Wo <= 8 ? 8 : (Wo <= 16 ? 16 : 28); }
 
-// Whether the register-weight kernel is compiled for the tile (the walk of
-// every other tile exists for all three filter sizes).
+// Whether the register-weight kernel is compiled for the tile.
 template <int R>
 bool reg_tile_compiled_r(RegTile t) {
     bool ok = false;
     tile::static_for<0, kRegTiles>([&](auto ic) {
         constexpr RegTile c = kRegTile[decltype(ic)::value];
-        if (c.th == t.th && c.tw == t.tw && c.same == t.same) ok = tile::AsmWalk<R, c.th, c.tw, c.same>::kAvailable;
+        if (c.th == t.th && c.tw == t.tw && c.same == t.same) ok = tile::AsmWalk<R, c.th, c.tw, c.same>::kReg;
     });
     return ok;
 }
@@ -212,13 +211,13 @@ int sparse_fused_kernel(const SparseShape &sh) {
     return sparse_fring_applies(sh) ? 5 : 0;
 }
 
-bool sparse_reg_time_model(const SparseShape &sh, RegTime *t) {
+bool sparse_reg_time_model(const SparseShape &sh, KernelTime *t) {
     using namespace fused;
     FusedPlan p;
     if (!fused_plan(sh, &p) || !p.wreg) return false;
     const RegCost c = reg_cost(sh, RegTile{p.th, p.tw, p.same});
     constexpr double kMs = 1.0 / 2.4e6;  // a cycle at 2.4 GHz
-    *t = RegTime{{(c.issue0 + c.fixed) * kMs, (c.chain0 + c.fixed) * kMs}, {c.issue1 * kMs, c.chain1 * kMs}};
+    *t = KernelTime{{(c.issue0 + c.fixed) * kMs, (c.chain0 + c.fixed) * kMs}, {c.issue1 * kMs, c.chain1 * kMs}};
     return true;
 }
 

@@ -42,11 +42,6 @@ constexpr int kMaxTile = 64;     // accumulators per lane
 constexpr int kRegSlots = kWaves / 2;  // phase-pair tiles of the register-weight kernel's reduction
 constexpr int kMinGroups = 256;  // workgroups that fill the CUs once
 constexpr int kWPitch = 64;      // maps per filter column in the repacked layout (K <= 64)
-constexpr int kPastPlane = static_cast<int>(0x80000000u);  // byte offset past any plane of the register-weight kernel
-// Word 3 of a raw buffer resource on gfx9-family chips (gfx950 included):
-// 32-bit data format, no swizzle, bounds checked against the record count.
-constexpr int kBufferFormat = 0x00020000;
-
 
 struct FusedArgs {
     const float *x;   // N x C x H x W
@@ -72,12 +67,12 @@ struct FusedPlan {
 };
 
 // Tiles of the register-weight kernel (each compiled for the filter sizes
-// whose walk gen_dispatch.py generates).
+// gen_dispatch.py lists it for).
 struct RegTile {
     int th, tw, same;  // same: which window positions the walk visits (gen_dispatch.py)
 };
 constexpr RegTile kRegTile[] = {
-    {7, 7, 2},  {8, 8, 2},  {7, 8, 2},  {4, 8, 1},  {7, 13, 1}, {5, 13, 1}, {4, 13, 1}, {3, 13, 1},
+    {7, 7, 2},  {8, 8, 2},  {4, 8, 1},  {7, 13, 1}, {5, 13, 1}, {4, 13, 1}, {3, 13, 1},
     {7, 14, 1}, {5, 14, 1}, {4, 14, 1}, {3, 14, 1}, {6, 16, 1}, {3, 16, 1}, {7, 7, 0},  {8, 8, 0},
     {4, 8, 0},  {2, 8, 0},  {7, 14, 0}, {5, 14, 0}, {3, 14, 0}, {6, 16, 0}, {3, 16, 0}, {2, 16, 0},
     {1, 16, 0}};
@@ -325,7 +320,7 @@ void sparse_conv_fused_reg_kernel(FusedArgs a) {
         const int wy = e / Walk::kCols;
         const int y = oy0 - P + Walk::kRow0 + wy, xx = e - wy * Walk::kCols - P + Walk::kCol0;
         const bool in = lane < CH && e < NQ && y >= 0 && y < H && xx >= 0 && xx < W;
-        xoff[q] = in ? (y * W + xx) * static_cast<int>(sizeof(float)) : kPastPlane;
+        xoff[q] = in ? (y * W + xx) * static_cast<int>(sizeof(float)) : tile::kPastPlane;
     }
 
     // the next channel's window and weights (loaded a channel ahead; the
@@ -338,14 +333,14 @@ void sparse_conv_fused_reg_kernel(FusedArgs a) {
     // channel's offset is one vector add, so a channel's RS2 loads take no
     // address arithmetic of their own.
     const __amdgpu_buffer_rsrc_t wres = __builtin_amdgcn_make_buffer_rsrc(
-        const_cast<float *>(a.wt), 0, C * RS2 * a.Kp * static_cast<int>(sizeof(float)), kBufferFormat);
+        const_cast<float *>(a.wt), 0, C * RS2 * a.Kp * static_cast<int>(sizeof(float)), tile::kBufferFormat);
     const int kp4 = a.Kp * static_cast<int>(sizeof(float));
     float xn[EPL];
     float wn[RS2];
     auto load_ch = [&](int i) {
         const int c = phase + min(i, ncw - 1) * cs;
         const __amdgpu_buffer_rsrc_t plane = __builtin_amdgcn_make_buffer_rsrc(
-            const_cast<float *>(x_n + static_cast<size_t>(c) * HW), 0, plane_bytes, kBufferFormat);
+            const_cast<float *>(x_n + static_cast<size_t>(c) * HW), 0, plane_bytes, tile::kBufferFormat);
 #pragma unroll
         for (int q = 0; q < EPL; ++q)
             xn[q] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(plane, xoff[q], 0, 0));
@@ -511,7 +506,7 @@ hipError_t launch_fused_rs(const FusedArgs &a, const FusedPlan &p, hipStream_t s
         hipError_t e = hipErrorInvalidValue;
         tile::static_for<0, kRegTiles>([&](auto ic) {
             constexpr RegTile t = kRegTile[decltype(ic)::value];
-            if constexpr (tile::AsmWalk<RS_, t.th, t.tw, t.same>::kAvailable) {
+            if constexpr (tile::AsmWalk<RS_, t.th, t.tw, t.same>::kReg) {
                 if (p.th == t.th && p.tw == t.tw && p.same == t.same)
                     e = launch_fused_reg_t<RS_, t.th, t.tw, t.same>(a, p.lds, s);
             }

@@ -24,6 +24,7 @@ namespace isc {
 namespace tile {
 
 constexpr int kLanes = 64;
+constexpr int kPastPlane = static_cast<int>(0x80000000u);  // byte offset past any plane
 constexpr int kWalkChunk = 63;  // window positions per ballot of AsmWalk (the next bit is its sentinel)
 
 // T_: the convolution's stride (output row oy reads input rows oy*T + r).
@@ -279,6 +280,19 @@ __device__ __forceinline__ void load_lds16(const float *src, float4 *dst) {
 // 4 bytes per lane from global memory straight into LDS at dst + 4 * lane.
 __device__ __forceinline__ void load_lds4(const float *src, float *dst) {
     __builtin_amdgcn_global_load_lds(src, dst, 4, 0, 0);
+}
+
+// Word 3 of a raw buffer resource on gfx9-family chips (gfx950 included):
+// 32-bit data format, no swizzle, bounds checked against the record count.
+constexpr int kBufferFormat = 0x00020000;
+
+// 16 or 4 bytes per lane at byte offset voff of the buffer straight into LDS
+// at dst + lane (dst wave-uniform); an offset past the buffer stores zero.
+__device__ __forceinline__ void buffer_lds16(__amdgpu_buffer_rsrc_t r, float *dst, int voff) {
+    __builtin_amdgcn_raw_ptr_buffer_load_lds(r, (__attribute__((address_space(3))) void *)dst, 16, voff, 0, 0, 0);
+}
+__device__ __forceinline__ void buffer_lds4(__amdgpu_buffer_rsrc_t r, float *dst, int voff) {
+    __builtin_amdgcn_raw_ptr_buffer_load_lds(r, (__attribute__((address_space(3))) void *)dst, 4, voff, 0, 0, 0);
 }
 
 // s_waitcnt vmcnt(VM) with lgkmcnt(0) when LGKM0, expcnt untouched.

@@ -626,6 +626,60 @@ def test_every_ring_tile(torch, isc, tile):
         assert np.array_equal(yi.cpu().numpy().astype(np.float64), oracle.conv2d_f64(xi, wi, T, P))
 
 
+@pytest.mark.parametrize("phases", [2, 4])
+@pytest.mark.parametrize("R,kpl,th,tw", [(5, 1, 9, 9), (5, 2, 1, 28), (3, 1, 7, 14), (1, 2, 4, 14)])
+def test_ring_phases(torch, isc, R, kpl, th, tw, phases):
+    """The filter-ring kernel with a tile's channels over several wavefronts
+    (fewer channels than phases, a channel count they do not divide, a last
+    workgroup with idle tiles), plain and rectified with the census."""
+    tu = {"kernel": "fused_ring", "maps_per_lane": kpl, "rows": th, "cols": tw, "phases": phases}
+    for case in [(2, 7, 19, 23, 70, 0.8), (1, 1, 9, 18, 130, 0.5), (3, 6, 28, 17, 64, 0.9)]:
+        N, C, H, W, K, sp = case
+        note("ring phases", R, kpl, th, tw, phases, case)
+        desc = isc.make_desc(N, C, H, W, K, R, R, 1, R // 2)
+        plan = isc.isc_sparse_plan(desc, tu)
+        assert (plan["kernel"], plan["rows"], plan["cols"], plan["phases"]) == ("fused_ring", th, tw, phases)
+        x, w = workloads.make_case(N, C, H, W, K, R, R, 1, R // 2, sp, seed=301 + sum(case[:5]))
+        y = isc.isc_sparse_conv_fused(to_dev(torch, x), isc.isc_repack_filter(to_dev(torch, w)), 1, R // 2,
+                                      tuning=tu).cpu().numpy()
+        assert_conv_close(y, oracle.conv2d_f64(x, w, 1, R // 2), "ring phases %s" % (case,))
+        yc = isc.census(desc)
+        z = isc.isc_conv2d_relu(to_dev(torch, x), to_dev(torch, w), 1, R // 2, path="sparse", y_census=yc,
+                                tuning=tu).cpu().numpy()
+        assert np.array_equal(z, np.maximum(y, 0))
+        assert isc.isc_census_read(yc) == (z.size, int(np.count_nonzero(z)))
+
+
+# (C, H, K, R, P, rows, cols): tall tiles of the register-weight kernel, their
+# ragged last bands, maps narrower than the tile and padding other than R/2
+REG_TALL = [(9, 13, 70, 3, 1, 7, 13), (9, 11, 70, 3, 1, 5, 13), (17, 14, 65, 3, 1, 7, 14), (3, 12, 67, 3, 1, 7, 14),
+            (9, 7, 130, 3, 1, 7, 7), (9, 5, 66, 3, 1, 7, 7), (8, 8, 66, 3, 1, 8, 8), (9, 10, 66, 3, 0, 8, 8),
+            (9, 16, 66, 3, 1, 6, 16), (9, 18, 66, 3, 0, 6, 16), (9, 7, 66, 5, 2, 7, 7),
+            (9, 8, 66, 5, 2, 4, 8), (9, 13, 66, 5, 2, 4, 13), (9, 14, 66, 5, 2, 4, 14), (9, 18, 66, 5, 1, 3, 16),
+            (20, 7, 66, 1, 0, 7, 7), (20, 14, 66, 1, 0, 7, 14), (20, 12, 66, 1, 1, 5, 14)]
+
+
+@pytest.mark.parametrize("case", REG_TALL)
+def test_register_kernel_tall_tiles(torch, isc, case):
+    C, H, K, R, P, th, tw = case
+    note("register tall", case)
+    desc = isc.make_desc(2, C, H, H, K, R, R, 1, P)
+    tu = {"kernel": "fused_reg", "rows": th, "cols": tw}
+    plan = isc.isc_sparse_plan(desc, tu)
+    assert (plan["kernel"], plan["rows"], plan["cols"]) == ("fused_reg", th, tw)
+    x, w = workloads.make_case(2, C, H, H, K, R, R, 1, P, 0.7, seed=401 + sum(case))
+    y = isc.isc_sparse_conv_fused(to_dev(torch, x), isc.isc_repack_filter(to_dev(torch, w)), 1, P,
+                                  tuning=tu).cpu().numpy()
+    assert_conv_close(y, oracle.conv2d_f64(x, w, 1, P), "register tall %s" % (case,))
+    yc = isc.census(desc)
+    z = isc.isc_conv2d_relu(to_dev(torch, x), to_dev(torch, w), 1, P, path="sparse", y_census=yc, tuning=tu)
+    assert np.array_equal(z.cpu().numpy(), np.maximum(y, 0))
+    assert isc.isc_census_read(yc) == (y.size, int((y > 0).sum()))
+    xi, wi = workloads.integer_case(2, C, H, H, K, R, R, seed=7 + sum(case))
+    yi = isc.isc_sparse_conv_fused(to_dev(torch, xi), isc.isc_repack_filter(to_dev(torch, wi)), 1, P, tuning=tu)
+    assert np.array_equal(yi.cpu().numpy().astype(np.float64), oracle.conv2d_f64(xi, wi, 1, P))
+
+
 def test_auto_crossover_both_sides(torch, isc):
     """AUTO with the per-shape crossover (the library's default threshold):
     on a shape whose modelled crossover lies inside (0, 1), an input below it
