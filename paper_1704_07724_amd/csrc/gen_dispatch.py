@@ -94,6 +94,9 @@ WALK_TILES += [(R, 7, 7, 2) for R in (3, 5)] + [(3, 8, 8, 2)]
 RING_TILES = [(5, TH, TW, 0, 1) for TH, TW in ((9, 9), (7, 14), (5, 14), (3, 14))] + [(5, 1, 28, 0, 2)]
 RING_TILES += [(3, TH, 14, 0, 1) for TH in (7, 4, 2)] + [(3, 4, 14, 0, 2)]
 RING_TILES += [(1, TH, 14, 0, 1) for TH in (4, 2)] + [(1, 4, 14, 0, 2)]  # 7 x 14: WALK_TILES
+# Tiles of the weight-gradient kernel: (R, TH, TW, SAME).
+GRAD_TILES = [(3, 7, 13, 1), (3, 7, 14, 1), (3, 7, 7, 2), (3, 7, 14, 0), (3, 4, 16, 0), (3, 2, 16, 0), (5, 7, 7, 2),
+              (5, 9, 9, 0), (5, 4, 14, 0), (5, 2, 14, 0), (1, 7, 7, 0), (1, 7, 14, 0), (1, 2, 14, 0)]
 WALK_CHUNK = 63  # window positions per ballot; the next bit is the sentinel
 WALK_HEAD = 32   # bytes of a leaf besides its FMAs: lane read (8), five scalar instructions (20), the jump (4)
 
@@ -105,8 +108,8 @@ def walk_positions(R, TH, TW, same):
     return [(wy, xp) for wy in rows for xp in cols]
 
 
-def walk_specialisation(R, TH, TW, same, kpl=1):
-    """AsmWalk<R, TH, TW, SAME, KPL>: every set bit of the window's ballots, in order.
+def walk_specialisation(R, TH, TW, same, kpl=1, grad=False):
+    """AsmWalk<R, TH, TW, SAME, KPL> (AsmGradWalk with grad): every set bit of the window's ballots, in order.
 
     Leaf q (chunk q / 64, lane q % 64 of that ballot) reads its nonzero's
     value from its lane, finds the next set bit, computes that bit's leaf
@@ -125,6 +128,8 @@ def walk_specialisation(R, TH, TW, same, kpl=1):
         return [" s_ff1_i32_b64 s46, %[m{}]".format(e), " s_bitset0_b64 %[m{}], s46".format(e),
                 " s_mulk_i32 s46, {}".format(stride), " s_add_u32 s48, s44, s46", " s_addc_u32 s49, s45, 0"]
 
+    # forward: a (the tile's outputs) += x * w; gradient: w += x * a
+    fma = " v_fmac_f32_e32 %[w{1}], s47, %[a{0}]" if grad else " v_fmac_f32_e32 %[a{0}], s47, %[w{1}]"
     jump = [" s_setpc_b64 s[48:49]"]
     lines = [" s_getpc_b64 s[44:45]", "W%=_base:", " s_add_u32 s44, s44, W%=_q0-W%=_base", " s_addc_u32 s45, s45, 0"]
     lines += find_next(0) + jump
@@ -133,7 +138,7 @@ def walk_specialisation(R, TH, TW, same, kpl=1):
         n = min(WALK_CHUNK, nq - e * WALK_CHUNK)
         for l in range(n):
             wy, xp = pos[e * WALK_CHUNK + l]
-            fmas = [" v_fmac_f32_e32 %[a{}], s47, %[w{}]".format(a * kpl + j, w * kpl + j)
+            fmas = [fma.format(a * kpl + j, w * kpl + j)
                     for a, w in leaf_fmas(R, TH, TW, wy, xp) for j in range(kpl)]
             nx = find_next(e)
             # the scalar chain between the FMAs; two instructions between the
@@ -156,18 +161,19 @@ def walk_specialisation(R, TH, TW, same, kpl=1):
                 lines.append(" .fill {}, 4, 0xbf800000".format((stride - 36) // 4))
     na, nw = TH * TW * kpl, R * R * kpl
     asm = "\n            ".join('"%s\\n"' % l for l in lines)
-    outs = ", ".join(['[a{0}] "+v"(acc[{0}])'.format(i) for i in range(na)] +
-                     ['[m{0}] "+s"(mask[{0}])'.format(e) for e in range(epl)])
-    ins = ", ".join(['[w{0}] "v"(w[{0}])'.format(i) for i in range(nw)] +
-                    ['[x{0}] "v"(x[{0}])'.format(e) for e in range(epl)])
+    ro, rw = ('"v"', '"+v"') if grad else ('"+v"', '"v"')
+    tile = ["[a{0}] {1}(acc[{0}])".format(i, ro) for i in range(na)]
+    taps = ["[w{0}] {1}(w[{0}])".format(i, rw) for i in range(nw)]
+    outs = ", ".join((taps if grad else tile) + ['[m{0}] "+s"(mask[{0}])'.format(e) for e in range(epl)])
+    ins = ", ".join((tile if grad else taps) + ['[x{0}] "v"(x[{0}])'.format(e) for e in range(epl)])
     return '''template <>
-struct AsmWalk<{R}, {TH}, {TW}, {same}, {kpl}> {{
+struct {name}<{R}, {TH}, {TW}, {same}, {kpl}> {{
     static constexpr bool kReg = {reg};  // a tile of the register-weight kernel
     // {nq} positions: {nr} window rows from {r0}, {nc} columns from {c0}
     static constexpr int kRow0 = {r0}, kCol0 = {c0}, kRows = {nr}, kCols = {nc}, kPositions = {nq}, kChunks = {epl};
     // leaves of at most {maxf} FMAs, stride {stride} bytes
     static __device__ __forceinline__ void run(unsigned long long (&mask)[{epl}], const float (&x)[{epl}],
-                                               float (&acc)[{na}], const float (&w)[{nw}]) {{
+                                               {ca}float (&acc)[{na}], {cw}float (&w)[{nw}]) {{
         asm volatile(
             {asm}
             : {outs}
@@ -176,7 +182,8 @@ struct AsmWalk<{R}, {TH}, {TW}, {same}, {kpl}> {{
     }}
 }};
 '''.format(R=R, TH=TH, TW=TW, same=same, epl=epl, nq=nq, maxf=maxf, stride=stride, na=na, nw=nw, asm=asm, outs=outs,
-           ins=ins, kpl=kpl,
+           ins=ins, kpl=kpl, name="AsmGradWalk" if grad else "AsmWalk", ca="const " if grad else "",
+           cw="" if grad else "const ",
            reg="true" if kpl == 1 and (R, TH, TW, same) in WALK_TILES else "false", r0=pos[0][0], c0=pos[0][1], nr=pos[-1][0] - pos[0][0] + 1, nc=pos[-1][1] - pos[0][1] + 1)
 
 
@@ -203,6 +210,9 @@ struct AsmWalk {
 };
 
 ''')
+    parts.append("template <int R, int TH, int TW, int SAME, int KPL = 1>\nstruct AsmGradWalk;\n\n")
+    for tile in GRAD_TILES:
+        parts.append(walk_specialisation(*tile, grad=True))
     for tile in WALK_TILES + RING_TILES:
         parts.append(walk_specialisation(*tile))
     parts.append('''}  // namespace tile

@@ -3,60 +3,104 @@
 #include "sparse_dw.hpp"
 
 #include <algorithm>
-#include <cstdlib>
 
 namespace isc {
 namespace dwk {
 namespace {
 
-// dw[e] = sum over ranges of part[range][e], ranges in order.
-__global__ __launch_bounds__(256)
-void dw_reduce_kernel(const float *__restrict__ part, int splits, int64_t n, float *__restrict__ dw) {
-    const int64_t e = static_cast<int64_t>(blockIdx.x) * blockDim.x + threadIdx.x;
-    if (e >= n) return;
-    float s = 0.0f;
-    for (int i = 0; i < splits; ++i) s += part[static_cast<int64_t>(i) * n + e];
-    dw[e] = s;
+// dw[k][e] = sum over ranges of part[range][e][k] (e = (c, r, s)): a block
+// takes 8 values of e times 64 maps; wavefront w adds the ranges w, w + 4, ...
+// in order, consecutive lanes on consecutive maps, eight loads in flight, then
+// the four sums are added in order and written with consecutive lanes on
+// consecutive e.  A sum that is not finite is taken again over the outputs
+// alone (sparse_dw.hpp), from the nonzero inputs in order.
+constexpr int kRedE = 8, kRedWaves = 4;
+
+__global__ __launch_bounds__(kRedWaves * kLanes)
+void dw_reduce_kernel(DwArgs a, int R, float *__restrict__ dw) {
+    __shared__ float turn[kRedWaves][kRedE][kLanes + 1];
+    const int crs = a.C * R * R;
+    const int e0 = blockIdx.x * kRedE, k0 = blockIdx.y * kLanes;
+    const int lane = threadIdx.x & (kLanes - 1), wave = threadIdx.x / kLanes;
+    const size_t stride = static_cast<size_t>(crs) * a.Kp;
+    const float *src = a.part + static_cast<size_t>(e0) * a.Kp + k0 + lane;
+    const int last = min(kRedE, crs - e0) - 1;  // rows past it load it again and are dropped
+    float sum[kRedE];
+#pragma unroll
+    for (int i = 0; i < kRedE; ++i) sum[i] = 0.0f;
+#pragma unroll 4
+    for (int sp = wave; sp < a.splits; sp += kRedWaves)
+#pragma unroll
+        for (int i = 0; i < kRedE; ++i) sum[i] += src[sp * stride + static_cast<size_t>(min(i, last)) * a.Kp];
+#pragma unroll
+    for (int i = 0; i < kRedE; ++i) turn[wave][i][lane] = sum[i];
+    __syncthreads();
+    const int col = threadIdx.x & (kRedE - 1);
+    if (e0 + col >= crs) return;
+    for (int m = threadIdx.x / kRedE; m < kLanes; m += kRedWaves * kLanes / kRedE) {
+        const int k = k0 + m;
+        if (k >= a.K) break;
+        float s = turn[0][col][m];
+        for (int w = 1; w < kRedWaves; ++w) s += turn[w][col][m];
+        if (!__builtin_isfinite(s)) {
+            const int e = e0 + col, c = e / (R * R), rs = e - c * R * R;
+            const int dyr = rs / R - a.P, dxs = rs % R - a.P;
+            s = 0.0f;
+            for (int n = 0; n < a.N && !__builtin_isnan(s); ++n)
+                for (int i = max(0, -dyr); i < min(a.Ho, a.H - dyr); ++i)
+                    for (int j = max(0, -dxs); j < min(a.Wo, a.W - dxs); ++j) {
+                        const float v = a.x[((static_cast<size_t>(n) * a.C + c) * a.H + i + dyr) * a.W + j + dxs];
+                        if (v != 0.0f)
+                            s = __builtin_fmaf(v, a.dy[((static_cast<size_t>(n) * a.K + k) * a.Ho + i) * a.Wo + j], s);
+                    }
+        }
+        dw[static_cast<size_t>(k) * crs + e0 + col] = s;
+    }
 }
 
-// Tile rows and maps per lane (measured on every workload layer):
-//  - 3x3 filters: one-row tiles, two maps per lane;
-//  - 5x5 and 1x1 filters: two-row tiles (each scanned nonzero feeds two
-//    output rows), two maps per lane -- one when K > 64 with 5x5 filters,
-//    which keeps three channels per wavefront instead of one.
-// A caller's tuning maps_per_lane (1, 2, 4) and rows (1, 2) override the
-// choice (four maps per lane only with one-row 16-column tiles, two rows
-// only with one or two maps per lane).
-int dw_th(const SparseShape &sh) {
-    const int t = sh.tu.rows;
-    if (t == 1 || t == 2) return t;
-    return sh.R == 3 ? 1 : 2;
-}
+// Workgroups the ranges are cut for: one round of three per CU.  More ranges
+// would write and read more partial sums (AlexNet conv3: 3.5 MB each).
+constexpr int64_t kDwGroups = 768;
 
-int dw_kpl(const SparseShape &sh, int th) {
-    const int k = sh.tu.maps_per_lane;
-    if ((k == 1 || k == 2) || (k == 4 && th == 1 && sh.Wo <= 16)) return k;
-    return sh.R == 5 && sh.K > kLanes ? 1 : 2;
-}
-int dw_tw(int Wo) { return Wo <= 16 ? 16 : 28; }
-
+// The cheapest tile among those that take the shape: a wavefront's cycles per
+// tile (reading the gradients, and per channel a fixed part and the window's
+// nonzeros at a tenth of its positions) times the tiles of all workgroups, or
+// of one round where the tiles do not fill it (small batches, where short
+// tiles give more workgroups).
 bool dw_plan(const SparseShape &sh, DwPlan *p) {
     if (sh.T != 1 || sh.R != sh.S || !(sh.R == 1 || sh.R == 3 || sh.R == 5)) return false;
-    p->th = dw_th(sh);
-    p->kpl = dw_kpl(sh, p->th);
-    p->ch = dw_ch_for(sh.R, p->kpl, p->th);
-    p->tw = p->th == 2 ? 16 : dw_tw(sh.Wo);
-    p->TWr = std::min(p->tw, sh.Wo);
-    p->ctiles = (sh.Wo + p->TWr - 1) / p->TWr;
-    p->bands = (sh.Ho + p->th - 1) / p->th;
-    p->kgroups = (sh.K + kLanes * p->kpl - 1) / (kLanes * p->kpl);
-    const int cgroups = (sh.C + p->ch - 1) / p->ch;
-    p->cquads = (cgroups + kDwWaves - 1) / kDwWaves;
-    const int64_t ntiles = static_cast<int64_t>(sh.N) * p->bands * p->ctiles;
+    const DwTile *tiles = sh.R == 1 ? kDwTiles1 : (sh.R == 3 ? kDwTiles3 : kDwTiles5);
+    const int n = static_cast<int>(sh.R == 1 ? sizeof(kDwTiles1) : (sh.R == 3 ? sizeof(kDwTiles3) : sizeof(kDwTiles5))) /
+                  static_cast<int>(sizeof(DwTile));
+    p->kgroups = (sh.K + kLanes - 1) / kLanes;
+    double best = -1.0;
+    int64_t ntiles = 0;
+    for (int i = 0; i < n; ++i) {
+        const DwTile &t = tiles[i];
+        if (t.same >= 1 && (sh.P != sh.R / 2 || sh.W > t.tw)) continue;
+        if (t.same >= 2 && sh.H > t.th) continue;
+        const int64_t bands = (sh.Ho + t.th - 1) / t.th, ctiles = (sh.Wo + t.tw - 1) / t.tw;
+        const int64_t cgroups = (sh.C + kDwWaves * t.ch - 1) / (kDwWaves * t.ch);
+        const int64_t nt = sh.N * bands * ctiles;
+        const double rows = std::min(t.same == 2 ? t.th : t.th + sh.R - 1, sh.H);
+        const double cols = std::min(t.same ? t.tw : t.tw + sh.R - 1, sh.W);
+        const double fmas = std::min<double>(t.th, sh.Ho) * std::min(t.tw, sh.Wo) * sh.R * sh.R / (rows * cols);
+        const double per = 400.0 + 8.0 * t.th * t.tw +
+                           t.ch * (150.0 + 8.0 * sh.R * sh.R + 0.1 * rows * cols * (15.0 + 4.0 * fmas));
+        const double cost = std::max<double>(static_cast<double>(nt) * cgroups * p->kgroups, kDwGroups) * per;
+        if (best < 0.0 || cost < best) {
+            best = cost;
+            ntiles = nt;
+            p->t = t;
+            p->bands = static_cast<int>(bands);
+            p->ctiles = static_cast<int>(ctiles);
+            p->cgroups = static_cast<int>(cgroups);
+        }
+    }
     if (ntiles > (1ll << 30)) return false;
     p->ntiles = static_cast<int>(ntiles);
-    const int64_t base = static_cast<int64_t>(p->kgroups) * p->cquads;
-    int64_t splits = std::max<int64_t>(1, std::min<int64_t>(ntiles, (kDwMinGroups + base - 1) / base));
+    const int64_t base = static_cast<int64_t>(p->kgroups) * p->cgroups;
+    const int64_t splits = std::max<int64_t>(1, std::min<int64_t>(ntiles, kDwGroups / base));
     p->per = static_cast<int>((ntiles + splits - 1) / splits);
     p->splits = static_cast<int>((ntiles + p->per - 1) / p->per);
     return base * p->splits < (1ll << 31);
@@ -70,20 +114,10 @@ bool sparse_dw_applies(const SparseShape &sh) {
     return dwk::dw_plan(sh, &p);
 }
 
-// The largest partial-sum buffer of any tile the overrides may force, so
-// that one workspace size holds for every plan.
 size_t sparse_dw_workspace_floats(const SparseShape &sh) {
-    size_t most = 0;
-    for (int th : {1, 2})
-        for (int kpl : {1, 2, 4}) {
-            SparseShape v = sh;
-            v.tu = isc_tuning{};
-            v.tu.rows = th;
-            v.tu.maps_per_lane = kpl;
-            dwk::DwPlan p;
-            if (dwk::dw_plan(v, &p)) most = std::max(most, static_cast<size_t>(p.splits) * sh.K * sh.C * sh.R * sh.S);
-        }
-    return most;
+    dwk::DwPlan p;
+    if (!dwk::dw_plan(sh, &p)) return 0;
+    return static_cast<size_t>(p.splits) * sh.C * sh.R * sh.S * p.kgroups * dwk::kLanes;
 }
 
 hipError_t launch_sparse_dw(const SparseShape &sh, const float *x, const float *dy, float *dw, float *part,
@@ -96,17 +130,18 @@ hipError_t launch_sparse_dw(const SparseShape &sh, const float *x, const float *
     a.dy = dy;
     a.part = part;
     a.N = sh.N; a.C = sh.C; a.H = sh.H; a.W = sh.W; a.K = sh.K; a.P = sh.P; a.Ho = sh.Ho; a.Wo = sh.Wo;
-    a.TWr = p.TWr;
+    a.Kp = p.kgroups * kLanes;
     a.ctiles = p.ctiles;
     a.bands = p.bands;
-    a.cquads = p.cquads;
+    a.cgroups = p.cgroups;
     a.splits = p.splits;
     a.per = p.per;
     a.ntiles = p.ntiles;
     hipError_t e = sh.R == 1 ? launch_r1(a, p, s) : sh.R == 3 ? launch_r3(a, p, s) : launch_r5(a, p, s);
     if (e != hipSuccess) return e;
-    const int64_t n = static_cast<int64_t>(sh.K) * sh.C * sh.R * sh.S;
-    dw_reduce_kernel<<<static_cast<unsigned>((n + 255) / 256), 256, 0, s>>>(part, p.splits, n, dw);
+    const int crs = sh.C * sh.R * sh.S;
+    const dim3 grid(static_cast<unsigned>((crs + kRedE - 1) / kRedE), static_cast<unsigned>(p.kgroups));
+    dw_reduce_kernel<<<grid, kRedWaves * kLanes, 0, s>>>(a, sh.R, dw);
     return hipGetLastError();
 }
 

@@ -14,21 +14,30 @@
 // for every tap (r, s) whose output lies in the tile, and adds x times it to
 // the K-contiguous gradient vector dw[:, c, r, s].
 //
-// A wavefront owns 64*KPL output maps (lanes over maps, as in the forward
-// kernels), CH input channels and a contiguous range of output tiles (TH
-// output rows, TW columns, one image each).  It keeps the CH*R*S*KPL
-// gradient sums in registers for the whole range; per tile it loads the
-// tile's output gradients for its maps (TH*TW*KPL registers) and, per channel,
-// the input window that reaches the tile, takes a ballot of the zero test and
-// scans it statically (tile::walk_scan_f): every set position runs a
-// straight-line block of multiply-adds whose register indices are constants.
-// The four wavefronts of a workgroup share maps and tile range and differ in
-// channels: per tile they load the output gradients of their maps once,
-// together, with consecutive lanes on consecutive columns of a map (whole
-// cache lines), and transpose them through LDS so that each lane then reads
-// its maps' values for every column.  Each wavefront finally stores its sums
-// for its range; a second launch adds the ranges in order (deterministic, no
-// atomics).
+// A wavefront owns 64 output maps (lanes over maps, as in the forward
+// kernels), CH input channels and a contiguous range of output tiles (TH x TW
+// outputs of one image each), and keeps its CH*R*S gradient sums in registers
+// for the whole range.  Per tile it holds the tile's output gradients of its
+// maps in registers and walks, channel by channel, the nonzeros of the
+// window that reaches the tile by computed jumps (AsmGradWalk, the forward
+// walk with accumulators and operands exchanged).  The four wavefronts of a
+// workgroup share maps and tile range and differ in channels: the tile's
+// gradients come into LDS once, by direct global->LDS loads, a map's
+// positions consecutive at an odd pitch, so that 64 lanes reading one position
+// of their maps meet 64 banks.  Between two barriers a wavefront reads its
+// gradients and windows into registers; the next tile's loads then land in
+// the same LDS while this one is walked.  Sums are taken per tile and then
+// added (shorter chains of rounding than one chain per range).  Each
+// wavefront finally stores its sums for its range, maps fastest; a second launch adds the ranges in a fixed order and
+// transposes (deterministic, no atomics).
+//
+// A position past the map's last row or column has gradient zero, so it adds
+// nothing to a finite sum; where an infinite or NaN input met one, the sum is
+// not finite, and the second launch sums such an entry again over the
+// outputs alone.
+//
+// Before, one-row tiles under a static scan met 1.9 nonzeros per channel
+// and tile with 2.2 FMAs each at 3x3; 7 x 13 tiles meet 4.9 with 7.2.
 #pragma once
 
 #include "sparse_tile.hpp"
@@ -38,34 +47,40 @@ namespace dwk {
 
 using tile::kLanes;
 constexpr int kDwWaves = 4;
-constexpr int kDwMinGroups = 1024;   // workgroups that fill 256 CUs four deep
-constexpr int kDwMaxRegs = 100;      // gradient sums per lane, at most
+// Range of the buffers a tile is read through: past the offsets of every row
+// a tile or its window spans (at most 13 of 65535 columns); a load outside the
+// map has tile::kPastPlane for an offset and reads zero.
+constexpr int kWindowBytes = 1 << 30;
 
 struct DwArgs {
     const float *x;    // N x C x H x W
     const float *dy;   // N x K x Ho x Wo
-    float *part;       // [splits][K][C*R*S]: sums of each tile range
+    float *part;       // [splits][C*R*S][Kp]: sums of each tile range
     int N, C, H, W, K, P, Ho, Wo;
-    int TWr, ctiles;   // output columns per tile in use, column tiles per row
+    int Kp;            // K rounded up to 64
+    int ctiles;        // column tiles per row band
     int bands;         // groups of TH output rows
-    int cquads;        // groups of kDwWaves * CH channels
+    int cgroups;       // groups of kDwWaves * CH channels
     int splits, per;   // tile ranges, tiles per range
     int ntiles;        // N * bands * ctiles
 };
 
-struct DwPlan {
-    int kpl, th, ch, tw, TWr, ctiles, bands, kgroups, cquads, splits, per, ntiles;
+// Tiles (TH x TW outputs; same: which window positions the walk visits, as in
+// gen_dispatch.py) and the channels per wavefront: the tile's gradients and the
+// sums leave three wavefronts per SIMD (168 registers), and a tile's
+// gradients, read from LDS by every wavefront, serve as many channels as that
+// allows.
+struct DwTile {
+    int th, tw, same, ch;
 };
+constexpr DwTile kDwTiles3[] = {{7, 7, 2, 4}, {7, 13, 1, 4}, {7, 14, 1, 3}, {7, 14, 0, 2}, {4, 16, 0, 4}, {2, 16, 0, 4}};
+constexpr DwTile kDwTiles5[] = {{7, 7, 2, 2}, {9, 9, 0, 1}, {4, 14, 0, 2}, {2, 14, 0, 2}};
+constexpr DwTile kDwTiles1[] = {{7, 7, 0, 8}, {7, 14, 0, 8}, {2, 14, 0, 8}};
 
-// Channels per wavefront for a filter size and maps per lane: as many as
-// kDwMaxRegs gradient sums allow, at most 16.
-// Two-row tiles hold twice the output gradients: the channels are cut so
-// that gradient sums and gradients together stay within the same budget.
-constexpr int dw_ch_for(int RS, int KPL, int TH = 1) {
-    const int room = kDwMaxRegs - (TH - 1) * 16 * KPL * 3 / 4;
-    const int ch = room / (RS * RS * KPL);
-    return ch < 1 ? 1 : (ch < 16 ? ch : 16);
-}
+struct DwPlan {
+    DwTile t;
+    int ctiles, bands, kgroups, cgroups, splits, per, ntiles;
+};
 
 // Launchers of the kernels of one filter size (sparse_dw_r{1,3,5}.hip).
 hipError_t launch_r1(const DwArgs &a, const DwPlan &p, hipStream_t s);
@@ -80,217 +95,149 @@ namespace isc {
 namespace dwk {
 namespace {
 
-template <int RS_, int KPL, int TH, int TW, int CH>
-__global__ __launch_bounds__(kDwWaves * kLanes)
+template <int RS_, int TH, int TW, int SAME, int CH>
+__global__ __launch_bounds__(kDwWaves * kLanes, 3)
 void sparse_dw_kernel(DwArgs a) {
-    using T = tile::Shape<RS_, RS_, KPL, TH, TW>;
-    constexpr int EPL = T::EPL, RS2 = RS_ * RS_;
+    using Walk = tile::AsmGradWalk<RS_, TH, TW, SAME>;
+    constexpr int RS2 = RS_ * RS_, EPL = Walk::kChunks, NQ = Walk::kPositions;
+    constexpr int WCH = tile::kWalkChunk, TP = TH * TW, PITCH = TP | 1;
+    constexpr int NL = (TP + kLanes - 1) / kLanes;   // loads of one map's positions
+    constexpr int MPW = kLanes / kDwWaves;           // maps each wavefront loads
+    // a tile's gradients, [map][position], then the wavefronts' windows
+    __shared__ float lds[kLanes * PITCH + kDwWaves * CH * EPL * kLanes];
+
     const int lane = threadIdx.x & (kLanes - 1);
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kLanes);
     int b = blockIdx.x;
-    const int cq = b % a.cquads;
-    b /= a.cquads;
+    const int cg = b % a.cgroups;
+    b /= a.cgroups;
     const int split = b % a.splits;
     const int kg = b / a.splits;
-    const int cbase = (cq * kDwWaves + wave) * CH;
-    const int kbase = kg * T::KW;
+    const int c0 = (cg * kDwWaves + wave) * CH;
+    const int kbase = kg * kLanes;
     const int C = a.C, H = a.H, W = a.W, K = a.K, P = a.P, Ho = a.Ho, Wo = a.Wo;
-    const size_t HW = static_cast<size_t>(H) * W;
+    float *win = lds + kLanes * PITCH + wave * CH * EPL * kLanes;
 
-    float acc[CH][RS_][RS_][KPL];
+    float acc[CH][RS2];
 #pragma unroll
     for (int ch = 0; ch < CH; ++ch)
 #pragma unroll
-        for (int r = 0; r < RS_; ++r)
-#pragma unroll
-            for (int s = 0; s < RS_; ++s)
-#pragma unroll
-                for (int j = 0; j < KPL; ++j) acc[ch][r][s][j] = 0.0f;
-
-    // this lane's maps
-    bool kok[KPL];
-#pragma unroll
-    for (int j = 0; j < KPL; ++j) kok[j] = kbase + lane * KPL + j < K;
-
-    // the tile's output gradients, [row * TW + column][map] (pitch KW + 1);
-    // the cooperative load: load i of the workgroup covers one row of 64 /
-    // COLS maps, lane l column l % COLS of map l / COLS
-    constexpr int KW = T::KW;
-    constexpr int COLS = TW <= 16 ? 16 : 32;
-    constexpr int MPI = kLanes / COLS;                 // maps per load
-    constexpr int GPR = KW / MPI;                      // loads per tile row
-    constexpr int NLD = TH * GPR / kDwWaves;           // loads per wavefront per tile
-    static_assert((TH * GPR) % kDwWaves == 0, "cooperative load");
-    static_assert(NLD <= 32, "validity bits");
-    __shared__ float gs[2][TH * TW][KW + 1];
-    const int lcol = lane % COLS;
-    const int lmap = lane / COLS;
-
-    // the loads of one tile, issued a tile ahead: its output gradients for
-    // the cooperative load (vg: gs[hr * TW + ox][m] = dy[n, kbase + m,
-    // oy0 + hr, ox0 + ox], zero past the map and past K) and this wavefront's channel
-    // windows (vx, element e = q*64 + lane at window row wy = e / WCOLS,
-    // input row oy0 - P + wy, shifted column xp, input column ox0 - P + xp;
-    // inw: the element lies in the map and its column reaches the tile)
-    float vg[NLD];
-    uint32_t vok = 0;  // bit i: vg[i] is a gradient of the tile (else stored as zero)
-    float vx[CH][EPL];
-    bool inw[EPL];
-    auto load_tile = [&](int t) {
-        const int ct = t % a.ctiles;
-        const int rest = t / a.ctiles;
-        const int oy0 = (rest % a.bands) * TH;
-        const int n = rest / a.bands;
-        const int ox0 = ct * a.TWr;
-        const int tw = min(a.TWr, Wo - ox0);
-        // every load in bounds (clamped), the validity kept aside: a select
-        // on the loaded value would let the compiler turn each load into a
-        // branch with its own wait
-        vok = 0;
-#pragma unroll
-        for (int i = 0; i < NLD; ++i) {
-            const int li = wave * NLD + i;
-            const int hr = li / GPR;
-            const int m = (li - hr * GPR) * MPI + lmap;
-            const int k = kbase + m;
-            const int oy = oy0 + hr;
-            const float *row =
-                a.dy + ((static_cast<size_t>(n) * K + min(k, K - 1)) * Ho + min(oy, Ho - 1)) * Wo + ox0;
-            vg[i] = row[min(lcol, tw - 1)];
-            vok |= (k < K && lcol < tw && oy < Ho) ? (1u << i) : 0u;
-        }
-        int xoff[EPL];
-#pragma unroll
-        for (int q = 0; q < EPL; ++q) {
-            const int e = q * kLanes + lane;
-            const int wy = e / T::WCOLS;
-            const int xp = e - wy * T::WCOLS;
-            const int y = oy0 - P + wy, xx = ox0 - P + xp;
-            inw[q] = e < T::WROWS * T::WCOLS && xp < tw + RS_ - 1 && y >= 0 && y < H && xx >= 0 && xx < W;
-            xoff[q] = inw[q] ? y * W + xx : 0;
-        }
-        tile::static_for<0, CH>([&](auto chc) {
-            constexpr int ch = decltype(chc)::value;
-            const int c = min(cbase + ch, C - 1);
-            const float *plane = a.x + (static_cast<size_t>(n) * C + c) * HW;
-#pragma unroll
-            for (int q = 0; q < EPL; ++q) vx[ch][q] = plane[xoff[q]];
-        });
-    };
+        for (int t = 0; t < RS2; ++t) acc[ch][t] = 0.0f;
 
     const int t0 = split * a.per;
     const int t1 = min(a.ntiles, t0 + a.per);
-    if (t0 < t1) load_tile(t0);
+    // the tile loaded next, counted on from t0: column tile, band, image
+    int ct = t0 % a.ctiles, band = t0 / a.ctiles % a.bands, n = t0 / a.ctiles / a.bands;
+
+    // the loads of one tile into LDS: its gradients (zero past the map; maps
+    // past K repeat the last one, their sums are dropped) and this
+    // wavefront's windows (position q * WCH + lane of the walk; lanes without
+    // one read zero)
+    auto load_tile = [&]() {
+        const int oy0 = band * TH, ox0 = ct * TW;
+        const int rows = Ho - oy0, cols = Wo - ox0;  // outputs from the tile's corner
+        int goff[NL];
+#pragma unroll
+        for (int j = 0; j < NL; ++j) {
+            const int p = j * kLanes + lane;
+            const int r = p / TW, c = p - r * TW;
+            goff[j] = r < rows && c < cols ? (r * Wo + ox0 + c) * static_cast<int>(sizeof(float)) : tile::kPastPlane;
+        }
+        // offsets count from the tile's first row: a plane may exceed 2^31 bytes
+        const float *gp = a.dy + (static_cast<size_t>(n) * K + kbase) * Ho * Wo + static_cast<size_t>(oy0) * Wo;
+        const int mlast = K - 1 - kbase;
+        gp += static_cast<size_t>(min(wave * MPW, mlast)) * (Ho * Wo);
+#pragma unroll
+        for (int i = 0; i < MPW; ++i) {
+            const int m = wave * MPW + i;
+            const __amdgpu_buffer_rsrc_t g =
+                __builtin_amdgcn_make_buffer_rsrc(const_cast<float *>(gp), 0, kWindowBytes, tile::kBufferFormat);
+#pragma unroll
+            for (int j = 0; j < NL; ++j)
+                if (j * kLanes + lane < TP) tile::buffer_lds4(g, lds + m * PITCH + j * kLanes, goff[j]);
+            gp += m < mlast ? Ho * Wo : 0;
+        }
+        const int y0 = max(0, oy0 - P);
+        int xoff[EPL];
+#pragma unroll
+        for (int q = 0; q < EPL; ++q) {
+            const int e = q * WCH + lane;
+            const int wy = e / Walk::kCols + Walk::kRow0, xp = e % Walk::kCols + Walk::kCol0;
+            const int y = oy0 - P + wy, xx = ox0 - P + xp;
+            const bool in = lane < WCH && e < NQ && wy < rows + RS_ - 1 && xp < cols + RS_ - 1 && y >= 0 && y < H &&
+                            xx >= 0 && xx < W;
+            xoff[q] = in ? ((y - y0) * W + xx) * static_cast<int>(sizeof(float)) : tile::kPastPlane;
+        }
+        const float *xp = a.x + (static_cast<size_t>(n) * C + min(c0, C - 1)) * H * W + static_cast<size_t>(y0) * W;
+#pragma unroll
+        for (int ch = 0; ch < CH; ++ch) {
+            const __amdgpu_buffer_rsrc_t x =
+                __builtin_amdgcn_make_buffer_rsrc(const_cast<float *>(xp), 0, kWindowBytes, tile::kBufferFormat);
+#pragma unroll
+            for (int q = 0; q < EPL; ++q) tile::buffer_lds4(x, win + (ch * EPL + q) * kLanes, xoff[q]);
+            xp += c0 + ch + 1 < C ? H * W : 0;
+        }
+        if (++ct == a.ctiles) {
+            ct = 0;
+            if (++band == a.bands) {
+                band = 0;
+                ++n;
+            }
+        }
+    };
+
+    if (t0 < t1) load_tile();
 #pragma unroll 1
     for (int t = t0; t < t1; ++t) {
-        // the tile loaded last into LDS (one buffer of two: the other one is
-        // still being read by wavefronts behind) and its windows into the
-        // working registers, then the next tile's loads go out and land
-        // while this one is scanned
-        const int buf = (t - t0) & 1;
+        tile::wait_vm_and_barrier<0>();  // everyone's loads of this tile have landed
+        float cur[CH][EPL], g[TP];
 #pragma unroll
-        for (int i = 0; i < NLD; ++i) {
-            const int li = wave * NLD + i;
-            const int hr = li / GPR;
-            const int m = (li - hr * GPR) * MPI + lmap;
-            if (lcol < TW) gs[buf][hr * TW + lcol][m] = ((vok >> i) & 1u) ? vg[i] : 0.0f;
-        }
-        // the windows move to working registers by explicit moves, which the
-        // compiler cannot forward: the loaded registers are free again before
-        // the next tile's loads, so none has to be copied (after a wait for
-        // every load in flight) at the loop's back edge
-        float cur[CH][EPL];
-        bool inwin[EPL];
-#pragma unroll
-        for (int q = 0; q < EPL; ++q) inwin[q] = inw[q];
+        for (int p = 0; p < TP; ++p) g[p] = lds[lane * PITCH + p];
 #pragma unroll
         for (int ch = 0; ch < CH; ++ch)
 #pragma unroll
-            for (int q = 0; q < EPL; ++q) asm volatile("v_mov_b32 %0, %1" : "=v"(cur[ch][q]) : "v"(vx[ch][q]));
-        __syncthreads();
-        if (t + 1 < t1) load_tile(t + 1);
-        tile::Acc<T> g;
-#pragma unroll
-        for (int oy = 0; oy < TH; ++oy)
-#pragma unroll
-            for (int ox = 0; ox < TW; ++ox)
-#pragma unroll
-                for (int j = 0; j < KPL; ++j) g[oy][ox][j] = gs[buf][oy * TW + ox][lane * KPL + j];
-
-        // per channel: ballot of the zero test, static scan of the window
+            for (int q = 0; q < EPL; ++q) cur[ch][q] = win[(ch * EPL + q) * kLanes + lane];
+        tile::wait_vm_and_barrier<0>();  // and been read
+        if (t + 1 < t1) load_tile();
         tile::static_for<0, CH>([&](auto chc) {
             constexpr int ch = decltype(chc)::value;
-            if (cbase + ch < C) {  // wave-uniform
-                unsigned long long mask[EPL];
+            unsigned long long mask[EPL];
 #pragma unroll
-                for (int q = 0; q < EPL; ++q)
-                    mask[q] = __ballot(inwin[q] && (__float_as_uint(cur[ch][q]) & 0x7fffffffu) != 0u);
-                // tap (r, s) reaches output (WY - r, XP - s) when it lies in
-                // the tile
-                auto blk = [&](auto wy_c, auto xp_c, float v) {
-                    constexpr int WY = decltype(wy_c)::value, XP = decltype(xp_c)::value;
-                    tile::static_for<0, RS_>([&](auto rc) {
-                        constexpr int r = decltype(rc)::value, oy = WY - r;
-                        if constexpr (oy >= 0 && oy < TH) {
-                            tile::static_for<0, RS_>([&](auto sc) {
-                                constexpr int sx = decltype(sc)::value, ox = XP - sx;
-                                if constexpr (ox >= 0 && ox < TW) {
-#pragma unroll
-                                    for (int j = 0; j < KPL; ++j)
-                                        acc[ch][r][sx][j] = __builtin_fmaf(v, g[oy][ox][j], acc[ch][r][sx][j]);
-                                }
-                            });
-                        }
-                    });
-                };
-                tile::walk_scan_f<T>(mask, cur[ch], blk);
+            for (int q = 0; q < EPL; ++q) {
+                constexpr int kLast = NQ - (EPL - 1) * WCH;  // positions of the last ballot
+                mask[q] = __ballot((__float_as_uint(cur[ch][q]) & 0x7fffffffu) != 0u) |
+                          (1ull << (q + 1 < EPL ? WCH : kLast));
             }
+            float sum[RS2];
+#pragma unroll
+            for (int i = 0; i < RS2; ++i) sum[i] = 0.0f;
+            Walk::run(mask, cur[ch], g, sum);
+#pragma unroll
+            for (int i = 0; i < RS2; ++i) acc[ch][i] += sum[i];
         });
     }
 
-    // this range's sums: part[split][k][c][r][s]
-    const size_t crs = static_cast<size_t>(C) * RS2;
-    tile::static_for<0, CH>([&](auto chc) {
-        constexpr int ch = decltype(chc)::value;
-        const int c = cbase + ch;
-        if (c < C) {
+    // this range's sums
 #pragma unroll
-            for (int j = 0; j < KPL; ++j) {
-                if (!kok[j]) continue;
-                float *dst = a.part + (static_cast<size_t>(split) * K + kbase + lane * KPL + j) * crs +
-                             static_cast<size_t>(c) * RS2;
+    for (int ch = 0; ch < CH; ++ch) {
+        if (c0 + ch >= C) break;
+        float *dst = a.part + (static_cast<size_t>(split) * C + c0 + ch) * RS2 * a.Kp + kbase + lane;
 #pragma unroll
-                for (int r = 0; r < RS_; ++r)
-#pragma unroll
-                    for (int s = 0; s < RS_; ++s) dst[r * RS_ + s] = acc[ch][r][s][j];
-            }
-        }
-    });
-}
-
-template <int RS_, int KPL, int TH, int TW>
-hipError_t launch_dw_t(const DwArgs &a, const DwPlan &p, hipStream_t s) {
-    constexpr int CH = dw_ch_for(RS_, KPL, TH);
-    static_assert(CH >= 1 && CH * RS_ * RS_ * KPL <= kDwMaxRegs, "gradient sums");
-    if (p.ch != CH) return hipErrorInvalidValue;
-    const int64_t grid = static_cast<int64_t>(p.kgroups) * a.splits * a.cquads;
-    sparse_dw_kernel<RS_, KPL, TH, TW, CH><<<static_cast<unsigned>(grid), kDwWaves * kLanes, 0, s>>>(a);
-    return hipGetLastError();
-}
-
-// One-row tiles of 16 or 28 columns with 1, 2 or 4 maps per lane (four
-// only with 16 columns); two-row tiles of 16 columns with 1 or 2.
-template <int RS_>
-hipError_t launch_dw_rs(const DwArgs &a, const DwPlan &p, hipStream_t s) {
-    if (p.th == 2) {
-        if (p.tw != 16) return hipErrorInvalidValue;
-        return p.kpl == 1 ? launch_dw_t<RS_, 1, 2, 16>(a, p, s)
-                          : (p.kpl == 2 ? launch_dw_t<RS_, 2, 2, 16>(a, p, s) : hipErrorInvalidValue);
+        for (int t = 0; t < RS2; ++t) dst[static_cast<size_t>(t) * a.Kp] = acc[ch][t];
     }
-    switch (p.kpl) {
-    case 1: return p.tw == 16 ? launch_dw_t<RS_, 1, 1, 16>(a, p, s) : launch_dw_t<RS_, 1, 1, 28>(a, p, s);
-    case 2: return p.tw == 16 ? launch_dw_t<RS_, 2, 1, 16>(a, p, s) : launch_dw_t<RS_, 2, 1, 28>(a, p, s);
-    default: return p.tw == 16 ? launch_dw_t<RS_, 4, 1, 16>(a, p, s) : hipErrorInvalidValue;
+}
+
+// The launcher of table entry I when it is the chosen tile, else the next's.
+template <int RS_, const DwTile *TILES, int I, int NT>
+hipError_t launch_dw_table(const DwArgs &a, const DwPlan &p, hipStream_t s) {
+    if constexpr (I >= NT) {
+        return hipErrorInvalidValue;
+    } else {
+        constexpr DwTile t = TILES[I];
+        if (p.t.th != t.th || p.t.tw != t.tw || p.t.same != t.same) return launch_dw_table<RS_, TILES, I + 1, NT>(a, p, s);
+        const int64_t grid = static_cast<int64_t>(p.kgroups) * a.splits * a.cgroups;
+        sparse_dw_kernel<RS_, t.th, t.tw, t.same, t.ch><<<static_cast<unsigned>(grid), kDwWaves * kLanes, 0, s>>>(a);
+        return hipGetLastError();
     }
 }
 

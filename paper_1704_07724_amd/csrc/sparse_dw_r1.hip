@@ -6,7 +6,7 @@
 namespace isc {
 namespace dwk {
 
-hipError_t launch_r1(const DwArgs &a, const DwPlan &p, hipStream_t s) { return launch_dw_rs<1>(a, p, s); }
+hipError_t launch_r1(const DwArgs &a, const DwPlan &p, hipStream_t s) { return launch_dw_table<1, kDwTiles1, 0, sizeof(kDwTiles1) / sizeof(kDwTiles1[0])>(a, p, s); }
 
 }  // namespace dwk
 }  // namespace isc

@@ -6,7 +6,7 @@
 namespace isc {
 namespace dwk {
 
-hipError_t launch_r3(const DwArgs &a, const DwPlan &p, hipStream_t s) { return launch_dw_rs<3>(a, p, s); }
+hipError_t launch_r3(const DwArgs &a, const DwPlan &p, hipStream_t s) { return launch_dw_table<3, kDwTiles3, 0, sizeof(kDwTiles3) / sizeof(kDwTiles3[0])>(a, p, s); }
 
 }  // namespace dwk
 }  // namespace isc

@@ -6,7 +6,7 @@
 namespace isc {
 namespace dwk {
 
-hipError_t launch_r5(const DwArgs &a, const DwPlan &p, hipStream_t s) { return launch_dw_rs<5>(a, p, s); }
+hipError_t launch_r5(const DwArgs &a, const DwPlan &p, hipStream_t s) { return launch_dw_table<5, kDwTiles5, 0, sizeof(kDwTiles5) / sizeof(kDwTiles5[0])>(a, p, s); }
 
 }  // namespace dwk
 }  // namespace isc

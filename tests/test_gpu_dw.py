@@ -140,3 +140,46 @@ def test_dw_every_tile_variant(torch, isc, R, W):
         got = isc.isc_conv2d_dw(to_dev(torch, x), to_dev(torch, dy), R, R, 1, P,
                                 tuning={"maps_per_lane": kpl, "rows": th}).cpu().numpy()
         assert_close(got, want, "dw R%d W%d kpl%d th%d" % (R, W, kpl, th))
+
+
+# (N, C, H, W, K, R, P): each tile of the kernel and its ragged edges
+DW_TILES = [(3, 9, 13, 13, 70, 3, 1), (3, 9, 14, 14, 66, 3, 1), (3, 17, 7, 7, 66, 3, 1), (2, 9, 5, 6, 66, 3, 1),
+            (40, 9, 30, 29, 66, 3, 1), (90, 9, 18, 18, 66, 3, 0), (2, 9, 20, 33, 66, 3, 2), (40, 9, 7, 7, 66, 5, 2),
+            (9, 5, 27, 27, 130, 5, 2), (20, 5, 13, 15, 66, 5, 0), (40, 35, 7, 7, 66, 1, 0), (20, 33, 14, 28, 66, 1, 0),
+            (1, 33, 6, 40, 66, 1, 1)]
+
+
+@pytest.mark.parametrize("case", DW_TILES)
+def test_dw_tiles_and_special_values(torch, isc, case):
+    """Sums of integers bitwise; and an infinite or NaN input or gradient
+    reaches exactly the entries whose outputs it meets."""
+    N, C, H, W, K, R, P = case
+    note("dw tiles", case)
+    rng = np.random.default_rng(sum(case))
+    Ho, Wo = oracle.out_size(H, R, P, 1), oracle.out_size(W, R, P, 1)
+    x, _ = workloads.integer_case(N, C, H, W, K, R, R, seed=sum(case), xmax=3)
+    dy = rng.integers(-3, 4, size=(N, K, Ho, Wo)).astype(np.float32)
+    got = isc.isc_conv2d_dw(to_dev(torch, x), to_dev(torch, dy), R, R, 1, P).cpu().numpy()
+    assert np.array_equal(got.astype(np.float64), oracle.conv2d_dw_f64(x, dy, R, R, 1, P))
+    dy[dy == 0] = 1.0
+    x[0, 0, H - 1, W - 1] = np.inf
+    x[N - 1, C - 1, 0, 0] = np.nan
+    dy[0, K - 1, Ho - 1, 0] = -np.inf
+    got = isc.isc_conv2d_dw(to_dev(torch, x), to_dev(torch, dy), R, R, 1, P).cpu().numpy()
+    want = np.zeros((K, C, R, R))  # over the nonzero inputs only
+    xp = np.pad(x.astype(np.float64), ((0, 0), (0, 0), (P, P), (P, P)))
+    d = dy.astype(np.float64)
+    with np.errstate(invalid="ignore"):
+        for r in range(R):
+            for s in range(R):
+                v = xp[:, :, r:r + Ho, s:s + Wo]
+                fin = np.where(np.isfinite(v), v, 0.0)
+                # the finite inputs against the finite gradients, then every
+                # term with an infinity or NaN on either side
+                want[:, :, r, s] = np.einsum("nkij,ncij->kc", np.where(np.isfinite(d), d, 0.0), fin)
+                for n, c, i, j in np.argwhere(~np.isfinite(v)):
+                    want[:, c, r, s] += d[n, :, i, j] * v[n, c, i, j]
+                for n, k, i, j in np.argwhere(~np.isfinite(d)):
+                    nzv = np.isfinite(v[n, :, i, j]) & (v[n, :, i, j] != 0)
+                    want[k, nzv, r, s] += d[n, k, i, j] * v[n, nzv, i, j]
+    assert np.array_equal(got.astype(np.float64), want, equal_nan=True)

@@ -50,36 +50,38 @@ def test_walk_tables_exact(tmp_path, R):
         pytest.skip("ROCm toolchain not available")
     B.generate()
     src = tmp_path / "walks.hip"
-    tiles = [(t + (1,))[:5] for t in G.WALK_TILES + G.RING_TILES if t[0] == R]
+    tiles = [(t + (1,))[:5] + (0,) for t in G.WALK_TILES + G.RING_TILES if t[0] == R]
+    tiles += [t + (1, 1) for t in G.GRAD_TILES if t[0] == R]
     src.write_text('#include "sparse_tile.hpp"\n' + "\n".join(
-        """__global__ __launch_bounds__(64) void k_{1}_{2}_{3}_{4}(const float *x, float *y) {{
-    using W = isc::tile::AsmWalk<{0}, {1}, {2}, {3}, {4}>;
+        """__global__ __launch_bounds__(64) void k_{1}_{2}_{3}_{4}_{5}(const float *x, float *y) {{
+    using W = isc::tile::{6}<{0}, {1}, {2}, {3}, {4}>;
     unsigned long long m[W::kChunks];
     float v[W::kChunks], acc[{1} * {2} * {4}], w[{0} * {0} * {4}];
     for (int i = 0; i < W::kChunks; ++i) {{ v[i] = x[i * 64 + threadIdx.x]; m[i] = __ballot(v[i] != 0.0f); }}
     for (int i = 0; i < {0} * {0} * {4}; ++i) w[i] = x[4096 + i * 64 + threadIdx.x];
-    for (int i = 0; i < {1} * {2} * {4}; ++i) acc[i] = 0.0f;
+    for (int i = 0; i < {1} * {2} * {4}; ++i) acc[i] = x[16384 + i * 64 + threadIdx.x];
     W::run(m, v, acc, w);
     for (int i = 0; i < {1} * {2} * {4}; ++i) y[i * 64 + threadIdx.x] = acc[i];
-}}""".format(*t) for t in tiles))
+    for (int i = 0; i < {0} * {0} * {4}; ++i) y[32768 + i * 64 + threadIdx.x] = w[i];
+}}""".format(*t, "AsmGradWalk" if t[5] else "AsmWalk") for t in tiles))
     obj = str(tmp_path / "walks.o")
     subprocess.run([B.HIPCC] + B.DEVICE_FLAGS + ["--offload-device-only", "--no-gpu-bundle-output", "-c", str(src),
                                                  "-o", obj], check=True, capture_output=True)
     text = subprocess.run([os.path.join(LLVM, "llvm-objdump"), "-d", "--mcpu=gfx950", obj], check=True,
                           capture_output=True, text=True).stdout
-    parts = re.split(r"(?m)^[0-9a-f]+ <_Z\S*k_(\d+)_(\d+)_(\d)_(\d)\S*>:", text)
+    parts = re.split(r"(?m)^[0-9a-f]+ <_Z\S*k_(\d+)_(\d+)_(\d)_(\d)_(\d)\S*>:", text)
     found = {}
-    for i in range(1, len(parts), 5):
-        s = walks(parts[i + 4])
+    for i in range(1, len(parts), 6):
+        s = walks(parts[i + 5])
         assert len(s) == 1
-        found[(R, int(parts[i]), int(parts[i + 1]), int(parts[i + 2]), int(parts[i + 3]))] = next(iter(s.values()))
+        found[(R, int(parts[i]), int(parts[i + 1]), int(parts[i + 2]), int(parts[i + 3]), int(parts[i + 4]))] = next(iter(s.values()))
     assert sorted(found) == sorted(tiles)
     for tile, site in found.items():
         check_walk(*tile, site)
 
 
-def check_walk(R, TH, TW, same, kpl, site):
-    what = (R, TH, TW, same, kpl)
+def check_walk(R, TH, TW, same, kpl, grad, site):
+    what = (R, TH, TW, same, kpl, grad)
     pos = G.walk_positions(R, TH, TW, same)
     nq = len(pos)
     chunks = -(-nq // G.WALK_CHUNK)
@@ -123,7 +125,8 @@ def check_walk(R, TH, TW, same, kpl, site):
         assert find[0][2][1] == masks[e] and find[1][2][0] == masks[e], (what, i)
         assert number(find[2][2][-1]) == stride and find[3][2][1] == tbl and body[-1][2][0] == nxt, (what, i)
         for t, (a, k) in zip(fmas, taps):
-            assert t[2][1] == v and acc.setdefault(a, t[2][0]) == t[2][0] and wreg.setdefault(k, t[2][2]) == t[2][2]
+            ra, rw = (t[2][2], t[2][0]) if grad else (t[2][0], t[2][2])
+            assert t[2][1] == v and acc.setdefault(a, ra) == ra and wreg.setdefault(k, rw) == rw, (what, i)
     assert len(set(masks.values())) == chunks and len(set(xreg.values())) == chunks, what
     assert len(set(acc.values())) == TH * TW * kpl and len(set(wreg.values())) == R * R * kpl, what
     assert not set(acc.values()) & (set(wreg.values()) | set(xreg.values())), what
