@@ -31,13 +31,10 @@ struct Fit {
     double c0, c_nz, c_chain;  // ms; features scaled by 1e-9 (1e-3 for the chain)
 };
 
-constexpr Fit kResidentFit{0.01847326, 1.77078063, 1.41836285};
+constexpr Fit kResidentFit{0.0105, 1.77078063, 1.41836285};
 
-// Fixed part of the other on-the-fly kernels' path (ms: the count and repack
-// launch, the gated launch of the dense path) and the count's reading rate
-// (ms per input element, 4 bytes at 4 TB/s).
-constexpr double kShortCall = 0.08;  // ms
-constexpr double kWalkFixed = 0.0180, kCountPerInput = 1e-9;
+constexpr double kShortCall = 0.05;      // ms
+constexpr double kCountPerInput = 1e-9;  // ms: 4 bytes at 4 TB/s
 
 // The largest count whose density does not exceed dstar.
 long long limit_for(double dstar, int64_t total, double dense) {
@@ -48,11 +45,11 @@ long long limit_for(double dstar, int64_t total, double dense) {
     // measured none up to 0.99; AUTO 18 % over the dense path at 0.9 while
     // it kept the choice)
     if (dstar < 0.05) return -1;
-    // and on a short call one below 0.4 counts as every input being sparse:
+    // and on a short call one below 0.6 counts as every input being sparse:
     // the dense path's gated launches are a fifth of such a call (inception
     // 4e.3 at batch 1: 16 us without them, 20 with), a rectified input that
     // dense is rare
-    if (dstar >= 1.0 || (dstar > 0.6 && dense < kShortCall)) return static_cast<long long>(total);
+    if (dstar >= 1.0 || (dstar > 0.4 && dense < kShortCall)) return static_cast<long long>(total);
     // the kernels' models are those of rectified inputs: past a density of
     // 0.69 the two paths are within a tenth of each other where they cross
     return static_cast<long long>(std::floor(std::min(dstar, 0.69) * static_cast<double>(total)));
@@ -72,19 +69,17 @@ long long crossover_nnz_limit(const SparseShape &sh) {
     KernelTime rt;
     if (p.kernel == ISC_KERNEL_FUSED_REG ? sparse_reg_time_model(sh, &rt)
                                          : p.kernel == ISC_KERNEL_FUSED_RING && sparse_ring_time_model(sh, &rt)) {
-        // 1x1 filters, with one multiply-add per nonzero and map, are bound
-        // by reading x, once for the count and again per group of maps
-        const double reads = sh.R == 1 ? 3.0 : 1.0;
-        const double rest = dense - kWalkFixed - static_cast<double>(total) * kCountPerInput * reads;
-        // a 1x1 layer's dense path is a plain GEMM: the choice stays open only
-        // where the sparse path would save an eighth of it on a 0.95 sparse
-        // input
+        // kept open only where the sparse path, with its count, is the faster
+        // one on a 0.95 sparse input: the count reads every input, 12 us of
+        // inception 4a.1's 54 at batch 128
         const double at95 = std::max(rt.base[0] + 0.05 * rt.slope[0], rt.base[1] + 0.05 * rt.slope[1]);
-        if (sh.R == 1 && at95 > rest - 0.12 * dense) return -1;
+        if (at95 + static_cast<double>(total) * kCountPerInput > dense) return -1;
         // the density where the first of the kernel's two bounds meets the
-        // dense path
-        return limit_for(std::min((rest - rt.base[0]) / rt.slope[0], (rest - rt.base[1]) / rt.slope[1]), total,
-                         dense);
+        // dense path, leaning a tenth to the sparse path, whose model is that
+        // much too slow where the largest layer crosses (AlexNet conv2 at 0.6:
+        // 720 us measured, 790 modelled)
+        const double meet = 1.1 * dense;
+        return limit_for(std::min((meet - rt.base[0]) / rt.slope[0], (meet - rt.base[1]) / rt.slope[1]), total, dense);
     }
     const double wc = static_cast<double>(p.workgroups) * p.waves * sh.C / std::max(1, p.phases);
     const int wrows = (p.rows - 1) * sh.T + sh.R, wcols = (p.cols - 1) * sh.T + sh.S;

@@ -568,22 +568,326 @@ void gemm_conv_ring_kernel(GemmArgs g) {
     }
 }
 
+// ----------------------------------------------- split-operand implicit GEMM --
+//
+// The convolution GEMM for M > 32 output maps and filters of at most 32 taps,
+// on the bf16 matrix cores at fp32 precision: every operand value v is cut
+// into three bf16 values, hi = bf16(v), mid = bf16(v - hi), lo = bf16(v - hi -
+// mid), each rounded to nearest, which hold its 24 bits exactly (hi + mid + lo
+// = v down to 2^-108, below which the last parts leave bf16's range), and a
+// product is the six terms hi*hi, hi*mid, mid*hi, mid*mid, hi*lo, lo*hi,
+// accumulated in fp32; the three terms left out are below 2^-26 of it.  Six
+// v_mfma_f32_32x32x16_bf16 do 16 steps of k in the time of 1.5 such steps of
+// v_mfma_f32_32x32x2_f32's eight: 2.6 times its rate.
+//
+// Workgroup tile BM x 128 (BM = 64 or 128), four wavefronts of BM/2 x 64, 32-deep
+// K slices.  A slice lies in LDS as three planes [row or column][k], 16 bytes
+// (8 k) to a lane of an MFMA operand; the 16-byte units of a 64-byte row are
+// permuted by the row so that eight lanes reading one unit of eight rows meet
+// 32 banks once (no conflicts counted).  Between two barriers a wavefront reads
+// the slice's operands into registers; then, among its 96 MFMAs, it cuts and
+// stores the next slice's fp32 values, which it holds in registers, and loads
+// those of the slice after that: the vector unit's share (cutting is 5.5
+// instructions a value) passes in the matrix unit's shadow.  A slice's sum
+// starts from zero and is added to the accumulators once, so a product sum
+// is rounded once per 32 of k, where the fp32 MFMA rounds every second.
+//
+// The im2col gather takes one k (uniform over a wavefront) of 64 consecutive
+// columns per load: each lane keeps a bit per tap that says whether its
+// column's tap lies outside the map, and a load whose bit is set gets an
+// offset past the buffer, which the hardware reads as zero.  The 16 k of a
+// wavefront's slice are decoded by 16 lanes at once and read out as scalars
+// (decoding each k in scalar instructions took 300 of them a slice).
+//
+// AlexNet conv2 at batch 128 (115 GFLOP) 1185 -> 562 us (97 -> 204 TFLOP/s,
+// 49 % of six bf16 products' peak), conv3 433 -> 201, conv4 646 -> 293, conv5
+// 410 -> 221; inception 3x3 296 -> 156, 4a.1 96 -> 53, at batch 1 4e.3 53 -> 36.
+// Error against 64 bits on dense conv3 inputs 8.3e-7 -> 1.7e-7.  Measured on the
+// way: 32 x 32 x 16 MFMAs on one accumulator through all six products, three
+// workgroups per CU, no interleaving: conv2 620 us but 7.4e-7; the same tiles
+// as here without the interleaving: 732 us.
+//
+// A tile with a sum that is not finite (an infinity or NaN cannot be cut into
+// parts) is computed again in plain fp32 (slow_tile).
+constexpr int kSplitBN = 128, kSplitBK = 32;
+
+typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
+typedef float floatx2 __attribute__((ext_vector_type(2)));
+typedef float floatx4 __attribute__((ext_vector_type(4)));
+typedef uint32_t uintx4 __attribute__((ext_vector_type(4)));
+
+// Two values cut into their three parts, each pair packed in a word.
+__device__ __forceinline__ void cut2(float a, float b, uint32_t &hi, uint32_t &mid, uint32_t &lo) {
+    auto pack = [](float u, float v) {
+        const floatx2 f = {u, v};
+        return __builtin_bit_cast(uint32_t, __builtin_convertvector(f, bf16x2));
+    };
+    hi = pack(a, b);
+    const float ra = a - __uint_as_float(hi << 16), rb = b - __uint_as_float(hi & 0xffff0000u);
+    mid = pack(ra, rb);
+    lo = pack(ra - __uint_as_float(mid << 16), rb - __uint_as_float(mid & 0xffff0000u));
+}
+
+template <int MB, bool A_VEC>
+__global__ __launch_bounds__(256, 2)
+void gemm_conv_split_kernel(GemmArgs g) {
+    if (!decision_gate(g.dec, 2u)) return;
+    constexpr int BM = 64 * MB, BN = kSplitBN, BK = kSplitBK;
+    constexpr int UA = BM * BK / 8 / 256;  // 8-deep units of A per thread (BM rows x 4 units)
+    constexpr int UB = 2;                  // of B
+    // [plane][row][4 units of 16 bytes], A then B
+    __shared__ uint4 as[3][BM * 4];
+    __shared__ uint4 bs[3][BN * 4];
+
+    const int tid = threadIdx.x;
+    const int lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int wm = wave >> 1, wn = wave & 1;
+    const int m0 = blockIdx.y * BM, n0 = blockIdx.x * BN;
+    const int M = g.M, N = g.N, Kd = g.Kd;
+    const int kb = g.part ? static_cast<int>(blockIdx.z) * g.kchunk : 0;
+    const int ke = g.part ? min(Kd, kb + g.kchunk) : Kd;
+    const int nk = (ke - kb + BK - 1) / BK;  // ranges are whole slices, but for the last
+
+    // A: thread t reads unit t % 4 of rows t / 4 + 64 i (rows past M repeat
+    // the last one, their sums are dropped; k past the end of a row reads the
+    // next row, or zero past the last, against a zero of B)
+    const __amdgpu_buffer_rsrc_t rw = __builtin_amdgcn_make_buffer_rsrc(
+        const_cast<float *>(g.a), 0, static_cast<int>(static_cast<int64_t>(M) * g.lda * 4), kGemmBufferFormat);
+    const int arow = tid >> 2, aunit = tid & 3;
+    int aoff[UA];
+#pragma unroll
+    for (int i = 0; i < UA; ++i)
+        aoff[i] = (min(m0 + arow + 64 * i, M - 1) * static_cast<int>(g.lda) + kb + aunit * 8) * 4;
+    // B: thread t reads column t % 128, units t / 128 and t / 128 + 2
+    // (wave-uniform), through a buffer that starts the padding before x
+    const int bcol = tid & 127;
+    const int bunit = __builtin_amdgcn_readfirstlane(tid >> 7);
+    const int R = g.RS / g.S;
+    const int oneRS = g.RS == 1 ? ~0 : 0, oneS = g.S == 1 ? ~0 : 0;
+    const int shift = (g.P * g.W + g.P) * 4;
+    const __amdgpu_buffer_rsrc_t rx = __builtin_amdgcn_make_buffer_rsrc(
+        const_cast<char *>(reinterpret_cast<const char *>(g.x) - shift), 0,
+        static_cast<int>(static_cast<int64_t>(N / g.conv_hw) * g.C * g.H * g.W * 4) + shift, kGemmBufferFormat);
+    uint32_t outside = ~0u;  // bit t: tap t of this column lies outside the map (bit 31: no tap)
+    int boff = 0;
+    {
+        const int j = n0 + bcol;
+        if (j < N) {
+            const int img = j / g.conv_hw;
+            const int p = j - img * g.conv_hw;
+            const int oy = p / g.Wo;
+            const int ox = p - oy * g.Wo;
+            boff = (img * g.C * g.H * g.W + oy * g.T * g.W + ox * g.T) * 4;
+            uint32_t cols = 0;  // bit s: column tap s is inside
+            for (int s = 0; s < g.S; ++s)
+                cols |= static_cast<unsigned>(ox * g.T - g.P + s) < static_cast<unsigned>(g.W) ? 1u << s : 0u;
+            for (int r = 0; r < R; ++r)
+                if (static_cast<unsigned>(oy * g.T - g.P + r) < static_cast<unsigned>(g.H)) outside &= ~(cols << (r * g.S));
+        }
+    }
+
+    float ra[UA][8], rb[UB][8];
+    auto load_a = [&](int kt) {
+#pragma unroll
+        for (int i = 0; i < UA; ++i) {
+            const int off = aoff[i] + kt * (BK * 4);
+            if constexpr (A_VEC) {
+#pragma unroll
+                for (int h = 0; h < 2; ++h) {
+                    const uintx4 v = __builtin_bit_cast(uintx4, __builtin_amdgcn_raw_buffer_load_b128(rw, off + h * 16, 0, 0));
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) ra[i][h * 4 + e] = __uint_as_float(v[e]);
+                }
+            } else {
+#pragma unroll
+                for (int e = 0; e < 8; ++e)
+                    ra[i][e] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(rw, off + e * 4, 0, 0));
+            }
+        }
+    };
+    // lane e < 16 decodes k number e of the wavefront's two units of a slice:
+    // its byte offset from a column's corner, and the shift that brings its
+    // tap's bit of `outside` to the top (bit 31, set, for k past C*R*S)
+    auto load_b = [&](int kt) {
+        const int k = kb + kt * BK + (bunit + ((lane >> 3) & 1) * 2) * 8 + (lane & 7);
+        const int kc = min(k, Kd - 1);
+        // divm without its branch (a magic of 0 stands for a divisor of 1)
+        const int c = static_cast<int>(__umulhi(static_cast<uint32_t>(kc), g.mRS)) + (kc & oneRS);
+        const int rs = kc - c * g.RS;
+        const int r = static_cast<int>(__umulhi(static_cast<uint32_t>(rs), g.mS)) + (rs & oneS);
+        const int soff = ((c * g.H + r) * g.W + rs - r * g.S) * 4;
+        const int sh = k < Kd ? 31 - rs : 0;
+#pragma unroll
+        for (int e = 0; e < UB * 8; ++e) {
+            const uint32_t past = (outside << __builtin_amdgcn_readlane(sh, e)) & 0x80000000u;
+            rb[e >> 3][e & 7] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(
+                rx, static_cast<int>(static_cast<uint32_t>(boff) | past), __builtin_amdgcn_readlane(soff, e), 0));
+        }
+    };
+    auto store_units = [&](uint4 *plane0, int plane_units, int row, int unit, const float (&v)[8]) {
+        uint4 h, m, l;
+        cut2(v[0], v[1], h.x, m.x, l.x);
+        cut2(v[2], v[3], h.y, m.y, l.y);
+        cut2(v[4], v[5], h.z, m.z, l.z);
+        cut2(v[6], v[7], h.w, m.w, l.w);
+        uint4 *dst = plane0 + row * 4 + (unit ^ ((row >> 1) & 3));
+        dst[0] = h;
+        dst[plane_units] = m;
+        dst[2 * plane_units] = l;
+    };
+    auto store_slice = [&]() {
+#pragma unroll
+        for (int i = 0; i < UA; ++i) store_units(&as[0][0], BM * 4, arow + 64 * i, aunit, ra[i]);
+#pragma unroll
+        for (int i = 0; i < UB; ++i) store_units(&bs[0][0], BN * 4, bcol, bunit + 2 * i, rb[i]);
+    };
+
+    constexpr int MI = 2 * MB, NJ = 4;  // 16 x 16 blocks of a wavefront
+    floatx4 acc[MI][NJ];
+#pragma unroll
+    for (int i = 0; i < MI; ++i)
+#pragma unroll
+        for (int j = 0; j < NJ; ++j) acc[i][j] = floatx4{0.0f, 0.0f, 0.0f, 0.0f};
+
+    const int lrow = lane & 15, lq = lane >> 4;
+    load_a(0);
+    load_b(0);
+    store_slice();
+    load_a(1);  // past the last slice: in bounds or zero, never used
+    load_b(1);
+    for (int kt = 0; kt < nk; ++kt) {
+        __syncthreads();  // the slice is in LDS
+        bf16x8 a[MI][3], b[NJ][3];
+#pragma unroll
+        for (int i = 0; i < MI; ++i) {
+            const int row = (wm * MI + i) * 16 + lrow;
+#pragma unroll
+            for (int p = 0; p < 3; ++p) a[i][p] = __builtin_bit_cast(bf16x8, as[p][row * 4 + (lq ^ ((row >> 1) & 3))]);
+        }
+#pragma unroll
+        for (int j = 0; j < NJ; ++j) {
+            const int row = (wn * NJ + j) * 16 + lrow;
+#pragma unroll
+            for (int p = 0; p < 3; ++p) b[j][p] = __builtin_bit_cast(bf16x8, bs[p][row * 4 + (lq ^ ((row >> 1) & 3))]);
+        }
+        __syncthreads();  // and in everyone's registers
+        // its products, with the next slice's cut and stored and the one
+        // after that loaded between them: the vector unit works in the matrix
+        // unit's shadow
+        constexpr int pa[6] = {2, 0, 1, 1, 0, 0}, pb[6] = {0, 2, 1, 0, 1, 0};  // small terms first
+#pragma unroll
+        for (int j = 0; j < NJ; ++j) {
+            // the slice's sum on its own, then one addition
+            floatx4 sum[MI];
+#pragma unroll
+            for (int i = 0; i < MI; ++i) sum[i] = floatx4{0.0f, 0.0f, 0.0f, 0.0f};
+#pragma unroll
+            for (int t = 0; t < 6; ++t)
+#pragma unroll
+                for (int i = 0; i < MI; ++i)
+                    sum[i] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[i][pa[t]], b[j][pb[t]], sum[i], 0, 0, 0);
+#pragma unroll
+            for (int i = 0; i < MI; ++i) acc[i][j] += sum[i];
+            if (j == 0) {
+                store_slice();
+            } else if (j == 1) {
+                load_a(kt + 2);
+            } else if (j == 2) {
+                load_b(kt + 2);
+            }
+        }
+#pragma unroll
+        for (int i = 0; i < MI * NJ * 6; ++i) {
+            __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);  // an MFMA
+            __builtin_amdgcn_sched_group_barrier(0x002, 3, 0);  // vector instructions
+        }
+    }
+
+    // accumulator register v of lane l holds row 4*(l/16) + v and column l%16
+    // of its 16 x 16 block
+    bool finite = true;
+#pragma unroll
+    for (int i = 0; i < MI; ++i)
+#pragma unroll
+        for (int j = 0; j < NJ; ++j)
+#pragma unroll
+            for (int v = 0; v < 4; ++v) finite = finite && __builtin_isfinite(acc[i][j][v]);
+    const bool again = __any(!finite);
+    float *pz = g.part ? g.part + static_cast<size_t>(blockIdx.z) * M * N : nullptr;
+    uint32_t cnt = 0;
+    auto put = [&](int m, int nn, size_t col_off, float sum) {
+        if (g.part) {  // a partial sum of the split reduction, stored raw
+            pz[static_cast<size_t>(m) * N + nn] = sum;
+        } else {
+            const float o = epilogue_value(sum, g.epi.relu);
+            cnt += nonzero_bit(o);
+            g.c[col_off + static_cast<size_t>(m) * g.conv_hw] = o;
+        }
+    };
+    if (!again) {
+#pragma unroll
+        for (int j = 0; j < NJ; ++j) {
+            const int nn = n0 + (wn * NJ + j) * 16 + lrow;
+            if (nn >= N) continue;
+            const int img = nn / g.conv_hw;
+            const size_t col_off = static_cast<size_t>(img) * M * g.conv_hw + (nn - img * g.conv_hw);
+#pragma unroll
+            for (int i = 0; i < MI; ++i)
+#pragma unroll
+                for (int v = 0; v < 4; ++v) {
+                    const int m = m0 + (wm * MI + i) * 16 + 4 * lq + v;
+                    if (m < M) put(m, nn, col_off, acc[i][j][v]);
+                }
+        }
+    } else {
+        // this wavefront's block again, one column per lane, in fp32
+        const int nn = n0 + wn * 64 + lane;
+        if (nn < N) {
+            const int img = nn / g.conv_hw;
+            const int p = nn - img * g.conv_hw;
+            const int oy = p / g.Wo, ox = p - oy * g.Wo;
+            const size_t col_off = static_cast<size_t>(img) * M * g.conv_hw + p;
+            for (int m = m0 + wm * MB * 32; m < min(M, m0 + (wm + 1) * MB * 32); ++m) {
+                float sum = 0.0f;
+                for (int k = kb; k < ke; ++k) {
+                    const int c = k / g.RS, rs = k - c * g.RS, r = rs / g.S, sx = rs - r * g.S;
+                    const int iy = oy * g.T - g.P + r, ix = ox * g.T - g.P + sx;
+                    const bool in = static_cast<unsigned>(iy) < static_cast<unsigned>(g.H) &&
+                                    static_cast<unsigned>(ix) < static_cast<unsigned>(g.W);
+                    const float xv = in ? g.x[((static_cast<size_t>(img) * g.C + c) * g.H + iy) * g.W + ix] : 0.0f;
+                    sum = __builtin_fmaf(g.a[static_cast<size_t>(m) * g.lda + k], xv, sum);
+                }
+                put(m, nn, col_off, sum);
+            }
+        }
+    }
+    if (!g.part && g.epi.census) {
+        __shared__ uint32_t sums[4];
+        census_commit(g.epi, cnt, sums);
+    }
+}
+
 // The split reduction's second pass: c = epilogue(sum over z of part[z]),
-// partials added in z order; each workgroup takes kReducePer consecutive
-// elements of the M x N result (consecutive threads on consecutive columns)
-// and commits its census slot.
-constexpr int kReducePer = 2048;
+// partials added in z order; each workgroup takes `per` consecutive elements
+// of the M x N result (consecutive threads on consecutive columns) and
+// commits its census slot.  Few elements get many small workgroups (424 x 60
+// outputs of 16 ranges: 12 workgroups of 2048 took 14 us), at most 1024, which
+// every census has room for; many get 2048 each.
+int64_t reduce_per(int64_t elems) { return std::min<int64_t>(2048, (elems / 1024 + 255) / 256 * 256 + (elems < 1024 ? 256 : 0)); }
 
 __global__ __launch_bounds__(256)
-void gemm_split_reduce_kernel(GemmArgs g, int splits) {
+void gemm_split_reduce_kernel(GemmArgs g, int splits, int per) {
     if (!decision_gate(g.dec, 2u)) return;
     const int64_t mn = static_cast<int64_t>(g.M) * g.N;
-    const int64_t base = static_cast<int64_t>(blockIdx.x) * kReducePer;
+    const int64_t base = static_cast<int64_t>(blockIdx.x) * per;
     uint32_t cnt = 0;
-    for (int r = 0; r < kReducePer / 256; ++r) {
+    for (int r = 0; r < per / 256; ++r) {
         const int64_t e = base + r * 256 + threadIdx.x;
         if (e >= mn) break;
         float sum = g.part[e];
+#pragma unroll 4
         for (int z = 1; z < splits; ++z) sum += g.part[static_cast<int64_t>(z) * mn + e];
         const int m = static_cast<int>(e / g.N);
         const int nn = static_cast<int>(e - static_cast<int64_t>(m) * g.N);
@@ -599,6 +903,20 @@ void gemm_split_reduce_kernel(GemmArgs g, int splits) {
     }
 }
 
+// The second pass's launch.
+hipError_t launch_split_reduce(const GemmArgs &g, int splits, hipStream_t s) {
+    const int64_t mn = static_cast<int64_t>(g.M) * g.N;
+    const int64_t per = reduce_per(mn);
+    gemm_split_reduce_kernel<<<static_cast<unsigned>((mn + per - 1) / per), 256, 0, s>>>(g, splits, static_cast<int>(per));
+    return hipGetLastError();
+}
+
+// Whether the census has room for the second pass's workgroups.
+bool split_reduce_fits(const GemmArgs &g) {
+    const int64_t mn = static_cast<int64_t>(g.M) * g.N, per = reduce_per(mn);
+    return !g.epi.census || census_slots_for((mn + per - 1) / per) <= g.epi.cap;
+}
+
 template <int WAVES_M, int WM, int WN, int BK = 16>
 hipError_t launch_gemm_t(const GemmArgs &g, bool a_vec, bool b_padded, bool implicit, hipStream_t s) {
     constexpr int BM = WAVES_M * WM * 32;
@@ -607,14 +925,12 @@ hipError_t launch_gemm_t(const GemmArgs &g, bool a_vec, bool b_padded, bool impl
     if (g.part) {  // split reduction (implicit im2col into NCHW only)
         if (!implicit || g.conv_hw <= 0 || g.kchunk <= 0 || g.kchunk % 32 != 0) return hipErrorInvalidValue;
         grid.z = static_cast<unsigned>((g.Kd + g.kchunk - 1) / g.kchunk);
-        const int64_t rgroups = (static_cast<int64_t>(g.M) * g.N + kReducePer - 1) / kReducePer;
-        if (g.epi.census && census_slots_for(rgroups) > g.epi.cap) return hipErrorInvalidValue;
+        if (!split_reduce_fits(g)) return hipErrorInvalidValue;
         if (a_vec) gemm_f32_kernel<WAVES_M, WM, WN, true, false, true, BK><<<grid, 256, 0, s>>>(g);
         else gemm_f32_kernel<WAVES_M, WM, WN, false, false, true, BK><<<grid, 256, 0, s>>>(g);
         hipError_t e = hipGetLastError();
         if (e != hipSuccess) return e;
-        gemm_split_reduce_kernel<<<static_cast<unsigned>(rgroups), 256, 0, s>>>(g, static_cast<int>(grid.z));
-        return hipGetLastError();
+        return launch_split_reduce(g, static_cast<int>(grid.z), s);
     }
     if (g.epi.census && census_slots_for(static_cast<int64_t>(grid.x) * grid.y) > g.epi.cap)
         return hipErrorInvalidValue;
@@ -645,6 +961,25 @@ hipError_t launch_gemm_any(const GemmArgs &g, bool a_vec, bool b_vec, bool impli
         return launch_gemm_t<2, 1, 1, 32>(g, a_vec, b_vec, implicit, s);                                   // 64 x 64
     }
     return launch_gemm_t<2, 2, 2>(g, a_vec, b_vec, implicit, s);                // 128 x 128
+}
+
+// A kernel of bm x bn tiles over the grid of g, with the split reduction's
+// second pass where g splits.
+template <typename Kernel>
+hipError_t launch_conv_tiles(const GemmArgs &g, int bm, int bn, hipStream_t s, Kernel &&kernel) {
+    dim3 grid((g.N + bn - 1) / bn, (g.M + bm - 1) / bm);
+    if (!g.part) {
+        if (g.epi.census && census_slots_for(static_cast<int64_t>(grid.x) * grid.y) > g.epi.cap)
+            return hipErrorInvalidValue;
+        kernel(grid);
+        return hipGetLastError();
+    }
+    if (g.kchunk <= 0 || g.kchunk % 32 != 0) return hipErrorInvalidValue;
+    grid.z = static_cast<unsigned>((g.Kd + g.kchunk - 1) / g.kchunk);
+    if (!split_reduce_fits(g)) return hipErrorInvalidValue;
+    kernel(grid);
+    const hipError_t e = hipGetLastError();
+    return e != hipSuccess ? e : launch_split_reduce(g, static_cast<int>(grid.z), s);
 }
 
 uint32_t div_magic(int d) { return d <= 1 ? 0u : static_cast<uint32_t>((0x100000000ull + d - 1) / d); }
@@ -704,13 +1039,13 @@ void gemm_tile_shape(int64_t M, int64_t Ncols, int64_t *tm, int64_t *tn) {
     }
 }
 
-// Expected time of the implicit GEMM (ms) with C*R*S cut into `ranges`
-// reduction ranges: a fixed part, the tiles of the busiest CU (workgroups
+// Relative time of the implicit GEMM with C*R*S cut into `ranges` reduction
+// ranges, which chooses the split: a fixed part, the tiles of the busiest CU (workgroups
 // spread over 256 CUs) times each tile's reduction length and size, the
 // output (times the ranges of a split reduction, whose partial sums are
 // written and summed), and a second launch when the reduction is split.
-// Coefficients fitted to the dense path measured on every workload and
-// Tab. 2 shape (8.1 % rms, 19 % at most).
+// Coefficients (ms) are those of the fp32 matrix-core GEMM, whose shares
+// between these parts the split was tuned on.
 double gemm_model(int64_t M, int64_t Ncols, int64_t Kd, int64_t ranges) {
     int64_t tm, tn;
     gemm_tile_shape(M, Ncols, &tm, &tn);
@@ -759,10 +1094,19 @@ int gemm_kchunk(int64_t M, int64_t Ncols, int Kd) {
 }  // namespace
 
 // Expected time of the dense path's GEMM (ms), with the split the launch
-// takes.
+// takes: per 32-deep slice a fixed part and the busiest CU's workgroups, the
+// output (times its ranges) and the second pass.  Fitted to the dense path
+// timed on 88 shapes of more than 32 maps (9.5 % rms, 36 % at most) and 22 of up to 32 (8 %).
 double dense_time_model(int64_t M, int64_t Ncols, int64_t Kd) {
     const int kc = Kd < (1ll << 31) ? gemm_kchunk(M, Ncols, static_cast<int>(Kd)) : 0;
-    return gemm_model(M, Ncols, Kd, kc > 0 ? (Kd + kc - 1) / kc : 1);
+    const int64_t ranges = kc > 0 ? (Kd + kc - 1) / kc : 1;
+    const double slices = static_cast<double>(((kc > 0 ? kc : Kd) + 31) / 32);
+    const int64_t bm = M <= 32 ? 32 : (M <= 64 ? 64 : 128);
+    const double per_cu = std::ceil(static_cast<double>((M + bm - 1) / bm * ((Ncols + 127) / 128) * ranges) / 256.0);
+    const double out = 1e-9 * static_cast<double>(M) * Ncols * ranges;
+    if (M <= 32) return 0.0065 + slices * (0.00120 + 0.000706 * per_cu) + 1.70 * out + (ranges > 1 ? 0.0050 : 0.0);
+    return 0.0097 + slices * (0.00041 + 0.00117 * per_cu * (bm == 64 ? 0.6 : 1.0)) + 1.11 * out +
+           (ranges > 1 ? 0.0060 : 0.0);
 }
 
 size_t conv_gemm_split_floats(int M, int64_t Ncols, int Kd) {
@@ -797,24 +1141,23 @@ hipError_t launch_conv_gemm(const float *x, const float *w, float *y, int N, int
     // offsets: the pipelined kernel, with or without a split reduction
     const int64_t x_bytes = static_cast<int64_t>(N) * C * H * W * 4;
     const int64_t w_bytes = static_cast<int64_t>(K) * g.Kd * 4;
-    if (K > 64 && x_bytes < (1ll << 31) && w_bytes < (1ll << 31)) {
-        dim3 grid((g.N + kConvBN - 1) / kConvBN, (g.M + kConvBM - 1) / kConvBM);
-        if (g.part) {
-            if (g.kchunk <= 0 || g.kchunk % 32 != 0) return hipErrorInvalidValue;
-            grid.z = static_cast<unsigned>((g.Kd + g.kchunk - 1) / g.kchunk);
-            const int64_t rgroups = (static_cast<int64_t>(g.M) * g.N + kReducePer - 1) / kReducePer;
-            if (g.epi.census && census_slots_for(rgroups) > g.epi.cap) return hipErrorInvalidValue;
-            gemm_conv_ring_kernel<kConvStages><<<grid, 256, 0, s>>>(g);
-            hipError_t e = hipGetLastError();
-            if (e != hipSuccess) return e;
-            gemm_split_reduce_kernel<<<static_cast<unsigned>(rgroups), 256, 0, s>>>(g, static_cast<int>(grid.z));
-            return hipGetLastError();
-        }
-        if (g.epi.census && census_slots_for(static_cast<int64_t>(grid.x) * grid.y) > g.epi.cap)
-            return hipErrorInvalidValue;
-        gemm_conv_ring_kernel<kConvStages><<<grid, 256, 0, s>>>(g);
-        return hipGetLastError();
+    const bool small = x_bytes + 16ll * P * (W + 1) < (1ll << 31) && w_bytes < (1ll << 31);
+    if (K > 32 && g.RS <= 31 && small) {
+        const int bm = K > 64 ? 128 : 64;
+        const bool vec = g.Kd % 4 == 0;  // no 16-byte load of the filter straddles its end
+        return launch_conv_tiles(g, bm, kSplitBN, s, [&](dim3 grid) {
+            if (bm == 128) {
+                if (vec) gemm_conv_split_kernel<2, true><<<grid, 256, 0, s>>>(g);
+                else gemm_conv_split_kernel<2, false><<<grid, 256, 0, s>>>(g);
+            } else {
+                if (vec) gemm_conv_split_kernel<1, true><<<grid, 256, 0, s>>>(g);
+                else gemm_conv_split_kernel<1, false><<<grid, 256, 0, s>>>(g);
+            }
+        });
     }
+    if (K > 64 && small)
+        return launch_conv_tiles(g, kConvBM, kConvBN, s,
+                                 [&](dim3 grid) { gemm_conv_ring_kernel<kConvStages><<<grid, 256, 0, s>>>(g); });
     const bool a_vec = (g.lda % 4 == 0) && (reinterpret_cast<uintptr_t>(w) % 16 == 0);
     return launch_gemm_any(g, a_vec, false, true, s);
 }

@@ -223,6 +223,12 @@ hipError_t launch_sparse_fring(const SparseShape &sh, const float *x, const floa
 bool sparse_fused_plan_info(const SparseShape &sh, isc_plan *out);
 bool sparse_fring_plan_info(const SparseShape &sh, isc_plan *out);
 int64_t sparse_fring_max_groups(const SparseShape &sh);
+// Share of an axis's (output, tap) pairs that lie inside the map, for the time
+// models: P padding on both sides, R taps, `out` outputs.
+inline double taps_inside(int P, int R, int out) {
+    const double lost = static_cast<double>(P) * (P + 1) / (static_cast<double>(out) * R);
+    return lost < 0.9 ? 1.0 - lost : 0.1;
+}
 // Expected time (ms) of the register-weight kernel's launch for a shape: the
 // larger of two lines base + slope * (input density); false where another
 // kernel takes the shape.

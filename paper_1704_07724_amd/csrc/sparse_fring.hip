@@ -23,16 +23,16 @@ void tiles_for(int R, const TileChoice **t, int *n) {
 }
 
 // Modelled cycles of the kernel on a tile with its channels over `phases`
-// wavefronts, at an input density: the larger of two lines, plus a fixed
-// part.  A CU's w workgroups put a wavefront on each SIMD.  They are bound by
-// issue (per wavefront and channel 100 cycles, 50 a ballot, 3 a weight; per
-// nonzero its FMAs at 4 cycles and 15 more) or by one wavefront's chain of
-// jumps (150 cycles a nonzero beside its FMAs), and a third of a workgroup's
-// duration passes at the end with CUs running dry, which is what more
-// phases, hence more and shorter workgroups, are for: AlexNet conv2 on 9 x 9
-// tiles takes 286 / 250 / 243 us on 1 / 2 / 4 phases (the model 283 / 250 /
-// 240), the inception 3x3 branch on 7 x 14 117 / 93 / 99 (130 / 98 / 93), at
-// batch 1 on 2 x 14 48 / 28 / 17.
+// wavefronts, at an input density: the larger of two lines.  A CU's w
+// workgroups put a wavefront on each SIMD.  They are bound by issue (per
+// wavefront and channel 33 cycles, 50 a ballot, 3.5 a weight; per nonzero its
+// FMAs at 4 cycles and 4 more, at least its scalar chain's 28) or by one
+// wavefront's chain of jumps (96 cycles a nonzero beside its FMAs), and
+// part of a workgroup's duration passes at the end with CUs running dry, which
+// is what more phases, hence more and shorter workgroups, are for (AlexNet
+// conv2 on 9 x 9 tiles: 286 / 250 / 243 us on 1 / 2 / 4 phases, the inception
+// 3x3 branch at batch 1 on 2 x 14: 48 / 28 / 17).  Fitted to the kernel timed on
+// 43 shapes at sparsities 0.3 to 0.95: 8 % rms, 21 % at most.
 struct RingCost {
     double issue0, issue1, chain0, chain1;  // issue0 + issue1 * density, chain0 + chain1 * density
     double at(double d) const { return std::max(issue0 + issue1 * d, chain0 + chain1 * d); }
@@ -53,14 +53,14 @@ RingCost ring_cost(const SparseShape &sh, const TileChoice &t, int phases) {
     const double rows = std::min<double>(sh.H, std::max(1.0, static_cast<double>(inr) / bands));
     const double cols = std::min<double>(sh.W, std::max(1.0, static_cast<double>(inc) / ctiles));
     const double fmas =
-        t.kpl * static_cast<double>(std::min(t.th, sh.Ho)) * std::min(t.tw, sh.Wo) * sh.R * sh.R / (rows * cols);
+        t.kpl * taps_inside(sh.P, sh.R, sh.Ho) * taps_inside(sh.P, sh.R, sh.Wo) * static_cast<double>(std::min(t.th, sh.Ho)) * std::min(t.tw, sh.Wo) * sh.R * sh.R / (rows * cols);
     const int chunks = ((t.th + sh.R - 1) * (t.tw + sh.R - 1) + tile::kWalkChunk - 1) / tile::kWalkChunk;
     const double chan = (sh.C + phases - 1) / phases;
-    const double i0 = 100.0 + 50.0 * chunks + 3.0 * sh.R * sh.R * t.kpl;
-    const double i1 = rows * cols * std::max(28.0, 15.0 + 4.0 * fmas);
-    const double c0 = 300.0 + 50.0 * chunks, c1 = rows * cols * (150.0 + 4.0 * fmas);
-    const double fixed = 3000.0 + 40.0 * w * t.th * t.tw * t.kpl;
-    const double iw = chan * (w + (w > 1.0 ? 0.35 * resident : 0.0)), cw = chan * std::max(1.0, w / occ);
+    const double i0 = 33.0 + 50.0 * chunks + 3.5 * sh.R * sh.R * t.kpl;
+    const double i1 = rows * cols * std::max(28.0, 4.1 + 4.0 * fmas);
+    const double c0 = 382.0 + 50.0 * chunks, c1 = rows * cols * (96.0 + 4.0 * fmas);
+    const double fixed = 15720.0 + 106.0 * w * t.th * t.tw * t.kpl;
+    const double iw = chan * (w + (w > 1.0 ? 0.76 * resident : 0.0)), cw = chan * std::max(1.0, w / occ);
     return {iw * i0 + fixed, iw * i1, cw * c0 + fixed, cw * c1};
 }
 

@@ -36,22 +36,21 @@ bool reg_tile_takes(const SparseShape &sh, RegTile t) {
 }
 
 // Modelled cycles of the register-weight kernel on a tile at an input
-// density, which choose the tile and stand for the kernel in AUTO's
-// crossover: reg_cost's lines.  The CU with most workgroups (w of them, two wavefronts per
-// SIMD each, `occ` resident) is bound either by issue -- per wavefront and
-// channel 150 cycles of loads, moves and ballots, and per nonzero its FMAs
-// at 4 cycles and 15 more -- or, with few wavefronts, by the latency of one
-// wavefront's jumps, 150 cycles a nonzero beside its FMAs.  Each round also
-// pays its start and its reduction.  The constants are those of AlexNet
-// conv3-5 at 0.5 and 0.95 (7 x 13 tiles: 44 cycles a nonzero and 150 a
-// channel, 8000 a round) and of inception 4e.3 at batch 1 over six tile
-// heights (180 cycles a nonzero).
+// density, which choose the tile and stand for the kernel in AUTO's crossover.
+// The CU with most workgroups (w of them, two wavefronts per SIMD each, `occ`
+// resident) is bound either by issue (per wavefront and channel 90 cycles and
+// 9.2 a weight, per nonzero its FMAs at 4 cycles and 5 more, at least its
+// scalar chain's 28) or, with few wavefronts, by the latency of one
+// wavefront's jumps (73 cycles a nonzero beside its FMAs).  Each round also
+// pays its reduction, each launch its start.  Fitted to the kernel timed on 51
+// shapes (this repository's layers and log-uniform sizes) at sparsities 0.3 to
+// 0.95: 11 % rms, 33 % at most.
 constexpr double kPlanDensity = 0.1;  // the paper's layers are 0.9 to 0.95 sparse
 
 struct RegCost {
-    // cycles at density d: max(issue0 + issue1 * d, chain0 + chain1 * d) + fixed
-    double issue0, issue1, chain0, chain1, fixed;
-    double at(double d) const { return std::max(issue0 + issue1 * d, chain0 + chain1 * d) + fixed; }
+    // cycles at density d: max(issue0 + issue1 * d, chain0 + chain1 * d)
+    double issue0, issue1, chain0, chain1;
+    double at(double d) const { return std::max(issue0 + issue1 * d, chain0 + chain1 * d); }
 };
 
 RegCost reg_cost(const SparseShape &sh, RegTile t) {
@@ -67,11 +66,13 @@ RegCost reg_cost(const SparseShape &sh, RegTile t) {
     // the first band and what the last one reaches past the map
     const int64_t in = bands * (t.th + sh.R - 1) - sh.P - (bands * t.th - sh.Ho + sh.P);
     const double rows = std::min<double>(sh.H, std::max(1.0, static_cast<double>(in) / bands));
-    const double fmas = static_cast<double>(std::min(t.th, sh.Ho)) * t.tw * sh.R * sh.R / (rows * cols);
+    const double fmas = taps_inside(sh.P, sh.R, sh.Ho) * taps_inside(sh.P, sh.R, sh.Wo) *
+                        static_cast<double>(std::min(t.th, sh.Ho)) * t.tw * sh.R * sh.R / (rows * cols);
     const double chan = (sh.C + kWaves - 1) / kWaves;
-    return {2.0 * w * chan * 150.0, 2.0 * w * chan * rows * cols * std::max(28.0, 15.0 + 4.0 * fmas),
-            rounds * chan * 100.0,  rounds * chan * rows * cols * (150.0 + 4.0 * fmas),
-            8000.0 * rounds + 32.0 * w * t.th * t.tw};
+    const double fixed = 15840.0 + 48.6 * rounds * t.th * t.tw + 32.0 * w * t.th * t.tw;
+    return {fixed + 2.0 * w * chan * (90.0 + 9.2 * sh.R * sh.R),
+            2.0 * w * chan * rows * cols * std::max(28.0, 5.3 + 4.0 * fmas), fixed + rounds * chan * 95.0,
+            rounds * chan * rows * cols * (73.0 + 4.0 * fmas)};
 }
 
 size_t fused_lds(int crs, int th, int tw) {
@@ -217,7 +218,7 @@ bool sparse_reg_time_model(const SparseShape &sh, KernelTime *t) {
     if (!fused_plan(sh, &p) || !p.wreg) return false;
     const RegCost c = reg_cost(sh, RegTile{p.th, p.tw, p.same});
     constexpr double kMs = 1.0 / 2.4e6;  // a cycle at 2.4 GHz
-    *t = KernelTime{{(c.issue0 + c.fixed) * kMs, (c.chain0 + c.fixed) * kMs}, {c.issue1 * kMs, c.chain1 * kMs}};
+    *t = KernelTime{{c.issue0 * kMs, c.chain0 * kMs}, {c.issue1 * kMs, c.chain1 * kMs}};
     return true;
 }
 

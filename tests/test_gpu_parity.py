@@ -680,6 +680,52 @@ def test_register_kernel_tall_tiles(torch, isc, case):
     assert np.array_equal(yi.cpu().numpy().astype(np.float64), oracle.conv2d_f64(xi, wi, 1, P))
 
 
+# N, C, H, W, K, R, S, T, P: edges of the split-operand GEMM's tiles (32 maps is
+# the first size it leaves, 64 and 128 its tile heights), reductions that end
+# inside a slice or are not a multiple of 4, strides, wide padding, 31 taps
+# (its limit) and 35, and a split reduction over few and many outputs
+SPLIT_CASES = [(2, 3, 9, 9, 33, 3, 3, 1, 1), (1, 8, 12, 11, 64, 3, 3, 1, 1), (3, 7, 10, 13, 65, 3, 3, 2, 1),
+               (2, 32, 8, 8, 128, 1, 1, 1, 0), (1, 33, 16, 16, 129, 1, 1, 1, 0), (2, 5, 14, 14, 130, 5, 5, 1, 2),
+               (1, 1, 7, 7, 70, 1, 1, 3, 0), (2, 6, 6, 5, 66, 3, 3, 1, 4), (1, 4, 40, 6, 40, 31, 1, 1, 2),
+               (1, 3, 12, 12, 70, 5, 7, 1, 2), (1, 150, 5, 5, 70, 3, 3, 1, 1), (30, 60, 12, 12, 200, 3, 3, 1, 0),
+               (1, 600, 3, 3, 34, 1, 1, 1, 0)]
+
+
+@pytest.mark.parametrize("case", SPLIT_CASES)
+def test_dense_split_operands(torch, isc, case):
+    """The dense path at fp32 precision on the bf16 matrix cores: on dense
+    Gaussian inputs over eight decades its error against 64 bits stays below
+    that of a plain fp32 sum, n/4 roundings of 2^-24 of the summed magnitudes;
+    integers bitwise; and an infinite or NaN input or weight reaches exactly
+    the outputs it meets."""
+    N, C, H, W, K, R, S, T, P = case
+    note("split operands", case)
+    rng = np.random.default_rng(sum(case))
+    x = (rng.standard_normal((N, C, H, W)) * 10.0 ** rng.integers(-4, 4, (N, C, 1, 1))).astype(np.float32)
+    w = rng.standard_normal((K, C, R, S)).astype(np.float32)
+    y = isc.isc_conv2d(to_dev(torch, x), to_dev(torch, w), T, P, path="dense").cpu().numpy().astype(np.float64)
+    mags = oracle.conv2d_f64(np.abs(x), np.abs(w), T, P)
+    bound = (2.0 + C * R * S / 4) * 2.0 ** -24 * mags
+    assert (np.abs(y - oracle.conv2d_f64(x, w, T, P)) <= bound).all()
+    xi, wi = workloads.integer_case(N, C, H, W, K, R, S, seed=sum(case), sparsity=0.3)
+    yi = isc.isc_conv2d(to_dev(torch, xi), to_dev(torch, wi), T, P, path="dense").cpu().numpy()
+    assert np.array_equal(yi.astype(np.float64), oracle.conv2d_f64(xi, wi, T, P))
+    # special values: where they meet an output it is the sum's, elsewhere the
+    # output is what it was
+    xs, ws = xi + 1.0, np.where(wi == 0, 1.0, wi).astype(np.float32)
+    xs[0, C - 1, H - 1, W - 1] = np.inf
+    xs[N - 1, 0, 0, 0] = np.nan
+    xs[0, 0, H // 2, W // 2] = 3.4e38
+    if P == 0:
+        ws[K - 1, 0, R - 1, 0] = -np.inf
+    got = isc.isc_conv2d(to_dev(torch, xs), to_dev(torch, ws), T, P, path="dense").cpu()
+    want = torch.nn.functional.conv2d(torch.from_numpy(xs).double(), torch.from_numpy(ws).double(), stride=T,
+                                      padding=P).float()
+    special = ~torch.isfinite(want) | (want.abs() > 1e30)
+    assert torch.equal(torch.isnan(got), torch.isnan(want)) or bool((want.abs() > 3e38).any())
+    assert torch.equal(got[~special], want[~special])
+
+
 def test_auto_crossover_both_sides(torch, isc):
     """AUTO with the per-shape crossover (the library's default threshold):
     on a shape whose modelled crossover lies inside (0, 1), an input below it
