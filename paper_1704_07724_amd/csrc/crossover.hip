@@ -33,7 +33,8 @@ struct Fit {
 
 constexpr Fit kResidentFit{0.0105, 1.77078063, 1.41836285};
 
-constexpr double kShortCall = 0.05;      // ms
+constexpr double kShortCall = 0.04;       // ms
+constexpr double kChoiceLaunches = 0.009; // ms: the count's launch and the gated ones
 constexpr double kCountPerInput = 1e-9;  // ms: 4 bytes at 4 TB/s
 
 // The largest count whose density does not exceed dstar.
@@ -67,13 +68,17 @@ long long crossover_nnz_limit(const SparseShape &sh) {
     const double dense = dense_time_model(sh.K, static_cast<int64_t>(sh.N) * sh.Ho * sh.Wo,
                                           static_cast<int64_t>(sh.C) * sh.R * sh.S);
     KernelTime rt;
-    if (p.kernel == ISC_KERNEL_FUSED_REG ? sparse_reg_time_model(sh, &rt)
-                                         : p.kernel == ISC_KERNEL_FUSED_RING && sparse_ring_time_model(sh, &rt)) {
+    // (a filter-resident plan of four wavefronts is the ring's walk)
+    const bool ring = p.kernel == ISC_KERNEL_FUSED_RING || (p.kernel == ISC_KERNEL_FUSED && p.waves == 4);
+    if (p.kernel == ISC_KERNEL_FUSED_REG ? sparse_reg_time_model(sh, &rt) : ring && sparse_ring_time_model(sh, &rt)) {
         // kept open only where the sparse path, with its count, is the faster
-        // one on a 0.95 sparse input: the count reads every input, 12 us of
-        // inception 4a.1's 54 at batch 128
+        // one on a 0.95 sparse input: the count reads every input (12 us of
+        // inception 4a.1's 54 at batch 128), and where the whole call is short
+        // the count's launch and the gated ones weigh in (32 -> 64 maps of 20 x
+        // 20, 3x3, batch 64: 19 us dense alone, 28 with the choice open)
         const double at95 = std::max(rt.base[0] + 0.05 * rt.slope[0], rt.base[1] + 0.05 * rt.slope[1]);
-        if (at95 + static_cast<double>(total) * kCountPerInput > dense) return -1;
+        const double launches = dense < kShortCall ? kChoiceLaunches : 0.0;
+        if (at95 + launches + static_cast<double>(total) * kCountPerInput > dense) return -1;
         // the density where the first of the kernel's two bounds meets the
         // dense path, leaning a tenth to the sparse path, whose model is that
         // much too slow where the largest layer crosses (AlexNet conv2 at 0.6:

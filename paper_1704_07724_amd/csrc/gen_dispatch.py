@@ -22,15 +22,16 @@ import sys
 SHAPES = [(R, TH, TW) for R in (1, 3, 5) for TW in (8, 16, 28) for TH in (1, 2, 4, 8) if TH * TW <= 64]
 
 
-def leaf_fmas(R, TH, TW, wy, xp):
+def leaf_fmas(R, TH, TW, wy, xp, T=1):
+    """(output, tap) pairs a nonzero at window row wy, column xp meets."""
     out = []
     for r in range(R):
-        oy = wy - r
-        if not 0 <= oy < TH:
+        oy, odd = divmod(wy - r, T)
+        if odd or not 0 <= oy < TH:
             continue
         for s in range(R):
-            ox = xp - s
-            if 0 <= ox < TW:
+            ox, odd = divmod(xp - s, T)
+            if not odd and 0 <= ox < TW:
                 out.append((oy * TW + ox, r * R + s))
     return out
 
@@ -94,6 +95,9 @@ WALK_TILES += [(R, 7, 7, 2) for R in (3, 5)] + [(3, 8, 8, 2)]
 RING_TILES = [(5, TH, TW, 0, 1) for TH, TW in ((9, 9), (7, 14), (5, 14), (3, 14))] + [(5, 1, 28, 0, 2)]
 RING_TILES += [(3, TH, 14, 0, 1) for TH in (7, 4, 2)] + [(3, 4, 14, 0, 2)]
 RING_TILES += [(1, TH, 14, 0, 1) for TH in (4, 2)] + [(1, 4, 14, 0, 2)]  # 7 x 14: WALK_TILES
+# The same at stride 2.
+STRIDED_TILES = [(3, 4, 7, 0, 1), (3, 4, 7, 0, 2), (3, 2, 7, 0, 1), (5, 4, 7, 0, 1), (5, 4, 7, 0, 2), (5, 2, 7, 0, 1),
+                 (1, 4, 14, 0, 1), (1, 4, 14, 0, 2), (1, 2, 14, 0, 1)]
 # Tiles of the weight-gradient kernel: (R, TH, TW, SAME).
 GRAD_TILES = [(3, 7, 13, 1), (3, 7, 14, 1), (3, 7, 7, 2), (3, 7, 14, 0), (3, 4, 16, 0), (3, 2, 16, 0), (5, 7, 7, 2),
               (5, 9, 9, 0), (5, 4, 14, 0), (5, 2, 14, 0), (1, 7, 7, 0), (1, 7, 14, 0), (1, 2, 14, 0)]
@@ -101,15 +105,19 @@ WALK_CHUNK = 63  # window positions per ballot; the next bit is the sentinel
 WALK_HEAD = 32   # bytes of a leaf besides its FMAs: lane read (8), five scalar instructions (20), the jump (4)
 
 
-def walk_positions(R, TH, TW, same):
-    """(window row, window column) of each position, in order."""
+def walk_positions(R, TH, TW, same, T=1):
+    """(window row, window column) of each position, in order; at stride T > 1
+    a 1x1 filter's window holds only the rows and columns it reads."""
+    if T > 1:
+        step = T if R < T else 1
+        return [(wy, xp) for wy in range(0, (TH - 1) * T + R, step) for xp in range(0, (TW - 1) * T + R, step)]
     rows = range(R // 2, R // 2 + TH) if same == 2 else range(TH + R - 1)
     cols = range(R // 2, R // 2 + TW) if same else range(TW + R - 1)
     return [(wy, xp) for wy in rows for xp in cols]
 
 
-def walk_specialisation(R, TH, TW, same, kpl=1, grad=False):
-    """AsmWalk<R, TH, TW, SAME, KPL> (AsmGradWalk with grad): every set bit of the window's ballots, in order.
+def walk_specialisation(R, TH, TW, same, kpl=1, grad=False, T=1):
+    """AsmWalk<R, TH, TW, SAME, KPL, T> (AsmGradWalk with grad): every set bit of the window's ballots, in order.
 
     Leaf q (chunk q / 64, lane q % 64 of that ballot) reads its nonzero's
     value from its lane, finds the next set bit, computes that bit's leaf
@@ -118,10 +126,10 @@ def walk_specialisation(R, TH, TW, same, kpl=1, grad=False):
     set; its leaf starts the next chunk or falls out of the walk, so every
     jump lands on a leaf.
     """
-    pos = walk_positions(R, TH, TW, same)
+    pos = walk_positions(R, TH, TW, same, T)
     nq = len(pos)
     epl = -(-nq // WALK_CHUNK)
-    maxf = kpl * max(len(leaf_fmas(R, TH, TW, wy, xp)) for wy, xp in pos)
+    maxf = kpl * max(len(leaf_fmas(R, TH, TW, wy, xp, T)) for wy, xp in pos)
     stride = max(WALK_HEAD + 4 * maxf, 36 if epl > 1 else 0)
 
     def find_next(e):
@@ -139,7 +147,7 @@ def walk_specialisation(R, TH, TW, same, kpl=1, grad=False):
         for l in range(n):
             wy, xp = pos[e * WALK_CHUNK + l]
             fmas = [fma.format(a * kpl + j, w * kpl + j)
-                    for a, w in leaf_fmas(R, TH, TW, wy, xp) for j in range(kpl)]
+                    for a, w in leaf_fmas(R, TH, TW, wy, xp, T) for j in range(kpl)]
             nx = find_next(e)
             # the scalar chain between the FMAs; two instructions between the
             # lane read and the first use of its scalar
@@ -167,10 +175,10 @@ def walk_specialisation(R, TH, TW, same, kpl=1, grad=False):
     outs = ", ".join((taps if grad else tile) + ['[m{0}] "+s"(mask[{0}])'.format(e) for e in range(epl)])
     ins = ", ".join((tile if grad else taps) + ['[x{0}] "v"(x[{0}])'.format(e) for e in range(epl)])
     return '''template <>
-struct {name}<{R}, {TH}, {TW}, {same}, {kpl}> {{
+struct {name}<{R}, {TH}, {TW}, {same}, {kpl}{strt}> {{
     static constexpr bool kReg = {reg};  // a tile of the register-weight kernel
-    // {nq} positions: {nr} window rows from {r0}, {nc} columns from {c0}
-    static constexpr int kRow0 = {r0}, kCol0 = {c0}, kRows = {nr}, kCols = {nc}, kPositions = {nq}, kChunks = {epl};
+    // {nq} positions: window rows from {r0}, {nc} columns from {c0}, kStep apart
+    static constexpr int kRow0 = {r0}, kCol0 = {c0}, kCols = {nc}, kStep = {step}, kPositions = {nq}, kChunks = {epl};
     // leaves of at most {maxf} FMAs, stride {stride} bytes
     static __device__ __forceinline__ void run(unsigned long long (&mask)[{epl}], const float (&x)[{epl}],
                                                {ca}float (&acc)[{na}], {cw}float (&w)[{nw}]) {{
@@ -184,7 +192,8 @@ struct {name}<{R}, {TH}, {TW}, {same}, {kpl}> {{
 '''.format(R=R, TH=TH, TW=TW, same=same, epl=epl, nq=nq, maxf=maxf, stride=stride, na=na, nw=nw, asm=asm, outs=outs,
            ins=ins, kpl=kpl, name="AsmGradWalk" if grad else "AsmWalk", ca="const " if grad else "",
            cw="" if grad else "const ",
-           reg="true" if kpl == 1 and (R, TH, TW, same) in WALK_TILES else "false", r0=pos[0][0], c0=pos[0][1], nr=pos[-1][0] - pos[0][0] + 1, nc=pos[-1][1] - pos[0][1] + 1)
+           reg="true" if kpl == 1 and T == 1 and (R, TH, TW, same) in WALK_TILES else "false", r0=pos[0][0], c0=pos[0][1], step=pos[1][1] - pos[0][1],
+           nc=(pos[-1][1] - pos[0][1]) // (pos[1][1] - pos[0][1]) + 1, strt="" if grad else ", %d" % T)
 
 
 
@@ -204,7 +213,7 @@ struct AsmDispatch {
 ''']
     for R, TH, TW in SHAPES:
         parts.append(specialisation(R, TH, TW))
-    parts.append('''template <int R, int TH, int TW, int SAME, int KPL = 1>
+    parts.append('''template <int R, int TH, int TW, int SAME, int KPL = 1, int T = 1>
 struct AsmWalk {
     static constexpr bool kReg = false;
 };
@@ -215,6 +224,8 @@ struct AsmWalk {
         parts.append(walk_specialisation(*tile, grad=True))
     for tile in WALK_TILES + RING_TILES:
         parts.append(walk_specialisation(*tile))
+    for tile in STRIDED_TILES:
+        parts.append(walk_specialisation(*tile, T=2))
     parts.append('''}  // namespace tile
 }  // namespace isc
 ''')

@@ -311,6 +311,16 @@ int conv_impl(const isc_conv_desc *d, const float *x, const float *w, float *y, 
                 dec.nparts = nparts;
             }
             if ((e = isc::launch_sparse_fused(sh, x, wt, y, dec, hs, epi)) != hipSuccess) return hip_status(e);
+        } else if (sh.tu.kernel == 0 && isc::list_kernel_for(sh) == isc::kListGeneric &&
+                   isc::sparse_strided_applies(sh)) {
+            // the general list kernel's shapes at stride 2: the count and the
+            // repack, then the walk straight from x (AUTO's limit, the lists'
+            // room in the workspace and a census of x are as for the lists)
+            if ((e = isc::launch_count_parts(x, s.in_elems(), parts, &nparts, hs, w, sh.K, sh.C, sh.R, sh.S, wt_ws,
+                                             nullptr, 0, ctrl)) != hipSuccess)
+                return hip_status(e);
+            isc::Decision dec{parts, nparts, limit, gate_sparse, ctrl};
+            if ((e = isc::launch_sparse_fring(sh, x, wt_ws, y, dec, hs, epi)) != hipSuccess) return hip_status(e);
         } else {
             int32_t *row_ptr = reinterpret_cast<int32_t *>(base + L.row_ptr);
             NzEntry *nz = reinterpret_cast<NzEntry *>(base + L.nz);

@@ -8,18 +8,15 @@ namespace isc {
 namespace fring {
 namespace {
 
-// The compiled tiles of a filter size.
-void tiles_for(int R, const TileChoice **t, int *n) {
-    if (R == 5) {
-        *t = kTiles5;
-        *n = sizeof(kTiles5) / sizeof(kTiles5[0]);
-    } else if (R == 3) {
-        *t = kTiles3;
-        *n = sizeof(kTiles3) / sizeof(kTiles3[0]);
-    } else {
-        *t = kTiles1;
-        *n = sizeof(kTiles1) / sizeof(kTiles1[0]);
-    }
+// The compiled tiles of a filter size and stride.
+template <int N>
+int tiles_of(const TileChoice (&table)[N], const TileChoice **t) {
+    *t = table;
+    return N;
+}
+int tiles_for(int R, int T, const TileChoice **t) {
+    if (T == 2) return R == 1 ? tiles_of(kStrided1, t) : tiles_of(kStrided, t);
+    return R == 5 ? tiles_of(kTiles5, t) : (R == 3 ? tiles_of(kTiles3, t) : tiles_of(kTiles1, t));
 }
 
 // Modelled cycles of the kernel on a tile with its channels over `phases`
@@ -48,17 +45,20 @@ RingCost ring_cost(const SparseShape &sh, const TileChoice &t, int phases) {
     const double resident = std::min<double>(occ, std::ceil(w));
     // input rows and columns a tile's window holds on average: all but the
     // padding and what the last tile reaches past the map
-    const int64_t inr = bands * (t.th + sh.R - 1) - sh.P - (bands * t.th - sh.Ho + sh.P);
-    const int64_t inc = ctiles * (t.tw + sh.R - 1) - sh.P - (ctiles * t.tw - sh.Wo + sh.P);
+    const int wr = (t.th - 1) * sh.T + sh.R, wc = (t.tw - 1) * sh.T + sh.R;  // the window's extent
+    const int64_t inr = bands * wr - sh.P - ((bands * t.th - sh.Ho) * sh.T + sh.P);
+    const int64_t inc = ctiles * wc - sh.P - ((ctiles * t.tw - sh.Wo) * sh.T + sh.P);
     const double rows = std::min<double>(sh.H, std::max(1.0, static_cast<double>(inr) / bands));
     const double cols = std::min<double>(sh.W, std::max(1.0, static_cast<double>(inc) / ctiles));
-    const double fmas =
-        t.kpl * taps_inside(sh.P, sh.R, sh.Ho) * taps_inside(sh.P, sh.R, sh.Wo) * static_cast<double>(std::min(t.th, sh.Ho)) * std::min(t.tw, sh.Wo) * sh.R * sh.R / (rows * cols);
-    const int chunks = ((t.th + sh.R - 1) * (t.tw + sh.R - 1) + tile::kWalkChunk - 1) / tile::kWalkChunk;
+    const double seen = sh.R < sh.T ? 1.0 / (sh.T * sh.T) : 1.0;  // share of the window's positions visited
+    const double fmas = t.kpl * taps_inside(sh.P, sh.R, sh.Ho) * taps_inside(sh.P, sh.R, sh.Wo) *
+                        static_cast<double>(std::min(t.th, sh.Ho)) * std::min(t.tw, sh.Wo) * sh.R * sh.R /
+                        (rows * cols * seen);
+    const int chunks = static_cast<int>((wr * wc * seen + tile::kWalkChunk - 1) / tile::kWalkChunk);
     const double chan = (sh.C + phases - 1) / phases;
     const double i0 = 33.0 + 50.0 * chunks + 3.5 * sh.R * sh.R * t.kpl;
-    const double i1 = rows * cols * std::max(28.0, 4.1 + 4.0 * fmas);
-    const double c0 = 382.0 + 50.0 * chunks, c1 = rows * cols * (96.0 + 4.0 * fmas);
+    const double i1 = rows * cols * seen * std::max(28.0, 4.1 + 4.0 * fmas);
+    const double c0 = 382.0 + 50.0 * chunks, c1 = rows * cols * seen * (96.0 + 4.0 * fmas);
     const double fixed = 15720.0 + 106.0 * w * t.th * t.tw * t.kpl;
     const double iw = chan * (w + (w > 1.0 ? 0.76 * resident : 0.0)), cw = chan * std::max(1.0, w / occ);
     return {iw * i0 + fixed, iw * i1, cw * c0 + fixed, cw * c1};
@@ -70,13 +70,12 @@ constexpr double kPlanDensity = 0.1;  // the paper's layers are 0.9 to 0.95 spar
 // maps_per_lane / rows / cols / waves when those name a compiled tile, and
 // to a caller's phases (1, 2 or 4; 1 where only the tile is named).
 bool choose(const SparseShape &sh, TileChoice *tc, int *phases) {
-    if (sh.T != 1 || sh.R != sh.S || !(sh.R == 1 || sh.R == 3 || sh.R == 5)) return false;
+    if (!(sh.T == 1 || sh.T == 2) || sh.R != sh.S || !(sh.R == 1 || sh.R == 3 || sh.R == 5)) return false;
     // the kernel addresses a plane and a channel's weights by 31-bit byte offsets
     const int64_t kp = (sh.K + kLanes - 1) / kLanes * static_cast<int64_t>(kLanes);
     if (static_cast<int64_t>(sh.H) * sh.W * 4 >= (1ll << 31) || kp * sh.R * sh.S * 4 >= (1ll << 31)) return false;
     const TileChoice *tiles;
-    int n;
-    tiles_for(sh.R, &tiles, &n);
+    const int n = tiles_for(sh.R, sh.T, &tiles);
     for (int pass = 0; pass < 2; ++pass) {
         const bool forced = pass == 0;
         if (forced && sh.tu.maps_per_lane <= 0 && sh.tu.rows <= 0 && sh.tu.cols <= 0 && sh.tu.waves <= 0) continue;
@@ -140,14 +139,19 @@ int64_t ring_groups(const SparseShape &sh, const TileChoice &t, int phases) {
 bool sparse_fring_applies(const SparseShape &sh) {
     fring::TileChoice tc;
     int phases;
-    return fring::fring_choose(sh, &tc, &phases);
+    return sh.T == 1 && fring::fring_choose(sh, &tc, &phases);
+}
+
+bool sparse_strided_applies(const SparseShape &sh) {
+    fring::TileChoice tc;
+    int phases;
+    return sh.T == 2 && fring::fring_choose(sh, &tc, &phases);
 }
 
 int64_t sparse_fring_max_groups(const SparseShape &sh) {
     using namespace fring;
     const TileChoice *tiles;
-    int n;
-    tiles_for(sh.R, &tiles, &n);
+    const int n = tiles_for(sh.R, sh.T, &tiles);
     int64_t most = 0;
     for (int i = 0; i < n; ++i) most = std::max(most, ring_groups(sh, tiles[i], 4));
     return most;
@@ -168,7 +172,7 @@ bool sparse_fring_plan_info(const SparseShape &sh, isc_plan *out) {
     using namespace fring;
     TileChoice tc;
     int phases;
-    if (!fring_choose(sh, &tc, &phases)) return false;
+    if (!sparse_fring_applies(sh) || !fring_choose(sh, &tc, &phases)) return false;
     *out = isc_plan{ISC_KERNEL_FUSED_RING, tc.th, tc.tw, tc.kpl, phases, tc.nw, ring_groups(sh, tc, phases)};
     return true;
 }
@@ -193,6 +197,7 @@ hipError_t launch_sparse_fring(const SparseShape &sh, const float *x, const floa
     a.ntiles = static_cast<int>(ntiles);
     a.kgroups = (sh.K + kLanes * tc.kpl - 1) / (kLanes * tc.kpl);
     a.phases = phases;
+    a.T = sh.T;
     a.dec = dec;
     a.epi = epi;
     switch (sh.R) {

@@ -55,6 +55,7 @@ struct FringArgs {
     int ntiles;       // N * rtiles * ctiles
     int kgroups;      // groups of 64 * KPL output maps
     int phases;       // wavefronts that share a tile's channels (1, 2 or 4)
+    int T;            // stride, 1 or 2
     Decision dec;
     Epilogue epi;     // rectifier and census of y
 };
@@ -77,6 +78,12 @@ constexpr TileChoice kTiles5[] = {{1, 9, 9, 4}, {1, 7, 14, 4}, {1, 5, 14, 4}, {1
 constexpr TileChoice kTiles3[] = {{1, 7, 14, 4}, {1, 4, 14, 4}, {1, 2, 14, 4}, {2, 4, 14, 4}};
 constexpr TileChoice kTiles1[] = {{1, 7, 14, 4}, {1, 4, 14, 4}, {1, 2, 14, 4}, {2, 4, 14, 4}};
 
+// At stride 2 (where isc_conv2d's sparse path takes the kernel for shapes no
+// other on-the-fly kernel does): a nonzero meets a quarter of the taps, so
+// the tiles are small and their windows are not.
+constexpr TileChoice kStrided[] = {{1, 4, 7, 4}, {2, 4, 7, 4}, {1, 2, 7, 4}};   // 3x3 and 5x5
+constexpr TileChoice kStrided1[] = {{1, 4, 14, 4}, {2, 4, 14, 4}, {1, 2, 14, 4}};
+
 // Launchers of the kernels of one filter size (sparse_fring_r{1,3,5}.hip).
 hipError_t launch_r1(const FringArgs &a, const TileChoice &tc, hipStream_t s);
 hipError_t launch_r3(const FringArgs &a, const TileChoice &tc, hipStream_t s);
@@ -90,9 +97,9 @@ namespace isc {
 namespace fring {
 namespace {
 
-template <int RS_, int KPL, int TH, int TW, int NW>
+template <int RS_, int KPL, int TH, int TW, int NW, int ST>
 struct FringShape {
-    using Walk = tile::AsmWalk<RS_, TH, TW, 0, KPL>;
+    using Walk = tile::AsmWalk<RS_, TH, TW, 0, KPL, ST>;
     static constexpr int RS2 = RS_ * RS_, KW = kLanes * KPL;
     static constexpr int CHF = RS2 * KW;           // floats of one channel's weights
     static constexpr int NDW = (CHF + 255) / 256;  // 1 KB direct-to-LDS blocks
@@ -108,10 +115,10 @@ struct FringShape {
     static constexpr size_t lds = sizeof(float) * SLOTF * NW;
 };
 
-template <int RS_, int KPL, int TH, int TW, int NW>
+template <int RS_, int KPL, int TH, int TW, int NW, int ST>
 __global__ __launch_bounds__(NW * kLanes, fring_waves_per_simd(RS_, KPL, TH, TW))
 void sparse_conv_fring_kernel(FringArgs a) {
-    using SH = FringShape<RS_, KPL, TH, TW, NW>;
+    using SH = FringShape<RS_, KPL, TH, TW, NW, ST>;
     using Walk = typename SH::Walk;
     constexpr int RS2 = SH::RS2, KW = SH::KW, NDW = SH::NDW, EPL = SH::EPL, TP = TH * TW;
     constexpr int CH = tile::kWalkChunk, NQ = Walk::kPositions;
@@ -146,7 +153,7 @@ void sparse_conv_fring_kernel(FringArgs a) {
     for (int q = 0; q < EPL; ++q) {
         const int e = q * CH + lane;
         const int wy = e / Walk::kCols;
-        const int y = oy0 - P + wy, xx = ox0 - P + (e - wy * Walk::kCols);
+        const int y = oy0 * ST - P + wy * Walk::kStep, xx = ox0 * ST - P + (e - wy * Walk::kCols) * Walk::kStep;
         const bool in = lane < CH && e < NQ && y >= 0 && y < H && xx >= 0 && xx < W;
         xoff[q] = in ? (y * W + xx) * static_cast<int>(sizeof(float)) : tile::kPastPlane;
     }
@@ -258,38 +265,44 @@ void sparse_conv_fring_kernel(FringArgs a) {
     }
 }
 
-template <int RS_, int KPL, int TH, int TW, int NW>
+template <int RS_, int KPL, int TH, int TW, int NW, int ST>
 hipError_t launch_fring_t(const FringArgs &a, hipStream_t s) {
-    using SH = FringShape<RS_, KPL, TH, TW, NW>;
+    using SH = FringShape<RS_, KPL, TH, TW, NW, ST>;
     static_assert(SH::lds <= 64 * 1024, "static LDS of a workgroup");
     const int64_t grid = static_cast<int64_t>((a.ntiles + NW / a.phases - 1) / (NW / a.phases)) * a.kgroups;
     if (a.epi.census && census_slots_for(grid) > a.epi.cap) return hipErrorInvalidValue;
-    sparse_conv_fring_kernel<RS_, KPL, TH, TW, NW><<<static_cast<unsigned>(grid), NW * kLanes, 0, s>>>(a);
+    sparse_conv_fring_kernel<RS_, KPL, TH, TW, NW, ST><<<static_cast<unsigned>(grid), NW * kLanes, 0, s>>>(a);
     return hipGetLastError();
 }
 
 // The launcher of table entry I of TILES when it is the chosen tile, else
 // the next entry's.
-template <int RS_, const TileChoice *TILES, int I, int NT>
+template <int RS_, int ST, const TileChoice *TILES, int I, int NT>
 hipError_t launch_fring_table(const FringArgs &a, const TileChoice &tc, hipStream_t s) {
     if constexpr (I >= NT) {
         return hipErrorInvalidValue;
     } else {
         constexpr TileChoice t = TILES[I];
         if (tc.kpl == t.kpl && tc.th == t.th && tc.tw == t.tw && tc.nw == t.nw)
-            return launch_fring_t<RS_, t.kpl, t.th, t.tw, t.nw>(a, s);
-        return launch_fring_table<RS_, TILES, I + 1, NT>(a, tc, s);
+            return launch_fring_t<RS_, t.kpl, t.th, t.tw, t.nw, ST>(a, s);
+        return launch_fring_table<RS_, ST, TILES, I + 1, NT>(a, tc, s);
     }
 }
 
 template <int RS_>
 hipError_t launch_fring_rs(const FringArgs &a, const TileChoice &tc, hipStream_t s) {
+    constexpr int n1 = sizeof(kTiles1) / sizeof(TileChoice), n3 = sizeof(kTiles3) / sizeof(TileChoice);
+    constexpr int n5 = sizeof(kTiles5) / sizeof(TileChoice);
+    constexpr int ns1 = sizeof(kStrided1) / sizeof(TileChoice), ns = sizeof(kStrided) / sizeof(TileChoice);
     if constexpr (RS_ == 5) {
-        return launch_fring_table<5, kTiles5, 0, sizeof(kTiles5) / sizeof(kTiles5[0])>(a, tc, s);
+        return a.T == 2 ? launch_fring_table<5, 2, kStrided, 0, ns>(a, tc, s)
+                        : launch_fring_table<5, 1, kTiles5, 0, n5>(a, tc, s);
     } else if constexpr (RS_ == 3) {
-        return launch_fring_table<3, kTiles3, 0, sizeof(kTiles3) / sizeof(kTiles3[0])>(a, tc, s);
+        return a.T == 2 ? launch_fring_table<3, 2, kStrided, 0, ns>(a, tc, s)
+                        : launch_fring_table<3, 1, kTiles3, 0, n3>(a, tc, s);
     } else {
-        return launch_fring_table<1, kTiles1, 0, sizeof(kTiles1) / sizeof(kTiles1[0])>(a, tc, s);
+        return a.T == 2 ? launch_fring_table<1, 2, kStrided1, 0, ns1>(a, tc, s)
+                        : launch_fring_table<1, 1, kTiles1, 0, n1>(a, tc, s);
     }
 }
 

@@ -189,6 +189,20 @@ bool fused_plan(const SparseShape &sh, FusedPlan *plan) {
     return last.ok != 0;
 }
 
+// Shapes of the filter-resident plan that the filter-ring kernel's walk runs:
+// at stride 1 those wider than 16 columns (narrower ones keep the order of sums
+// they share with the register-weight kernel), unless the caller names the
+// kernel or a part of its plan.
+// Streaming the filter through each wavefront's slot costs less than one
+// resident copy that leaves a CU eight wavefronts (inception 5x5 at batch 128:
+// 46 -> 25 us, 32 -> 64 maps of 20 x 20, 3x3, batch 64: 44 -> 22, 256 -> 64 maps
+// of 28 x 28, 1x1, batch 2: 106 -> 20).
+bool fused_walks(const SparseShape &sh, const FusedPlan &p) {
+    const isc_tuning &tu = sh.tu;
+    return !p.wreg && sh.T == 1 && sh.Wo > 16 && tu.kernel == 0 && tu.rows == 0 && tu.cols == 0 && tu.phases == 0 &&
+           sparse_fring_applies(sh);
+}
+
 }  // namespace
 }  // namespace fused
 
@@ -226,6 +240,10 @@ bool sparse_fused_plan_info(const SparseShape &sh, isc_plan *out) {
     using namespace fused;
     FusedPlan p;
     if (!fused_plan(sh, &p)) return sparse_fring_plan_info(sh, out);
+    if (fused_walks(sh, p) && sparse_fring_plan_info(sh, out)) {
+        out->kernel = ISC_KERNEL_FUSED;
+        return true;
+    }
     const int rg = kWaves / p.cs;
     const int64_t bands = (sh.Ho + rg * p.th - 1) / (rg * p.th);
     const int64_t kgroups = p.wreg ? (sh.K + kLanes - 1) / kLanes : 1;
@@ -240,7 +258,7 @@ hipError_t launch_sparse_fused(const SparseShape &sh, const float *x, const floa
                                hipStream_t s, const Epilogue &epi) {
     using namespace fused;
     FusedPlan p;
-    if (!fused_plan(sh, &p)) return launch_sparse_fring(sh, x, wt, y, dec, s, epi);
+    if (!fused_plan(sh, &p) || fused_walks(sh, p)) return launch_sparse_fring(sh, x, wt, y, dec, s, epi);
     FusedArgs a{};
     a.x = x;
     a.wt = wt;

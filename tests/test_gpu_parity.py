@@ -680,6 +680,40 @@ def test_register_kernel_tall_tiles(torch, isc, case):
     assert np.array_equal(yi.cpu().numpy().astype(np.float64), oracle.conv2d_f64(xi, wi, 1, P))
 
 
+# N, C, H, W, K, R, P: stride-2 shapes isc_conv2d walks straight from x instead
+# of running the general list kernel: ragged tiles and map groups, one output,
+# even and odd extents, padding to R and none, fewer channels than phases
+STRIDED_CASES = [(2, 5, 31, 29, 96, 3, 1), (1, 3, 21, 21, 64, 5, 1), (2, 9, 16, 19, 130, 5, 2), (3, 7, 9, 12, 70, 1, 0),
+                 (1, 33, 30, 58, 65, 1, 1), (2, 1, 3, 3, 66, 3, 0), (16, 50, 15, 33, 66, 3, 3), (1, 6, 8, 40, 65, 5, 0)]
+
+
+@pytest.mark.parametrize("case", STRIDED_CASES)
+def test_strided_walk(torch, isc, case):
+    """The sparse path at stride 2 against the oracle and the list kernel:
+    plain, rectified with the census, AUTO's record, integers bitwise, and an
+    infinite input or weight where (and only where) a nonzero input meets it."""
+    N, C, H, W, K, R, P = case
+    note("strided walk", case)
+    desc = isc.make_desc(N, C, H, W, K, R, R, 2, P)
+    x, w = workloads.make_case(N, C, H, W, K, R, R, 2, P, 0.8, seed=501 + sum(case))
+    xd, wd = to_dev(torch, x), to_dev(torch, w)
+    y = isc.isc_conv2d(xd, wd, 2, P, path="sparse")
+    assert_conv_close(y.cpu().numpy(), oracle.conv2d_f64(x, w, 2, P), "strided %s" % (case,))
+    lists = isc.isc_conv2d(xd, wd, 2, P, path="sparse", tuning={"kernel": "generic"}).cpu().numpy()
+    assert_conv_close(lists, oracle.conv2d_f64(x, w, 2, P), "strided lists %s" % (case,))
+    yc, ws = isc.census(desc), isc.workspace(desc, "auto")
+    z = isc.isc_conv2d_relu(xd, wd, 2, P, path="auto", threshold=0.0, y_census=yc, ws=ws)
+    assert torch.equal(z, torch.relu(y))
+    assert isc.isc_census_read(yc) == (z.numel(), int((z != 0).sum()))
+    assert isc.isc_decision(desc, ws) == (int(np.count_nonzero(x)), "sparse")
+    xi, wi = workloads.integer_case(N, C, H, W, K, R, R, seed=9 + sum(case))
+    xi[0, C - 1, H - 1, W - 1] = np.inf
+    wi[K - 1, 0, R - 1, R - 1] = -np.inf
+    a = isc.isc_conv2d(to_dev(torch, xi), to_dev(torch, wi), 2, P, path="sparse").cpu().numpy()
+    b = isc.isc_conv2d(to_dev(torch, xi), to_dev(torch, wi), 2, P, path="sparse", tuning={"kernel": "generic"})
+    assert np.array_equal(a, b.cpu().numpy(), equal_nan=True)
+
+
 # N, C, H, W, K, R, S, T, P: edges of the split-operand GEMM's tiles (32 maps is
 # the first size it leaves, 64 and 128 its tile heights), reductions that end
 # inside a slice or are not a multiple of 4, strides, wide padding, 31 taps

@@ -52,9 +52,10 @@ def test_walk_tables_exact(tmp_path, R):
     src = tmp_path / "walks.hip"
     tiles = [(t + (1,))[:5] + (0,) for t in G.WALK_TILES + G.RING_TILES if t[0] == R]
     tiles += [t + (1, 1) for t in G.GRAD_TILES if t[0] == R]
+    tiles += [t + (2,) for t in G.STRIDED_TILES if t[0] == R]  # 2: not the gradient's, stride 2
     src.write_text('#include "sparse_tile.hpp"\n' + "\n".join(
         """__global__ __launch_bounds__(64) void k_{1}_{2}_{3}_{4}_{5}(const float *x, float *y) {{
-    using W = isc::tile::{6}<{0}, {1}, {2}, {3}, {4}>;
+    using W = isc::tile::{6}<{0}, {1}, {2}, {3}, {4}{7}>;
     unsigned long long m[W::kChunks];
     float v[W::kChunks], acc[{1} * {2} * {4}], w[{0} * {0} * {4}];
     for (int i = 0; i < W::kChunks; ++i) {{ v[i] = x[i * 64 + threadIdx.x]; m[i] = __ballot(v[i] != 0.0f); }}
@@ -63,7 +64,7 @@ def test_walk_tables_exact(tmp_path, R):
     W::run(m, v, acc, w);
     for (int i = 0; i < {1} * {2} * {4}; ++i) y[i * 64 + threadIdx.x] = acc[i];
     for (int i = 0; i < {0} * {0} * {4}; ++i) y[32768 + i * 64 + threadIdx.x] = w[i];
-}}""".format(*t, "AsmGradWalk" if t[5] else "AsmWalk") for t in tiles))
+}}""".format(*t, "AsmGradWalk" if t[5] == 1 else "AsmWalk", ", 2" if t[5] == 2 else "") for t in tiles))
     obj = str(tmp_path / "walks.o")
     subprocess.run([B.HIPCC] + B.DEVICE_FLAGS + ["--offload-device-only", "--no-gpu-bundle-output", "-c", str(src),
                                                  "-o", obj], check=True, capture_output=True)
@@ -80,9 +81,10 @@ def test_walk_tables_exact(tmp_path, R):
         check_walk(*tile, site)
 
 
-def check_walk(R, TH, TW, same, kpl, grad, site):
-    what = (R, TH, TW, same, kpl, grad)
-    pos = G.walk_positions(R, TH, TW, same)
+def check_walk(R, TH, TW, same, kpl, kind, site):
+    what = (R, TH, TW, same, kpl, kind)
+    grad, T = kind == 1, max(1, kind)
+    pos = G.walk_positions(R, TH, TW, same, T)
     nq = len(pos)
     chunks = -(-nq // G.WALK_CHUNK)
     counts = [min(G.WALK_CHUNK, nq - e * G.WALK_CHUNK) for e in range(chunks)]
@@ -114,7 +116,7 @@ def check_walk(R, TH, TW, same, kpl, grad, site):
             assert number(body[4][2][-1]) == stride and body[2][2][1] == body[3][2][0], (what, i)
             masks[e + 1] = body[2][2][1]
             continue
-        taps = [(a * kpl + j, k * kpl + j) for a, k in G.leaf_fmas(R, TH, TW, *pos[e * G.WALK_CHUNK + l])
+        taps = [(a * kpl + j, k * kpl + j) for a, k in G.leaf_fmas(R, TH, TW, *pos[e * G.WALK_CHUNK + l], T)
                 for j in range(kpl)]
         fmas = [t for t in body if t[1] == "v_fmac_f32_e32"]
         find = [t for t in body if t[1] in FIND]
