@@ -4,8 +4,9 @@
 //
 // M_I has row (c, r, s) and column (n, i, j).  The GEMM multiplies the
 // filter tensor, read in place as the row-major K x CRS matrix M_K, by M_I on
-// the fp32 matrix cores (v_mfma_f32_32x32x2_f32) and scatters each output
-// column back to NCHW in its epilogue.  For convolutions it gathers M_I from
+// the matrix cores (convolutions into more than 32 maps on the bf16 ones with
+// fp32 operands cut in three, the rest on v_mfma_f32_32x32x2_f32) and scatters
+// each output column back to NCHW in its epilogue.  For convolutions it gathers M_I from
 // the input while loading its B tiles (implicit im2col: no M_I in memory);
 // im2col_kernel writes M_I out for the stand-alone entry point and for
 // C*R*S >= 2^16.
@@ -570,27 +571,34 @@ void gemm_conv_ring_kernel(GemmArgs g) {
 
 // ----------------------------------------------- split-operand implicit GEMM --
 //
-// The convolution GEMM for M > 32 output maps and filters of at most 32 taps,
+// The convolution GEMM for M > 32 output maps and filters of at most 31 taps,
 // on the bf16 matrix cores at fp32 precision: every operand value v is cut
 // into three bf16 values, hi = bf16(v), mid = bf16(v - hi), lo = bf16(v - hi -
 // mid), each rounded to nearest, which hold its 24 bits exactly (hi + mid + lo
 // = v down to 2^-108, below which the last parts leave bf16's range), and a
 // product is the six terms hi*hi, hi*mid, mid*hi, mid*mid, hi*lo, lo*hi,
 // accumulated in fp32; the three terms left out are below 2^-26 of it.  Six
-// v_mfma_f32_32x32x16_bf16 do 16 steps of k in the time of 1.5 such steps of
-// v_mfma_f32_32x32x2_f32's eight: 2.6 times its rate.
+// v_mfma_f32_16x16x32_bf16 do 32 steps of k for 256 outputs in 48 passes of the
+// matrix unit, the fp32 MFMA in 128.
+//
+// hi * hi has an accumulator of its own, and the five small terms, 2^-8 of it
+// and less, a second one, added at the end: the large sum is rounded once per
+// MFMA (32 of k), as the fp32 MFMA rounds it every second k, and the roundings of
+// the small terms are below its own.  With one accumulator for all six, or a
+// slice's sum from zero added to it, an input 0.99 sparse, whose slices hold
+// a nonzero or two, had up to 1.4 times the error of plain fp32.
 //
 // Workgroup tile BM x 128 (BM = 64 or 128), four wavefronts of BM/2 x 64, 32-deep
 // K slices.  A slice lies in LDS as three planes [row or column][k], 16 bytes
 // (8 k) to a lane of an MFMA operand; the 16-byte units of a 64-byte row are
 // permuted by the row so that eight lanes reading one unit of eight rows meet
-// 32 banks once (no conflicts counted).  Between two barriers a wavefront reads
-// the slice's operands into registers; then, among its 96 MFMAs, it cuts and
-// stores the next slice's fp32 values, which it holds in registers, and loads
-// those of the slice after that: the vector unit's share (cutting is 5.5
-// instructions a value) passes in the matrix unit's shadow.  A slice's sum
-// starts from zero and is added to the accumulators once, so a product sum
-// is rounded once per 32 of k, where the fp32 MFMA rounds every second.
+// 32 banks once (no conflicts counted).  A wavefront holds the slice's A operands
+// in registers and reads B's 16 columns at a time, B's slices taking turns in
+// two buffers: the two sets of accumulators leave no room for both operands
+// (252 of 256 registers; A and B held, 47 spilled, conv2 674 us).  Among the
+// slice's 96 MFMAs it cuts and stores the next slice's fp32 values, which it
+// holds in registers, and loads those of the slice after that: the vector unit's share
+// (cutting is 5.5 instructions a value) passes in the matrix unit's shadow.
 //
 // The im2col gather takes one k (uniform over a wavefront) of 64 consecutive
 // columns per load: each lane keeps a bit per tap that says whether its
@@ -599,17 +607,19 @@ void gemm_conv_ring_kernel(GemmArgs g) {
 // wavefront's slice are decoded by 16 lanes at once and read out as scalars
 // (decoding each k in scalar instructions took 300 of them a slice).
 //
-// AlexNet conv2 at batch 128 (115 GFLOP) 1185 -> 562 us (97 -> 204 TFLOP/s,
-// 49 % of six bf16 products' peak), conv3 433 -> 201, conv4 646 -> 293, conv5
-// 410 -> 221; inception 3x3 296 -> 156, 4a.1 96 -> 53, at batch 1 4e.3 53 -> 36.
-// Error against 64 bits on dense conv3 inputs 8.3e-7 -> 1.7e-7.  Measured on the
-// way: 32 x 32 x 16 MFMAs on one accumulator through all six products, three
-// workgroups per CU, no interleaving: conv2 620 us but 7.4e-7; the same tiles
-// as here without the interleaving: 732 us.
+// AlexNet conv2 at batch 128 (115 GFLOP) 1185 -> 557 us (97 -> 206 TFLOP/s,
+// 49 % of six bf16 products' peak), conv4 646 -> 290, conv5 410 -> 219; inception
+// 3x3 296 -> 153, 4a.1 96 -> 52, at batch 1 4e.3 53 -> 22.  Error against 64 bits on
+// dense conv2 inputs 8.7e-7 -> 3.0e-7, 0.9 sparse 2.7e-7 -> 1.0e-7; 0.99 sparse, 100 maps
+// of 3x3 taps, 5.3e-8 -> 4.4e-8.  Measured on the way: 32 x 32 x 16 MFMAs on one
+// accumulator through all six products, three workgroups per CU, no
+// interleaving: conv2 620 us, 7.4e-7; these tiles without the interleaving: 732 us.
 //
-// A tile with a sum that is not finite (an infinity or NaN cannot be cut into
-// parts) is computed again in plain fp32 (slow_tile).
+// A wavefront's tile with a sum that is not finite (an infinity or NaN cannot
+// be cut into parts), or that is not zero but so small that its operands' last
+// parts may lie below bf16's range, is computed again in plain fp32.
 constexpr int kSplitBN = 128, kSplitBK = 32;
+constexpr float kSplitLeast = 0x1p-90f;
 
 typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
@@ -636,9 +646,9 @@ void gemm_conv_split_kernel(GemmArgs g) {
     constexpr int BM = 64 * MB, BN = kSplitBN, BK = kSplitBK;
     constexpr int UA = BM * BK / 8 / 256;  // 8-deep units of A per thread (BM rows x 4 units)
     constexpr int UB = 2;                  // of B
-    // [plane][row][4 units of 16 bytes], A then B
+    // [plane][row][4 units of 16 bytes]; A, and two slices of B
     __shared__ uint4 as[3][BM * 4];
-    __shared__ uint4 bs[3][BN * 4];
+    __shared__ uint4 bs[2][3][BN * 4];
 
     const int tid = threadIdx.x;
     const int lane = tid & 63;
@@ -737,84 +747,96 @@ void gemm_conv_split_kernel(GemmArgs g) {
         dst[plane_units] = m;
         dst[2 * plane_units] = l;
     };
-    auto store_slice = [&]() {
+    auto store_a = [&]() {
 #pragma unroll
         for (int i = 0; i < UA; ++i) store_units(&as[0][0], BM * 4, arow + 64 * i, aunit, ra[i]);
+    };
+    auto store_b = [&](int buf) {
 #pragma unroll
-        for (int i = 0; i < UB; ++i) store_units(&bs[0][0], BN * 4, bcol, bunit + 2 * i, rb[i]);
+        for (int i = 0; i < UB; ++i) store_units(&bs[buf][0][0], BN * 4, bcol, bunit + 2 * i, rb[i]);
     };
 
     constexpr int MI = 2 * MB, NJ = 4;  // 16 x 16 blocks of a wavefront
-    floatx4 acc[MI][NJ];
+    floatx4 acc[MI][NJ], low[MI][NJ];  // the sums of hi * hi, and of the other terms
 #pragma unroll
     for (int i = 0; i < MI; ++i)
 #pragma unroll
-        for (int j = 0; j < NJ; ++j) acc[i][j] = floatx4{0.0f, 0.0f, 0.0f, 0.0f};
+        for (int j = 0; j < NJ; ++j) acc[i][j] = low[i][j] = floatx4{0.0f, 0.0f, 0.0f, 0.0f};
 
     const int lrow = lane & 15, lq = lane >> 4;
     load_a(0);
     load_b(0);
-    store_slice();
+    store_a();
+    store_b(0);
     load_a(1);  // past the last slice: in bounds or zero, never used
     load_b(1);
     for (int kt = 0; kt < nk; ++kt) {
         __syncthreads();  // the slice is in LDS
-        bf16x8 a[MI][3], b[NJ][3];
+        const int buf = kt & 1;
+        bf16x8 a[MI][3], b[2][3];
 #pragma unroll
         for (int i = 0; i < MI; ++i) {
             const int row = (wm * MI + i) * 16 + lrow;
 #pragma unroll
             for (int p = 0; p < 3; ++p) a[i][p] = __builtin_bit_cast(bf16x8, as[p][row * 4 + (lq ^ ((row >> 1) & 3))]);
         }
-#pragma unroll
-        for (int j = 0; j < NJ; ++j) {
+        auto read_b = [&](int j) {
             const int row = (wn * NJ + j) * 16 + lrow;
 #pragma unroll
-            for (int p = 0; p < 3; ++p) b[j][p] = __builtin_bit_cast(bf16x8, bs[p][row * 4 + (lq ^ ((row >> 1) & 3))]);
-        }
-        __syncthreads();  // and in everyone's registers
+            for (int p = 0; p < 3; ++p)
+                b[j & 1][p] = __builtin_bit_cast(bf16x8, bs[buf][p][row * 4 + (lq ^ ((row >> 1) & 3))]);
+        };
+        read_b(0);
+        __syncthreads();  // the slice of A is in everyone's registers
         // its products, with the next slice's cut and stored and the one
         // after that loaded between them: the vector unit works in the matrix
         // unit's shadow
         constexpr int pa[6] = {2, 0, 1, 1, 0, 0}, pb[6] = {0, 2, 1, 0, 1, 0};  // small terms first
 #pragma unroll
         for (int j = 0; j < NJ; ++j) {
-            // the slice's sum on its own, then one addition
-            floatx4 sum[MI];
+            if (j + 1 < NJ) read_b(j + 1);
 #pragma unroll
-            for (int i = 0; i < MI; ++i) sum[i] = floatx4{0.0f, 0.0f, 0.0f, 0.0f};
-#pragma unroll
-            for (int t = 0; t < 6; ++t)
+            for (int t = 0; t < 5; ++t)
 #pragma unroll
                 for (int i = 0; i < MI; ++i)
-                    sum[i] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[i][pa[t]], b[j][pb[t]], sum[i], 0, 0, 0);
+                    low[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[i][pa[t]], b[j & 1][pb[t]], low[i][j], 0, 0, 0);
 #pragma unroll
-            for (int i = 0; i < MI; ++i) acc[i][j] += sum[i];
+            for (int i = 0; i < MI; ++i)
+                acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[i][0], b[j & 1][0], acc[i][j], 0, 0, 0);
             if (j == 0) {
-                store_slice();
+                store_a();
             } else if (j == 1) {
                 load_a(kt + 2);
+                store_b(buf ^ 1);
             } else if (j == 2) {
                 load_b(kt + 2);
             }
-        }
 #pragma unroll
-        for (int i = 0; i < MI * NJ * 6; ++i) {
-            __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);  // an MFMA
-            __builtin_amdgcn_sched_group_barrier(0x002, 3, 0);  // vector instructions
+            for (int i = 0; i < MI * 6; ++i) {
+                __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);  // an MFMA
+                __builtin_amdgcn_sched_group_barrier(0x002, 2, 0);  // vector instructions
+            }
+            __builtin_amdgcn_sched_barrier(0);
         }
     }
+#pragma unroll
+    for (int i = 0; i < MI; ++i)
+#pragma unroll
+        for (int j = 0; j < NJ; ++j) acc[i][j] += low[i][j];
 
     // accumulator register v of lane l holds row 4*(l/16) + v and column l%16
     // of its 16 x 16 block
-    bool finite = true;
+    bool whole = true;
 #pragma unroll
     for (int i = 0; i < MI; ++i)
 #pragma unroll
         for (int j = 0; j < NJ; ++j)
 #pragma unroll
-            for (int v = 0; v < 4; ++v) finite = finite && __builtin_isfinite(acc[i][j][v]);
-    const bool again = __any(!finite);
+            for (int v = 0; v < 4; ++v) {
+                const float m = __builtin_fabsf(acc[i][j][v]);
+                whole = whole && m < __builtin_inff() && (m == 0.0f || m >= kSplitLeast);
+            }
+    const bool again = __any(!whole);
     float *pz = g.part ? g.part + static_cast<size_t>(blockIdx.z) * M * N : nullptr;
     uint32_t cnt = 0;
     auto put = [&](int m, int nn, size_t col_off, float sum) {
@@ -1137,13 +1159,20 @@ hipError_t launch_conv_gemm(const float *x, const float *w, float *y, int N, int
     g.C = C; g.H = H; g.W = W; g.T = T; g.P = P; g.Wo = Wo; g.RS = R * S; g.S = S;
     g.mRS = div_magic(R * S);
     g.mS = div_magic(S);
-    // more than 64 output maps, operands addressable by 31-bit byte
-    // offsets: the pipelined kernel, with or without a split reduction
+    // operands addressable by 31-bit byte offsets: the split-operand kernel,
+    // with or without a split reduction.  Below 16 products a sum has fewer
+    // roundings in plain fp32 (3 products, 99 % of inputs zero: 2.52e-8 against
+    // 2.56e-8), and moving the outputs takes most of the time.
     const int64_t x_bytes = static_cast<int64_t>(N) * C * H * W * 4;
     const int64_t w_bytes = static_cast<int64_t>(K) * g.Kd * 4;
     const bool small = x_bytes + 16ll * P * (W + 1) < (1ll << 31) && w_bytes < (1ll << 31);
-    if (K > 32 && g.RS <= 31 && small) {
-        const int bm = K > 64 ? 128 : 64;
+    if (K > 32 && g.RS <= 31 && g.Kd >= 16 && small) {
+        // 64 maps of a workgroup where that leaves a compute unit to each (4e.3
+        // at batch 1: 28 -> 22 us; with more workgroups than units the larger
+        // tile reads and cuts half as much per product, conv2 557 against 652)
+        const int64_t ranges = kc > 0 ? (g.Kd + kc - 1) / kc : 1;
+        const int64_t small_tiles = (K + 63ll) / 64 * ((g.N + kSplitBN - 1ll) / kSplitBN);
+        const int bm = K > 64 && small_tiles * ranges > 256 ? 128 : 64;
         const bool vec = g.Kd % 4 == 0;  // no 16-byte load of the filter straddles its end
         return launch_conv_tiles(g, bm, kSplitBN, s, [&](dim3 grid) {
             if (bm == 128) {

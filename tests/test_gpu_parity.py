@@ -741,6 +741,12 @@ def test_dense_split_operands(torch, isc, case):
     mags = oracle.conv2d_f64(np.abs(x), np.abs(w), T, P)
     bound = (2.0 + C * R * S / 4) * 2.0 ** -24 * mags
     assert (np.abs(y - oracle.conv2d_f64(x, w, T, P)) <= bound).all()
+    # so small that the last of an input's three parts is below bf16's range:
+    # the same bound, and half of the least subnormal a rounding
+    tiny = (x * 2.0 ** -110).astype(np.float32)
+    yt = isc.isc_conv2d(to_dev(torch, tiny), to_dev(torch, w), T, P, path="dense").cpu().numpy().astype(np.float64)
+    floor = (1 + C * R * S) * 2.0 ** -150
+    assert (np.abs(yt - oracle.conv2d_f64(tiny, w, T, P)) <= bound * 2.0 ** -110 + floor).all()
     xi, wi = workloads.integer_case(N, C, H, W, K, R, S, seed=sum(case), sparsity=0.3)
     yi = isc.isc_conv2d(to_dev(torch, xi), to_dev(torch, wi), T, P, path="dense").cpu().numpy()
     assert np.array_equal(yi.astype(np.float64), oracle.conv2d_f64(xi, wi, T, P))
