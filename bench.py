@@ -27,7 +27,7 @@ interleaved, rep i of each before rep i + 1 of any.
 
 Prints ONE JSON line: value = dense-equivalent TFLOP/s of the step
 (2*N*K*C*R*S*Ho*Wo per step), speedup against the same GPU's dense path
-(fp32-MFMA GEMM with the im2col gather inside) and against the vendor
+(the matrix-core GEMM with the im2col gather inside) and against the vendor
 library's fp32 convolution, nonzero-MAC/s, the LeNet conv2 sparsity sweep
 0.5 .. 0.99 with roofline fractions per point, the roofline of the dominant
 kernel (HIP events on the launch stream), and the CPU oracle timed on a
@@ -56,6 +56,9 @@ HBM_PEAK_GBS = 8000.0
 VALU_F32_PEAK_TFLOPS = 78.6
 VALU_F32_PACKED_PEAK_TFLOPS = 157.3
 MFMA_F32_PEAK_TFLOPS = 157.3
+# the dense path's GEMM at fp32 precision on the bf16 matrix cores: six bf16
+# products per multiply of the dense bf16 peak (2.5 PFLOP/s)
+MFMA_SPLIT_PEAK_TFLOPS = 2500.0 / 6
 
 
 def dense_flops(layer, Ho, Wo) -> float:
@@ -308,7 +311,11 @@ class LayerRun:
         out["speedup_sparse_vs_dense"] = round(res["t_dense_ms"] / res["t_sparse_ms"], 3)
         out["sparse_kernel_tflops_nonzero"] = round(2 * nzm / (res["t_sparse_kernel_ms"] * 1e-3) / 1e12, 3)
         out["sparse_kernel_frac_valu_peak"] = round(out["sparse_kernel_tflops_nonzero"] / VALU_F32_PEAK_TFLOPS, 4)
-        out["dense_frac_mfma_peak"] = round(f / (res["t_dense_ms"] * 1e-3) / 1e12 / MFMA_F32_PEAK_TFLOPS, 4)
+        # the GEMM with operands cut in three takes K > 32, at most 31 taps
+        # and at least 16 products per output
+        split = L.K > 32 and L.R * L.S <= 31 and L.C * L.R * L.S >= 16
+        peak = MFMA_SPLIT_PEAK_TFLOPS if split else MFMA_F32_PEAK_TFLOPS
+        out["dense_frac_mfma_peak"] = round(f / (res["t_dense_ms"] * 1e-3) / 1e12 / peak, 4)
         return out
 
 
