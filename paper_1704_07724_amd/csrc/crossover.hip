@@ -73,12 +73,12 @@ long long crossover_nnz_limit(const SparseShape &sh) {
     if (p.kernel == ISC_KERNEL_FUSED_REG ? sparse_reg_time_model(sh, &rt) : ring && sparse_ring_time_model(sh, &rt)) {
         // kept open only where the sparse path, with its count, is the faster
         // one on a 0.95 sparse input: the count reads every input (12 us of
-        // inception 4a.1's 54 at batch 128), and its launch and the gated ones
-        // weigh in (32 -> 64 maps of 20 x 20, 3x3, batch 64: 19 us dense alone,
-        // 28 with the choice open; inception 5a.1 at batch 128, 0.95 sparse:
-        // 42 us dense alone, 59 with the choice open and the sparse path taken)
+        // inception 4a.1's 54 at batch 128), and where the whole call is short
+        // the count's launch and the gated ones weigh in (32 -> 64 maps of 20 x
+        // 20, 3x3, batch 64: 19 us dense alone, 28 with the choice open)
         const double at95 = std::max(rt.base[0] + 0.05 * rt.slope[0], rt.base[1] + 0.05 * rt.slope[1]);
-        if (at95 + kChoiceLaunches + static_cast<double>(total) * kCountPerInput > dense) return -1;
+        const double launches = dense < kShortCall ? kChoiceLaunches : 0.0;
+        if (at95 + launches + static_cast<double>(total) * kCountPerInput > dense) return -1;
         // the density where the first of the kernel's two bounds meets the
         // dense path, leaning a tenth to the sparse path, whose model is that
         // much too slow where the largest layer crosses (AlexNet conv2 at 0.6:
