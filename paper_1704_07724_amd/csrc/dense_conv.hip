@@ -892,13 +892,9 @@ void gemm_conv_split_kernel(GemmArgs g) {
 }
 
 // The split reduction's second pass: c = epilogue(sum over z of part[z]),
-// partials added in z order; each workgroup takes `per` consecutive elements
-// of the M x N result (consecutive threads on consecutive columns) and
-// commits its census slot.  Few elements get many small workgroups (424 x 60
-// outputs of 16 ranges: 12 workgroups of 2048 took 14 us), at most 1024, which
-// every census has room for; many get 2048 each.
-int64_t reduce_per(int64_t elems) { return std::min<int64_t>(2048, (elems / 1024 + 255) / 256 * 256 + (elems < 1024 ? 256 : 0)); }
-
+// partials added in z order; each workgroup takes `per` (split_reduce_per)
+// consecutive elements of the M x N result (consecutive threads on consecutive
+// columns) and commits its census slot.
 __global__ __launch_bounds__(256)
 void gemm_split_reduce_kernel(GemmArgs g, int splits, int per) {
     if (!decision_gate(g.dec, 2u)) return;
@@ -928,14 +924,14 @@ void gemm_split_reduce_kernel(GemmArgs g, int splits, int per) {
 // The second pass's launch.
 hipError_t launch_split_reduce(const GemmArgs &g, int splits, hipStream_t s) {
     const int64_t mn = static_cast<int64_t>(g.M) * g.N;
-    const int64_t per = reduce_per(mn);
+    const int64_t per = split_reduce_per(mn);
     gemm_split_reduce_kernel<<<static_cast<unsigned>((mn + per - 1) / per), 256, 0, s>>>(g, splits, static_cast<int>(per));
     return hipGetLastError();
 }
 
 // Whether the census has room for the second pass's workgroups.
 bool split_reduce_fits(const GemmArgs &g) {
-    const int64_t mn = static_cast<int64_t>(g.M) * g.N, per = reduce_per(mn);
+    const int64_t mn = static_cast<int64_t>(g.M) * g.N, per = split_reduce_per(mn);
     return !g.epi.census || census_slots_for((mn + per - 1) / per) <= g.epi.cap;
 }
 
@@ -1033,7 +1029,7 @@ int64_t gemm_max_groups(int64_t M, int64_t Ncols) {
     // the smallest tiles launch_gemm_any picks are 32 rows x 128 columns
     // (M <= 32) and 64 x 64 (M <= 64); the widest grid of any tile is at most
     // ceil(M / 32) * ceil(Ncols / 64), and the split reduction's second pass
-    // ceil(M * Ncols / 2048) <= that
+    // ceil(M * Ncols / 2048) <= that, or 1024 (split_reduce_per)
     return (M + 31) / 32 * ((Ncols + 63) / 64);
 }
 

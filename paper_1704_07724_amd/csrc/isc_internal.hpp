@@ -301,6 +301,15 @@ hipError_t launch_conv_gemm(const float *x, const float *w, float *y, int N, int
 // an M x Ncols x Kd product, 0 when it does not split (grids that fill the
 // chip, or short reductions).
 size_t conv_gemm_split_floats(int M, int64_t Ncols, int Kd);
+// Elements per workgroup of the split reduction's second pass over `elems`
+// outputs, a multiple of its 256 threads: few elements get many small workgroups
+// (424 x 60 outputs of 16 ranges: 12 workgroups of 2048 took 14 us), at most
+// 1024, which every census has room for; many get 2048 each, no more workgroups
+// than the GEMM's smallest tile has.
+constexpr int64_t split_reduce_per(int64_t elems) {
+    const int64_t per = ((elems + 1023) / 1024 + 255) / 256 * 256;
+    return per < 2048 ? per : 2048;
+}
 // Upper bound of the GEMM's workgroups for an M x Ncols product (the census
 // slots its epilogue may write).
 int64_t gemm_max_groups(int64_t M, int64_t Ncols);

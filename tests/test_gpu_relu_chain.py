@@ -145,6 +145,23 @@ def test_relu_dense_materialised_im2col(torch, isc):
     assert isc.isc_census_read(yc) == (want.size, nnz_want)
 
 
+# N, C, H, K: split reductions whose outputs, K*N*H*H, lie just past a multiple
+# of 2^18, where the second pass's workgroups come closest to the census's 1024
+# counts (the 32-map GEMM and the 64-map one)
+@pytest.mark.parametrize("case", [(82, 64, 10, 32), (41, 64, 10, 64), (114, 64, 6, 64)])
+def test_relu_split_reduction_census_room(torch, isc, case):
+    N, C, H, K = case
+    note("relu split reduction census", case)
+    desc = isc.make_desc(N, C, H, H, K, 3, 3, 1, 1)
+    assert isc.isc_workspace_size(desc, "dense") > isc.isc_workspace_size(isc.make_desc(N, 1, H, H, K, 1, 1, 1, 0), "dense")
+    x, w = workloads.integer_case(N, C, H, H, K, 3, 3, seed=sum(case), sparsity=0.5)
+    want, nnz_want = oracle.relu_conv2d_f64(x, w, 1, 1)
+    for path in ("dense", "auto"):
+        _, y, yc, _ = _relu_layer(torch, isc, x, w, 1, 1, path)
+        assert np.array_equal(y.cpu().numpy().astype(np.float64), want)
+        assert isc.isc_census_read(yc) == (want.size, nnz_want)
+
+
 def test_relu_without_census_and_with_repacked_filter(torch, isc):
     N, C, H, W, K, R, S, T, P = 2, 16, 13, 13, 96, 3, 3, 1, 1
     note("relu no census, repacked filter")
