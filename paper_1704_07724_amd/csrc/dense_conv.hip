@@ -595,10 +595,11 @@ void gemm_conv_ring_kernel(GemmArgs g) {
 // 32 banks once (no conflicts counted).  A wavefront holds the slice's A operands
 // in registers and reads B's 16 columns at a time, B's slices taking turns in
 // two buffers: the two sets of accumulators leave no room for both operands
-// (252 of 256 registers; A and B held, 47 spilled, conv2 674 us).  Among the
+// (255 of 256 registers; A and B held, 47 spilled, conv2 674 us).  Among the
 // slice's 96 MFMAs it cuts and stores the next slice's fp32 values, which it
 // holds in registers, and loads those of the slice after that: the vector unit's share
-// (cutting is 5.5 instructions a value) passes in the matrix unit's shadow.
+// (cutting is 5.5 instructions a value, the largest operand one more) passes in
+// the matrix unit's shadow.
 //
 // The im2col gather takes one k (uniform over a wavefront) of 64 consecutive
 // columns per load: each lane keeps a bit per tap that says whether its
@@ -615,11 +616,20 @@ void gemm_conv_ring_kernel(GemmArgs g) {
 // accumulator through all six products, three workgroups per CU, no
 // interleaving: conv2 620 us, 7.4e-7; these tiles without the interleaving: 732 us.
 //
-// A wavefront's tile with a sum that is not finite (an infinity or NaN cannot
-// be cut into parts), or that is not zero but so small that its operands' last
-// parts may lie below bf16's range, is computed again in plain fp32.
+// Where cutting loses bits, a wavefront's tile is computed again in plain fp32.
+// A value's part below bf16's least subnormal, 2^-133, is lost, at most 2^-134
+// of it, so a product loses at most 2^-133 times the largest operand, and below
+// 2^-126 its six terms are rounded at 2^-149 each.  A sum that is no less than
+// kSplitLost times the largest operand, and no less than kSplitLeast, has lost
+// less than 2^-28 a product by either, its own rounding being 2^-24; any other
+// nonzero sum is taken again, as is one that is not finite (an infinity or NaN
+// cannot be cut).  A sum of zero is right unless operands vanished or products
+// underflowed, which only small operands do: where a tile has one, the
+// workgroup reads its operands once more for the least of them.  The largest
+// operand and the vote cost 1 % (conv2 590 -> 597 us, conv5 218 -> 220, 4e.3 at
+// batch 1 none).
 constexpr int kSplitBN = 128, kSplitBK = 32;
-constexpr float kSplitLeast = 0x1p-90f;
+constexpr float kSplitLost = 0x1p-104f, kSplitLeast = 0x1p-112f, kSplitOrdinary = 0x1p16f;
 
 typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
@@ -651,7 +661,7 @@ void gemm_conv_split_kernel(GemmArgs g) {
     __shared__ uint4 bs[2][3][BN * 4];
 
     const int tid = threadIdx.x;
-    const int lane = tid & 63;
+    int lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int wm = wave >> 1, wn = wave & 1;
     const int m0 = blockIdx.y * BM, n0 = blockIdx.x * BN;
@@ -736,7 +746,11 @@ void gemm_conv_split_kernel(GemmArgs g) {
                 rx, static_cast<int>(static_cast<uint32_t>(boff) | past), __builtin_amdgcn_readlane(soff, e), 0));
         }
     };
+    float most = 0.0f;  // the largest magnitude this thread cut
     auto store_units = [&](uint4 *plane0, int plane_units, int row, int unit, const float (&v)[8]) {
+        // (a median with infinity: fmaxf would quieten each value first)
+#pragma unroll
+        for (int e = 0; e < 8; ++e) most = __builtin_amdgcn_fmed3f(most, __builtin_fabsf(v[e]), __builtin_inff());
         uint4 h, m, l;
         cut2(v[0], v[1], h.x, m.x, l.x);
         cut2(v[2], v[3], h.y, m.y, l.y);
@@ -763,7 +777,7 @@ void gemm_conv_split_kernel(GemmArgs g) {
 #pragma unroll
         for (int j = 0; j < NJ; ++j) acc[i][j] = low[i][j] = floatx4{0.0f, 0.0f, 0.0f, 0.0f};
 
-    const int lrow = lane & 15, lq = lane >> 4;
+    int lrow = lane & 15, lq = lane >> 4;
     load_a(0);
     load_b(0);
     store_a();
@@ -823,20 +837,87 @@ void gemm_conv_split_kernel(GemmArgs g) {
     for (int i = 0; i < MI; ++i)
 #pragma unroll
         for (int j = 0; j < NJ; ++j) acc[i][j] += low[i][j];
+    // the lane's number anew, which leaves the loop above no registers to carry
+    uint32_t none;
+    asm volatile("s_mov_b32 %0, 0" : "=s"(none));
+    lane = static_cast<int>(__builtin_amdgcn_mbcnt_hi(~0u, __builtin_amdgcn_mbcnt_lo(~0u, none)));
+    lrow = lane & 15;
+    lq = lane >> 4;
 
     // accumulator register v of lane l holds row 4*(l/16) + v and column l%16
     // of its 16 x 16 block
-    bool whole = true;
+    // whether a sum may have lost bits: at first against what operands up to
+    // kSplitOrdinary lose, one vote of the workgroup
+    float least = __builtin_inff(), finite = 0.0f;  // the least magnitude of a sum; NaN where one is not finite
 #pragma unroll
-    for (int i = 0; i < MI; ++i)
+    for (int j = 0; j < NJ; ++j) {
+        float l = __builtin_inff();
 #pragma unroll
-        for (int j = 0; j < NJ; ++j)
+        for (int i = 0; i < MI; ++i)
 #pragma unroll
             for (int v = 0; v < 4; ++v) {
-                const float m = __builtin_fabsf(acc[i][j][v]);
-                whole = whole && m < __builtin_inff() && (m == 0.0f || m >= kSplitLeast);
+                l = __builtin_fminf(l, __builtin_fabsf(acc[i][j][v]));
+                finite = __builtin_fmaf(acc[i][j][v], 0.0f, finite);
             }
-    const bool again = __any(!whole);
+        if (n0 + (wn * NJ + j) * 16 + lrow < N) least = __builtin_fminf(least, l);  // columns past N hold zeros
+    }
+    __shared__ uint32_t vote[4];
+    const bool doubt = !(finite == 0.0f) || least < kSplitLost * kSplitOrdinary || most > kSplitOrdinary;
+    if (lane == 0) vote[wave] = 0u;
+    if (__any(doubt) && lane == 0) vote[wave] = 1u;
+    __syncthreads();
+    bool again = false;
+    if (vote[0] | vote[1] | vote[2] | vote[3]) {
+        // the workgroup's largest operand, then the sums one by one
+        __shared__ float red[3][4];
+        auto wave_max = [](float v) {
+#pragma unroll
+            for (int off = 32; off > 0; off >>= 1) v = __builtin_fmaxf(v, __shfl_xor(v, off));
+            return v;
+        };
+        most = wave_max(most);
+        if (lane == 0) red[0][wave] = most;
+        const bool zero = __syncthreads_or(least == 0.0f);
+        for (int w = 0; w < 4; ++w) most = __builtin_fmaxf(most, red[0][w]);
+        const float bound = __builtin_fmaxf(kSplitLeast, kSplitLost * most);
+        float least_nz = __builtin_inff();
+#pragma unroll
+        for (int i = 0; i < MI; ++i)
+#pragma unroll
+            for (int j = 0; j < NJ; ++j)
+#pragma unroll
+                for (int v = 0; v < 4; ++v)
+                    least_nz = __builtin_fminf(least_nz, acc[i][j][v] == 0.0f ? __builtin_inff() : __builtin_fabsf(acc[i][j][v]));
+        again = __any(!(finite == 0.0f) || least_nz < bound);
+        if (zero) {
+            // the least nonzero magnitude of the tile's operands, as 2 |v| - 1 so that a zero is the largest
+            uint32_t la = ~0u, lb = ~0u;
+            for (int kt = 0; kt < nk; ++kt) {
+                load_a(kt);
+                load_b(kt);
+#pragma unroll
+                for (int e = 0; e < 8; ++e) {
+#pragma unroll
+                    for (int i = 0; i < UA; ++i) la = min(la, (__float_as_uint(ra[i][e]) << 1) - 1u);
+#pragma unroll
+                    for (int i = 0; i < UB; ++i) lb = min(lb, (__float_as_uint(rb[i][e]) << 1) - 1u);
+                }
+            }
+            auto magnitude = [](uint32_t u) { return u == ~0u ? 1.0f : __uint_as_float((u + 1u) >> 1); };
+            const float fa = -wave_max(-magnitude(la)), fb = -wave_max(-magnitude(lb));
+            if (lane == 0) {
+                red[1][wave] = fa;
+                red[2][wave] = fb;
+            }
+            __syncthreads();
+            float ma = red[1][0], mb = red[2][0];
+            for (int w = 1; w < 4; ++w) {
+                ma = __builtin_fminf(ma, red[1][w]);
+                mb = __builtin_fminf(mb, red[2][w]);
+            }
+            again = again || (__any(least == 0.0f) && (ma < 0x1p-126f || mb < 0x1p-126f || ma * mb < 0x1p-126f));
+        }
+    }
     float *pz = g.part ? g.part + static_cast<size_t>(blockIdx.z) * M * N : nullptr;
     uint32_t cnt = 0;
     auto put = [&](int m, int nn, size_t col_off, float sum) {

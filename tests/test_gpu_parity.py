@@ -766,6 +766,40 @@ def test_dense_split_operands(torch, isc, case):
     assert torch.equal(got[~special], want[~special])
 
 
+# Powers of two on the inputs and the weights: operands whose last parts, or all
+# of them, lie below bf16's range, with partners that bring the products back
+# into fp32's or leave them at its lower end
+OPERAND_SCALES = [(-118, 60), (-125, 60), (-140, 60), (60, -125), (60, -140), (-70, -70), (-140, 0), (0, -140)]
+
+
+@pytest.mark.parametrize("case", SPLIT_CASES)
+def test_dense_operand_range(torch, isc, case):
+    """The dense path keeps fp32's precision for operands over all of fp32's
+    range, subnormal ones among them: the error bound of
+    test_dense_split_operands, and half of the least subnormal a rounding."""
+    N, C, H, W, K, R, S, T, P = case
+    rng = np.random.default_rng(3 + sum(case))
+    x0 = rng.standard_normal((N, C, H, W)).astype(np.float32)
+    w0 = rng.standard_normal((K, C, R, S)).astype(np.float32)
+    scaled = [("all", ex, ew, np.ldexp(x0, ex), np.ldexp(w0, ew)) for ex, ew in OPERAND_SCALES]
+    # one channel of tiny inputs under large weights among ordinary ones (at
+    # the end, where the reduction's other products are in the sum already),
+    # and an image of its own
+    x, w = x0.copy(), w0.copy()
+    x[:, C - 1], w[:, C - 1] = np.ldexp(x0[:, C - 1], -125), np.ldexp(w0[:, C - 1], 120)
+    scaled.append(("channel", -125, 120, x, w))
+    x = x0.copy()
+    x[N - 1] = np.ldexp(x0[N - 1], -138)
+    scaled.append(("image", -138, 20, x, np.ldexp(w0, 20)))
+    for kind, ex, ew, x, w in scaled:
+        note("operand range", case, kind, ex, ew)
+        y = isc.isc_conv2d(to_dev(torch, x), to_dev(torch, w), T, P, path="dense").cpu().numpy().astype(np.float64)
+        want, mags = oracle.conv2d_f64(x, w, T, P), oracle.conv2d_f64(np.abs(x), np.abs(w), T, P)
+        bound = (2.0 + C * R * S / 4) * 2.0 ** -24 * mags + (1 + C * R * S) * 2.0 ** -150
+        bad = np.abs(y - want) > bound
+        assert not bad.any(), (case, kind, ex, ew, int(bad.sum()), y[bad][0], want[bad][0])
+
+
 def test_auto_crossover_both_sides(torch, isc):
     """AUTO with the per-shape crossover (the library's default threshold):
     on a shape whose modelled crossover lies inside (0, 1), an input below it
