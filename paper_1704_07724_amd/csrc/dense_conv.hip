@@ -616,7 +616,7 @@ void gemm_conv_ring_kernel(GemmArgs g) {
 // accumulator through all six products, three workgroups per CU, no
 // interleaving: conv2 620 us, 7.4e-7; these tiles without the interleaving: 732 us.
 //
-// Where cutting loses bits, a wavefront's tile is computed again in plain fp32.
+// Where cutting loses bits, the workgroup computes its tile again in plain fp32.
 // A value's part below bf16's least subnormal, 2^-133, is lost, at most 2^-134
 // of it, so a product loses at most 2^-133 times the largest operand, and below
 // 2^-126 its six terms are rounded at 2^-149 each.  A sum that is no less than
@@ -627,7 +627,11 @@ void gemm_conv_ring_kernel(GemmArgs g) {
 // underflowed, which only small operands do: where a tile has one, the
 // workgroup reads its operands once more for the least of them.  The largest
 // operand and the vote cost 1 % (conv2 590 -> 597 us, conv5 218 -> 220, 4e.3 at
-// batch 1 none).
+// batch 1 none).  The tile again, staged through LDS for the fp32 MFMA, costs
+// conv2 40 us where one input is infinite (32 ms when a lane went through its
+// column alone), 1070 in all where every tile meets a NaN and 1640 where every
+// product is below 2^-112 (the fp32 GEMM: 1190); the look for the least operand
+// 20 of conv5's 220 where an image is zero.
 constexpr int kSplitBN = 128, kSplitBK = 32;
 constexpr float kSplitLost = 0x1p-104f, kSplitLeast = 0x1p-112f, kSplitOrdinary = 0x1p16f;
 
@@ -888,7 +892,7 @@ void gemm_conv_split_kernel(GemmArgs g) {
 #pragma unroll
                 for (int v = 0; v < 4; ++v)
                     least_nz = __builtin_fminf(least_nz, acc[i][j][v] == 0.0f ? __builtin_inff() : __builtin_fabsf(acc[i][j][v]));
-        again = __any(!(finite == 0.0f) || least_nz < bound);
+        again = !(finite == 0.0f) || least_nz < bound;
         if (zero) {
             // the least nonzero magnitude of the tile's operands, as 2 |v| - 1 so that a zero is the largest
             uint32_t la = ~0u, lb = ~0u;
@@ -915,56 +919,77 @@ void gemm_conv_split_kernel(GemmArgs g) {
                 ma = __builtin_fminf(ma, red[1][w]);
                 mb = __builtin_fminf(mb, red[2][w]);
             }
-            again = again || (__any(least == 0.0f) && (ma < 0x1p-126f || mb < 0x1p-126f || ma * mb < 0x1p-126f));
+            again = again || ma < 0x1p-126f || mb < 0x1p-126f || ma * mb < 0x1p-126f;
+        }
+        again = __syncthreads_or(again);
+    }
+    if (again) {
+        // the workgroup's tile again in fp32: a slice's operands as they are, in
+        // LDS rows of 33 words, through v_mfma_f32_16x16x4_f32
+        constexpr int PITCH = BK + 1;
+        static_assert(sizeof(float) * PITCH * BM <= sizeof(as) && sizeof(float) * PITCH * BN <= sizeof(bs), "room for fp32");
+        float *fa = reinterpret_cast<float *>(&as[0][0]), *fb = reinterpret_cast<float *>(&bs[0][0][0]);
+        const int t = wave * 64 + lane;
+#pragma unroll
+        for (int i = 0; i < MI; ++i)
+#pragma unroll
+            for (int j = 0; j < NJ; ++j) acc[i][j] = floatx4{0.0f, 0.0f, 0.0f, 0.0f};
+        load_a(0);
+        load_b(0);
+#pragma unroll 1
+        for (int kt = 0; kt < nk; ++kt) {
+#pragma unroll
+            for (int e = 0; e < 8; ++e) {
+                const int k = (t & 3) * 8 + e;
+#pragma unroll
+                for (int i = 0; i < UA; ++i)  // (what lies past the range may be an infinity)
+                    fa[((t >> 2) + 64 * i) * PITCH + k] = kb + kt * BK + k < ke ? ra[i][e] : 0.0f;
+#pragma unroll
+                for (int i = 0; i < UB; ++i) fb[(t & 127) * PITCH + (bunit + 2 * i) * 8 + e] = rb[i][e];
+            }
+            __syncthreads();
+            if (kt + 1 < nk) {
+                load_a(kt + 1);
+                load_b(kt + 1);
+            }
+#pragma unroll
+            for (int k = 0; k < BK; k += 4) {
+                float a[MI], b[NJ];
+#pragma unroll
+                for (int i = 0; i < MI; ++i) a[i] = fa[((wm * MI + i) * 16 + lrow) * PITCH + k + lq];
+#pragma unroll
+                for (int j = 0; j < NJ; ++j) b[j] = fb[((wn * NJ + j) * 16 + lrow) * PITCH + k + lq];
+#pragma unroll
+                for (int i = 0; i < MI; ++i)
+#pragma unroll
+                    for (int j = 0; j < NJ; ++j)
+                        acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[i], b[j], acc[i][j], 0, 0, 0);
+            }
+            __syncthreads();
         }
     }
     float *pz = g.part ? g.part + static_cast<size_t>(blockIdx.z) * M * N : nullptr;
     uint32_t cnt = 0;
-    auto put = [&](int m, int nn, size_t col_off, float sum) {
-        if (g.part) {  // a partial sum of the split reduction, stored raw
-            pz[static_cast<size_t>(m) * N + nn] = sum;
-        } else {
-            const float o = epilogue_value(sum, g.epi.relu);
-            cnt += nonzero_bit(o);
-            g.c[col_off + static_cast<size_t>(m) * g.conv_hw] = o;
-        }
-    };
-    if (!again) {
 #pragma unroll
-        for (int j = 0; j < NJ; ++j) {
-            const int nn = n0 + (wn * NJ + j) * 16 + lrow;
-            if (nn >= N) continue;
-            const int img = nn / g.conv_hw;
-            const size_t col_off = static_cast<size_t>(img) * M * g.conv_hw + (nn - img * g.conv_hw);
+    for (int j = 0; j < NJ; ++j) {
+        const int nn = n0 + (wn * NJ + j) * 16 + lrow;
+        if (nn >= N) continue;
+        const int img = nn / g.conv_hw;
+        const size_t col_off = static_cast<size_t>(img) * M * g.conv_hw + (nn - img * g.conv_hw);
 #pragma unroll
-            for (int i = 0; i < MI; ++i)
+        for (int i = 0; i < MI; ++i)
 #pragma unroll
-                for (int v = 0; v < 4; ++v) {
-                    const int m = m0 + (wm * MI + i) * 16 + 4 * lq + v;
-                    if (m < M) put(m, nn, col_off, acc[i][j][v]);
+            for (int v = 0; v < 4; ++v) {
+                const int m = m0 + (wm * MI + i) * 16 + 4 * lq + v;
+                if (m >= M) continue;
+                if (g.part) {  // a partial sum of the split reduction, stored raw
+                    pz[static_cast<size_t>(m) * N + nn] = acc[i][j][v];
+                } else {
+                    const float o = epilogue_value(acc[i][j][v], g.epi.relu);
+                    cnt += nonzero_bit(o);
+                    g.c[col_off + static_cast<size_t>(m) * g.conv_hw] = o;
                 }
-        }
-    } else {
-        // this wavefront's block again, one column per lane, in fp32
-        const int nn = n0 + wn * 64 + lane;
-        if (nn < N) {
-            const int img = nn / g.conv_hw;
-            const int p = nn - img * g.conv_hw;
-            const int oy = p / g.Wo, ox = p - oy * g.Wo;
-            const size_t col_off = static_cast<size_t>(img) * M * g.conv_hw + p;
-            for (int m = m0 + wm * MB * 32; m < min(M, m0 + (wm + 1) * MB * 32); ++m) {
-                float sum = 0.0f;
-                for (int k = kb; k < ke; ++k) {
-                    const int c = k / g.RS, rs = k - c * g.RS, r = rs / g.S, sx = rs - r * g.S;
-                    const int iy = oy * g.T - g.P + r, ix = ox * g.T - g.P + sx;
-                    const bool in = static_cast<unsigned>(iy) < static_cast<unsigned>(g.H) &&
-                                    static_cast<unsigned>(ix) < static_cast<unsigned>(g.W);
-                    const float xv = in ? g.x[((static_cast<size_t>(img) * g.C + c) * g.H + iy) * g.W + ix] : 0.0f;
-                    sum = __builtin_fmaf(g.a[static_cast<size_t>(m) * g.lda + k], xv, sum);
-                }
-                put(m, nn, col_off, sum);
             }
-        }
     }
     if (!g.part && g.epi.census) {
         __shared__ uint32_t sums[4];
