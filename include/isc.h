@@ -392,11 +392,11 @@ int isc_conv2d_dw_workspace_size(const isc_conv_desc *d, size_t *bytes);
  *   dw: device K x C x R x S, fully written; must not overlap x, dy or ws.
  *   ws, ws_bytes: workspace of isc_conv2d_dw_workspace_size bytes, 256-byte
  *     aligned; contents on entry are ignored.
- *   tuning: plan overrides (rows, maps_per_lane), or NULL; the workspace
- *     size holds for every override.
- * Two launches: one wavefront per 64 or 128 output maps, a few input channels
- * and a range of output rows sums in registers over the nonzero inputs of
- * its range; the ranges' sums are then added in order.  fp32, deterministic.
+ *   tuning: plan overrides (rows and cols name a wavefront's output tile), or
+ *     NULL; the workspace size holds for every override.
+ * Two launches: one wavefront per 64 output maps, a few input channels and a
+ * range of output tiles sums in registers over the nonzero inputs of its
+ * range; the ranges' sums are then added in order.  fp32, deterministic.
  * Errors: NULL, SHAPE, LIMIT, WORKSPACE, ALIAS, ALIGN, DEVICE, HIP. */
 int isc_conv2d_dw(const isc_conv_desc *d, const float *x, const float *dy, float *dw,
                   void *ws, size_t ws_bytes, const isc_tuning *tuning, void *stream);

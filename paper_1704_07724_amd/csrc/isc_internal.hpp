@@ -251,6 +251,13 @@ int64_t sparse_fused_max_groups(const SparseShape &sh);
 // floats), then their ordered sum into dw (K x C x R x S).
 bool sparse_dw_applies(const SparseShape &sh);
 size_t sparse_dw_workspace_floats(const SparseShape &sh);
+// The tile a shape's gradient runs on: rows x cols outputs, which window
+// positions its walk visits (gen_dispatch.py's SAME), channels per wavefront,
+// and the ranges its tiles are cut into.
+struct DwPlanInfo {
+    int rows, cols, same, channels, ranges;
+};
+bool sparse_dw_plan_info(const SparseShape &sh, DwPlanInfo *out);
 hipError_t launch_sparse_dw(const SparseShape &sh, const float *x, const float *dy, float *dw, float *part,
                             hipStream_t s);
 

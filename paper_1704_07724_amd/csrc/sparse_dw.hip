@@ -62,23 +62,40 @@ void dw_reduce_kernel(DwArgs a, int R, float *__restrict__ dw) {
 // would write and read more partial sums (AlexNet conv3: 3.5 MB each).
 constexpr int64_t kDwGroups = 768;
 
-// The cheapest tile among those that take the shape: a wavefront's cycles per
+// The tiles compiled for a filter size.
+int dw_tiles(int R, const DwTile **tiles) {
+    *tiles = R == 1 ? kDwTiles1 : (R == 3 ? kDwTiles3 : kDwTiles5);
+    return static_cast<int>(R == 1 ? sizeof(kDwTiles1) : (R == 3 ? sizeof(kDwTiles3) : sizeof(kDwTiles5))) /
+           static_cast<int>(sizeof(DwTile));
+}
+
+// Whether a tile takes the shape: the positions its walk leaves out are padding.
+bool dw_tile_takes(const SparseShape &sh, const DwTile &t) {
+    if (t.same >= 1 && (sh.P != sh.R / 2 || sh.W > t.tw)) return false;
+    return t.same < 2 || sh.H <= t.th;
+}
+
+// The first tile that takes the shape and that a caller's rows and cols name;
+// else the cheapest among those that take it: a wavefront's cycles per
 // tile (reading the gradients, and per channel a fixed part and the window's
 // nonzeros at a tenth of its positions) times the tiles of all workgroups, or
 // of one round where the tiles do not fill it (small batches, where short
 // tiles give more workgroups).
 bool dw_plan(const SparseShape &sh, DwPlan *p) {
     if (sh.T != 1 || sh.R != sh.S || !(sh.R == 1 || sh.R == 3 || sh.R == 5)) return false;
-    const DwTile *tiles = sh.R == 1 ? kDwTiles1 : (sh.R == 3 ? kDwTiles3 : kDwTiles5);
-    const int n = static_cast<int>(sh.R == 1 ? sizeof(kDwTiles1) : (sh.R == 3 ? sizeof(kDwTiles3) : sizeof(kDwTiles5))) /
-                  static_cast<int>(sizeof(DwTile));
+    const DwTile *tiles;
+    const int n = dw_tiles(sh.R, &tiles);
+    int named = -1;
+    for (int i = 0; i < n && named < 0 && (sh.tu.rows > 0 || sh.tu.cols > 0); ++i)
+        if (dw_tile_takes(sh, tiles[i]) && (sh.tu.rows <= 0 || tiles[i].th == sh.tu.rows) &&
+            (sh.tu.cols <= 0 || tiles[i].tw == sh.tu.cols))
+            named = i;
     p->kgroups = (sh.K + kLanes - 1) / kLanes;
     double best = -1.0;
     int64_t ntiles = 0;
     for (int i = 0; i < n; ++i) {
         const DwTile &t = tiles[i];
-        if (t.same >= 1 && (sh.P != sh.R / 2 || sh.W > t.tw)) continue;
-        if (t.same >= 2 && sh.H > t.th) continue;
+        if (named >= 0 ? i != named : !dw_tile_takes(sh, t)) continue;
         const int64_t bands = (sh.Ho + t.th - 1) / t.th, ctiles = (sh.Wo + t.tw - 1) / t.tw;
         const int64_t cgroups = (sh.C + kDwWaves * t.ch - 1) / (kDwWaves * t.ch);
         const int64_t nt = sh.N * bands * ctiles;
@@ -114,10 +131,30 @@ bool sparse_dw_applies(const SparseShape &sh) {
     return dwk::dw_plan(sh, &p);
 }
 
-size_t sparse_dw_workspace_floats(const SparseShape &sh) {
+bool sparse_dw_plan_info(const SparseShape &sh, DwPlanInfo *out) {
     dwk::DwPlan p;
-    if (!dwk::dw_plan(sh, &p)) return 0;
-    return static_cast<size_t>(p.splits) * sh.C * sh.R * sh.S * p.kgroups * dwk::kLanes;
+    if (!dwk::dw_plan(sh, &p)) return false;
+    *out = DwPlanInfo{p.t.th, p.t.tw, p.t.same, p.t.ch, p.splits};
+    return true;
+}
+
+// The largest partial-sum buffer of any tile a caller may name, so that one
+// workspace size holds for every plan.
+size_t sparse_dw_workspace_floats(const SparseShape &sh) {
+    using namespace dwk;
+    DwPlan p;
+    if (!dw_plan(sh, &p)) return 0;
+    int most = p.splits;
+    const DwTile *tiles;
+    const int n = dw_tiles(sh.R, &tiles);
+    SparseShape v = sh;
+    v.tu = isc_tuning{};
+    for (int i = 0; i < n; ++i) {
+        v.tu.rows = tiles[i].th;
+        v.tu.cols = tiles[i].tw;
+        if (dw_plan(v, &p)) most = std::max(most, p.splits);
+    }
+    return static_cast<size_t>(most) * sh.C * sh.R * sh.S * p.kgroups * kLanes;
 }
 
 hipError_t launch_sparse_dw(const SparseShape &sh, const float *x, const float *dy, float *dw, float *part,

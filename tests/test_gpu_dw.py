@@ -50,16 +50,16 @@ def assert_close(got, want, what):
                              % (what, int(bad.sum()), bad.size, i, got.ravel()[i], want.ravel()[i]))
 
 
-# N, C, H, W, K, R, P, sparsity: every kernel variant (filter size, 64 or 128
-# maps per lane group, 16- or 28-column tiles) with ragged maps and channels
+# N, C, H, W, K, R, P, sparsity: every filter size on the library's own choice of
+# tile, with ragged maps and channels
 DW_CASES = [
-    (3, 20, 12, 12, 50, 5, 0, 0.9),     # LeNet conv2-like: 5x5, K <= 64, 16-column tiles
-    (2, 7, 27, 27, 70, 5, 2, 0.9),      # AlexNet conv2-like: 28-column tiles, ragged map group
-    (2, 13, 13, 13, 64, 3, 1, 0.95),    # 3x3, one map per lane
-    (2, 23, 13, 13, 200, 3, 1, 0.9),    # 3x3, two maps per lane, ragged
-    (1, 9, 20, 30, 130, 3, 1, 0.8),     # 28-column tiles, ragged last tile
-    (2, 37, 7, 7, 96, 1, 0, 0.9),       # 1x1, two maps per lane
-    (3, 70, 14, 14, 20, 1, 0, 0.9),     # 1x1, one map per lane, many channels
+    (3, 20, 12, 12, 50, 5, 0, 0.9),     # LeNet conv2-like: 5x5, K <= 64
+    (2, 7, 27, 27, 70, 5, 2, 0.9),      # AlexNet conv2-like: column tiles, ragged map group
+    (2, 13, 13, 13, 64, 3, 1, 0.95),    # 3x3, one full group of maps
+    (2, 23, 13, 13, 200, 3, 1, 0.9),    # 3x3, several groups of maps, ragged
+    (1, 9, 20, 30, 130, 3, 1, 0.8),     # column tiles, ragged last tile
+    (2, 37, 7, 7, 96, 1, 0, 0.9),       # 1x1, ragged map group
+    (3, 70, 14, 14, 20, 1, 0, 0.9),     # 1x1, many channels
     (1, 2, 5, 5, 3, 5, 2, 0.5),         # tiny, filter wider than the map
     (1, 1, 1, 1, 1, 1, 0, 0.0),         # one element
 ]
@@ -124,48 +124,51 @@ def test_dw_full_size_every_entry(torch, isc):
     assert_close(got, want, "dw full size")
 
 
-@pytest.mark.parametrize("R,W", [(1, 13), (3, 13), (3, 30), (5, 11), (5, 27)])
-def test_dw_every_tile_variant(torch, isc, R, W):
-    """Every compiled tile (rows per tile, maps per lane, 16- or 28-column
-    tiles), forced through the measurement overrides, against the oracle on
-    ragged maps and channels."""
-    N, C, H, K, P = 2, 9, 10, 70, R // 2
-    x, _ = workloads.make_case(N, C, H, W, K, R, R, 1, P, 0.8, seed=61 + R + W)
+# (N, C, H, W, K, R, P, rows, cols): every tile of the kernel, named, on maps it
+# fits and on ragged ones; which tile a case runs is checked on the host
+# (test_dw_plan.py)
+DW_TILES = [(3, 17, 7, 7, 66, 3, 1, 7, 7), (2, 9, 5, 6, 66, 3, 1, 7, 7), (3, 9, 13, 13, 70, 3, 1, 7, 13),
+            (2, 9, 10, 11, 66, 3, 1, 7, 13), (3, 9, 14, 14, 66, 3, 1, 7, 14), (2, 5, 9, 12, 66, 3, 1, 7, 14),
+            (9, 9, 18, 18, 66, 3, 0, 7, 14), (2, 9, 20, 33, 66, 3, 2, 7, 14), (4, 9, 30, 29, 66, 3, 1, 4, 16),
+            (3, 9, 5, 40, 66, 3, 1, 2, 16), (8, 9, 7, 7, 66, 5, 2, 7, 7), (2, 9, 4, 6, 130, 5, 2, 7, 7),
+            (9, 5, 27, 27, 130, 5, 2, 9, 9), (2, 5, 10, 14, 66, 5, 1, 9, 9), (6, 5, 13, 15, 66, 5, 0, 4, 14),
+            (3, 9, 11, 27, 66, 5, 2, 2, 14), (20, 35, 7, 7, 66, 1, 0, 7, 7), (8, 33, 14, 28, 66, 1, 0, 7, 14),
+            (1, 33, 6, 40, 66, 1, 1, 2, 14)]
+
+
+@pytest.mark.parametrize("case", DW_TILES)
+def test_dw_every_tile(torch, isc, case):
+    """Every compiled tile against the oracle on rectified Gaussian inputs, and
+    the library's own choice within the bar of the same call."""
+    N, C, H, W, K, R, P, rows, cols = case
+    x, _ = workloads.make_case(N, C, H, W, K, R, R, 1, P, 0.8, seed=61 + sum(case))
     Ho, Wo = oracle.out_size(H, R, P, 1), oracle.out_size(W, R, P, 1)
-    dy = _dy((N, K, Ho, Wo), 62 + R + W)
+    dy = _dy((N, K, Ho, Wo), 62 + sum(case))
     want = oracle.conv2d_dw_f64(x, dy, R, R, 1, P)
-    variants = [(1, 1), (2, 1), (1, 2), (2, 2)] + ([(4, 1)] if Wo <= 16 else [])
-    for kpl, th in variants:
-        note("dw variant", R, W, "kpl", kpl, "th", th)
-        got = isc.isc_conv2d_dw(to_dev(torch, x), to_dev(torch, dy), R, R, 1, P,
-                                tuning={"maps_per_lane": kpl, "rows": th}).cpu().numpy()
-        assert_close(got, want, "dw R%d W%d kpl%d th%d" % (R, W, kpl, th))
-
-
-# (N, C, H, W, K, R, P): each tile of the kernel and its ragged edges
-DW_TILES = [(3, 9, 13, 13, 70, 3, 1), (3, 9, 14, 14, 66, 3, 1), (3, 17, 7, 7, 66, 3, 1), (2, 9, 5, 6, 66, 3, 1),
-            (40, 9, 30, 29, 66, 3, 1), (90, 9, 18, 18, 66, 3, 0), (2, 9, 20, 33, 66, 3, 2), (40, 9, 7, 7, 66, 5, 2),
-            (9, 5, 27, 27, 130, 5, 2), (20, 5, 13, 15, 66, 5, 0), (40, 35, 7, 7, 66, 1, 0), (20, 33, 14, 28, 66, 1, 0),
-            (1, 33, 6, 40, 66, 1, 1)]
+    for tu in ({"rows": rows, "cols": cols}, None):
+        note("dw tile", case, tu)
+        got = isc.isc_conv2d_dw(to_dev(torch, x), to_dev(torch, dy), R, R, 1, P, tuning=tu).cpu().numpy()
+        assert_close(got, want, "dw %s %s" % (case, tu))
 
 
 @pytest.mark.parametrize("case", DW_TILES)
 def test_dw_tiles_and_special_values(torch, isc, case):
     """Sums of integers bitwise; and an infinite or NaN input or gradient
     reaches exactly the entries whose outputs it meets."""
-    N, C, H, W, K, R, P = case
+    N, C, H, W, K, R, P, rows, cols = case
+    tu = {"rows": rows, "cols": cols}
     note("dw tiles", case)
     rng = np.random.default_rng(sum(case))
     Ho, Wo = oracle.out_size(H, R, P, 1), oracle.out_size(W, R, P, 1)
     x, _ = workloads.integer_case(N, C, H, W, K, R, R, seed=sum(case), xmax=3)
     dy = rng.integers(-3, 4, size=(N, K, Ho, Wo)).astype(np.float32)
-    got = isc.isc_conv2d_dw(to_dev(torch, x), to_dev(torch, dy), R, R, 1, P).cpu().numpy()
+    got = isc.isc_conv2d_dw(to_dev(torch, x), to_dev(torch, dy), R, R, 1, P, tuning=tu).cpu().numpy()
     assert np.array_equal(got.astype(np.float64), oracle.conv2d_dw_f64(x, dy, R, R, 1, P))
     dy[dy == 0] = 1.0
     x[0, 0, H - 1, W - 1] = np.inf
     x[N - 1, C - 1, 0, 0] = np.nan
     dy[0, K - 1, Ho - 1, 0] = -np.inf
-    got = isc.isc_conv2d_dw(to_dev(torch, x), to_dev(torch, dy), R, R, 1, P).cpu().numpy()
+    got = isc.isc_conv2d_dw(to_dev(torch, x), to_dev(torch, dy), R, R, 1, P, tuning=tu).cpu().numpy()
     want = np.zeros((K, C, R, R))  # over the nonzero inputs only
     xp = np.pad(x.astype(np.float64), ((0, 0), (0, 0), (P, P), (P, P)))
     d = dy.astype(np.float64)
