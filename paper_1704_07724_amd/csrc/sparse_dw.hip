@@ -8,12 +8,45 @@ namespace isc {
 namespace dwk {
 namespace {
 
+// One range's sums for (c, r, s) = e and the 64 maps of a wavefront's lanes
+// (map k, at most K - 1), over the outputs alone and the nonzero inputs in
+// order: 64 inputs are tested at a time, each nonzero meets the maps' gradients.
+// Ends early where every wanted lane has its NaN.
+__device__ float dw_range_again(const DwArgs &a, int R, int range, int e, int k, bool wanted) {
+    const int lane = threadIdx.x & (kLanes - 1);
+    const int c = e / (R * R), rs = e - c * R * R;
+    const int dyr = rs / R - a.P, dxs = rs % R - a.P;
+    float sum = 0.0f;
+    const int t1 = min(a.ntiles, (range + 1) * a.per);
+    for (int t = range * a.per; t < t1; ++t) {
+        const int ox0 = t % a.ctiles * a.tw, oy0 = t / a.ctiles % a.bands * a.th, n = t / a.ctiles / a.bands;
+        const int rows = min(a.th, a.Ho - oy0), cols = min(a.tw, a.Wo - ox0);
+        const float *x = a.x + (static_cast<size_t>(n) * a.C + c) * a.H * a.W;
+        const float *g = a.dy + ((static_cast<size_t>(n) * a.K + k) * a.Ho + oy0) * a.Wo + ox0;
+        for (int p0 = 0; p0 < rows * cols; p0 += kLanes) {
+            const int p = p0 + lane, i = p / cols, j = p - i * cols;
+            const int y = oy0 + i + dyr, xx = ox0 + j + dxs;
+            float v = 0.0f;
+            if (i < rows && y >= 0 && y < a.H && xx >= 0 && xx < a.W) v = x[static_cast<size_t>(y) * a.W + xx];
+            for (unsigned long long nz = __ballot(v != 0.0f); nz; nz &= nz - 1) {
+                const int l = __builtin_ctzll(nz), q = p0 + l;
+                const float vl = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), l));
+                sum = __builtin_fmaf(vl, g[static_cast<size_t>(q / cols) * a.Wo + q % cols], sum);
+            }
+            if (!__any(wanted && !__builtin_isnan(sum))) return sum;
+        }
+    }
+    return sum;
+}
+
 // dw[k][e] = sum over ranges of part[range][e][k] (e = (c, r, s)): a block
 // takes 8 values of e times 64 maps; wavefront w adds the ranges w, w + 4, ...
-// in order, consecutive lanes on consecutive maps, eight loads in flight, then
-// the four sums are added in order and written with consecutive lanes on
-// consecutive e.  A sum that is not finite is taken again over the outputs
-// alone (sparse_dw.hpp), from the nonzero inputs in order.
+// in order, consecutive lanes on consecutive maps, eight loads and more in
+// flight, then the four sums are added in order and written with consecutive
+// lanes on consecutive e.  Where a sum is not finite, its ranges are added again,
+// those that are not finite themselves summed anew (AlexNet conv3 with one NaN
+// 178 us in all, 141 without, conv2 497 and 351; a thread per entry over all its
+// outputs took 5600 and 27500).
 constexpr int kRedE = 8, kRedWaves = 4;
 
 __global__ __launch_bounds__(kRedWaves * kLanes)
@@ -36,25 +69,34 @@ void dw_reduce_kernel(DwArgs a, int R, float *__restrict__ dw) {
     for (int i = 0; i < kRedE; ++i) turn[wave][i][lane] = sum[i];
     __syncthreads();
     const int col = threadIdx.x & (kRedE - 1);
-    if (e0 + col >= crs) return;
-    for (int m = threadIdx.x / kRedE; m < kLanes; m += kRedWaves * kLanes / kRedE) {
-        const int k = k0 + m;
-        if (k >= a.K) break;
-        float s = turn[0][col][m];
-        for (int w = 1; w < kRedWaves; ++w) s += turn[w][col][m];
-        if (!__builtin_isfinite(s)) {
-            const int e = e0 + col, c = e / (R * R), rs = e - c * R * R;
-            const int dyr = rs / R - a.P, dxs = rs % R - a.P;
-            s = 0.0f;
-            for (int n = 0; n < a.N && !__builtin_isnan(s); ++n)
-                for (int i = max(0, -dyr); i < min(a.Ho, a.H - dyr); ++i)
-                    for (int j = max(0, -dxs); j < min(a.Wo, a.W - dxs); ++j) {
-                        const float v = a.x[((static_cast<size_t>(n) * a.C + c) * a.H + i + dyr) * a.W + j + dxs];
-                        if (v != 0.0f)
-                            s = __builtin_fmaf(v, a.dy[((static_cast<size_t>(n) * a.K + k) * a.Ho + i) * a.Wo + j], s);
-                    }
+    float finite = 0.0f;  // NaN where a sum is not finite
+    if (e0 + col < crs) {
+        for (int m = threadIdx.x / kRedE; m < kLanes; m += kRedWaves * kLanes / kRedE) {
+            const int k = k0 + m;
+            if (k >= a.K) break;
+            float s = turn[0][col][m];
+            for (int w = 1; w < kRedWaves; ++w) s += turn[w][col][m];
+            finite = __builtin_fmaf(s, 0.0f, finite);
+            dw[static_cast<size_t>(k) * crs + e0 + col] = s;
         }
-        dw[static_cast<size_t>(k) * crs + e0 + col] = s;
+    }
+    if (!__syncthreads_or(!(finite == 0.0f))) return;
+    for (int i = wave; i <= last; i += kRedWaves) {
+        float s = turn[0][i][lane];
+        for (int w = 1; w < kRedWaves; ++w) s += turn[w][i][lane];
+        const bool odd = k0 + lane < a.K && !__builtin_isfinite(s);
+        if (!__any(odd)) continue;
+        float all = 0.0f;
+        for (int sp = 0; sp < a.splits; ++sp) {
+            float v = src[sp * stride + static_cast<size_t>(i) * a.Kp];
+            const bool again = odd && !__builtin_isfinite(v);
+            if (__any(again)) {
+                const float r = dw_range_again(a, R, sp, e0 + i, min(k0 + lane, a.K - 1), again);
+                v = again ? r : v;
+            }
+            all += v;
+        }
+        if (odd) dw[static_cast<size_t>(k0 + lane) * crs + e0 + i] = all;
     }
 }
 
@@ -174,6 +216,8 @@ hipError_t launch_sparse_dw(const SparseShape &sh, const float *x, const float *
     a.splits = p.splits;
     a.per = p.per;
     a.ntiles = p.ntiles;
+    a.th = p.t.th;
+    a.tw = p.t.tw;
     hipError_t e = sh.R == 1 ? launch_r1(a, p, s) : sh.R == 3 ? launch_r3(a, p, s) : launch_r5(a, p, s);
     if (e != hipSuccess) return e;
     const int crs = sh.C * sh.R * sh.S;

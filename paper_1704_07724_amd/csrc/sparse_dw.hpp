@@ -32,8 +32,8 @@
 // transposes (deterministic, no atomics).
 //
 // A position past the map's last row or column has gradient zero, so it adds
-// nothing to a finite sum; where an infinite or NaN input met one, the sum is
-// not finite, and the second launch sums such an entry again over the
+// nothing to a finite product; where an infinite or NaN input met one, the
+// range's sum is not finite, and the second launch takes it again over the
 // outputs alone.
 //
 // Before, one-row tiles under a static scan met 1.9 nonzeros per channel
@@ -63,6 +63,7 @@ struct DwArgs {
     int cgroups;       // groups of kDwWaves * CH channels
     int splits, per;   // tile ranges, tiles per range
     int ntiles;        // N * bands * ctiles
+    int th, tw;        // outputs of a tile
 };
 
 // Tiles (TH x TW outputs; same: which window positions the walk visits, as in

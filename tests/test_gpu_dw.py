@@ -186,3 +186,29 @@ def test_dw_tiles_and_special_values(torch, isc, case):
                     nzv = np.isfinite(v[n, :, i, j]) & (v[n, :, i, j] != 0)
                     want[k, nzv, r, s] += d[n, k, i, j] * v[n, nzv, i, j]
     assert np.array_equal(got.astype(np.float64), want, equal_nan=True)
+
+
+def test_dw_special_values_cost(torch, isc):
+    """One NaN among AlexNet conv2's inputs costs the entries it reaches their
+    range again, not all their outputs one by one: within five times the usual
+    call (80 times, a thread per entry over every output)."""
+    note("dw special values' cost")
+    x = torch.randn((128, 96, 27, 27), device="cuda").abs_()
+    x *= torch.rand_like(x) >= 0.9
+    dy = torch.randn((128, 256, 27, 27), device="cuda")
+
+    def ms(v):
+        best = float("inf")
+        for _ in range(4):
+            t0, t1 = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+            t0.record()
+            isc.isc_conv2d_dw(v, dy, 5, 5, 1, 2)
+            t1.record()
+            t1.synchronize()
+            best = min(best, t0.elapsed_time(t1))
+        return best
+
+    usual = ms(x)
+    special = x.clone()
+    special[100, 3, 5, 5] = float("nan")
+    assert ms(special) < 5 * usual
