@@ -1163,6 +1163,14 @@ void gemm_tile_shape(int64_t M, int64_t Ncols, int64_t *tm, int64_t *tn) {
     }
 }
 
+// Output maps of a workgroup of the split-operand kernel: 64 where that leaves a
+// compute unit to each workgroup (4e.3 at batch 1: 28 -> 22 us; with more
+// workgroups than units the larger tile reads and cuts half as much per product,
+// conv2 557 against 652).
+int split_rows(int64_t M, int64_t Ncols, int64_t ranges) {
+    return M > 64 && (M + 63) / 64 * ((Ncols + kSplitBN - 1) / kSplitBN) * ranges > 256 ? 128 : 64;
+}
+
 // Relative time of the implicit GEMM with C*R*S cut into `ranges` reduction
 // ranges, which chooses the split: a fixed part, the tiles of the busiest CU (workgroups
 // spread over 256 CUs) times each tile's reduction length and size, the
@@ -1217,20 +1225,22 @@ int gemm_kchunk(int64_t M, int64_t Ncols, int Kd) {
 
 }  // namespace
 
-// Expected time of the dense path's GEMM (ms), with the split the launch
-// takes: per 32-deep slice a fixed part and the busiest CU's workgroups, the
-// output (times its ranges) and the second pass.  Fitted to the dense path
-// timed on 88 shapes of more than 32 maps (9.5 % rms, 36 % at most) and 22 of up to 32 (8 %).
+// Expected time of the dense path's GEMM (ms), with the split and the tile the
+// launch takes: per 32-deep slice a fixed part and the busiest CU's workgroups,
+// the output (times its ranges) and the second pass.  Fitted per tile height to
+// the dense path timed: 32 rows on 22 shapes (8 % rms; on 27 others 12 %), 64 on
+// 81 (8 %, 32 % at most), 128 on 88 (9.5 %, 36 % at most; on 42 others 9 %).
 double dense_time_model(int64_t M, int64_t Ncols, int64_t Kd) {
     const int kc = Kd < (1ll << 31) ? gemm_kchunk(M, Ncols, static_cast<int>(Kd)) : 0;
     const int64_t ranges = kc > 0 ? (Kd + kc - 1) / kc : 1;
     const double slices = static_cast<double>(((kc > 0 ? kc : Kd) + 31) / 32);
-    const int64_t bm = M <= 32 ? 32 : (M <= 64 ? 64 : 128);
+    const int64_t bm = M <= 32 ? 32 : split_rows(M, Ncols, ranges);
     const double per_cu = std::ceil(static_cast<double>((M + bm - 1) / bm * ((Ncols + 127) / 128) * ranges) / 256.0);
     const double out = 1e-9 * static_cast<double>(M) * Ncols * ranges;
     if (M <= 32) return 0.0065 + slices * (0.00120 + 0.000706 * per_cu) + 1.70 * out + (ranges > 1 ? 0.0050 : 0.0);
-    return 0.0097 + slices * (0.00041 + 0.00117 * per_cu * (bm == 64 ? 0.6 : 1.0)) + 1.11 * out +
-           (ranges > 1 ? 0.0060 : 0.0);
+    if (bm == 64)
+        return 0.0098 + slices * (0.00013 + 0.00096 * per_cu) + 0.68 * out + (ranges > 1 ? 0.0038 : 0.0);
+    return 0.0097 + slices * (0.00041 + 0.00117 * per_cu) + 1.11 * out + (ranges > 1 ? 0.0060 : 0.0);
 }
 
 size_t conv_gemm_split_floats(int M, int64_t Ncols, int Kd) {
@@ -1269,12 +1279,7 @@ hipError_t launch_conv_gemm(const float *x, const float *w, float *y, int N, int
     const int64_t w_bytes = static_cast<int64_t>(K) * g.Kd * 4;
     const bool small = x_bytes + 16ll * P * (W + 1) < (1ll << 31) && w_bytes < (1ll << 31);
     if (K > 32 && g.RS <= 31 && g.Kd >= 16 && small) {
-        // 64 maps of a workgroup where that leaves a compute unit to each (4e.3
-        // at batch 1: 28 -> 22 us; with more workgroups than units the larger
-        // tile reads and cuts half as much per product, conv2 557 against 652)
-        const int64_t ranges = kc > 0 ? (g.Kd + kc - 1) / kc : 1;
-        const int64_t small_tiles = (K + 63ll) / 64 * ((g.N + kSplitBN - 1ll) / kSplitBN);
-        const int bm = K > 64 && small_tiles * ranges > 256 ? 128 : 64;
+        const int bm = split_rows(K, g.N, kc > 0 ? (g.Kd + kc - 1) / kc : 1);
         const bool vec = g.Kd % 4 == 0;  // no 16-byte load of the filter straddles its end
         return launch_conv_tiles(g, bm, kSplitBN, s, [&](dim3 grid) {
             if (bm == 128) {
