@@ -623,15 +623,17 @@ void gemm_conv_ring_kernel(GemmArgs g) {
 // kSplitLost times the largest operand, and no less than kSplitLeast, has lost
 // less than 2^-28 a product by either, its own rounding being 2^-24; any other
 // nonzero sum is taken again, as is one that is not finite (an infinity or NaN
-// cannot be cut).  A sum of zero is right unless operands vanished or products
-// underflowed, which only small operands do: where a tile has one, the
-// workgroup reads its operands once more for the least of them.  The largest
-// operand and the vote cost 1 % (conv2 590 -> 597 us, conv5 218 -> 220, 4e.3 at
-// batch 1 none).  The tile again, staged through LDS for the fp32 MFMA, costs
-// conv2 40 us where one input is infinite (32 ms when a lane went through its
-// column alone), 1070 in all where every tile meets a NaN and 1640 where every
-// product is below 2^-112 (the fp32 GEMM: 1190); the look for the least operand
-// 20 of conv5's 220 where an image is zero.
+// cannot be cut).  A sum of zero is right where its row or its column is zero
+// throughout; else operands may have vanished or products underflowed, which only
+// small operands do: the workgroup reads its operands once more for the least of
+// them.  The largest operands and the vote cost 1 % (conv2 600 -> 601 us, conv3
+// 198 -> 200, inception 3x3 148 -> 149), zero rows and columns 3 % where every
+// tile has some (63 images, 15 -> 488 maps of 5 x 5 at 0.95: 15.0 -> 15.6 us, 21
+// with the operands read again; conv5 with a fifth of the maps zero: 245 -> 252).
+// The tile again, staged through LDS for the fp32 MFMA, costs conv2 40 us where
+// one input is infinite (32 ms when a lane went through its column alone), 1070
+// in all where every tile meets a NaN and 1650 where every product is below
+// 2^-112 (the fp32 GEMM: 1190).
 constexpr int kSplitBN = 128, kSplitBK = 32;
 constexpr float kSplitLost = 0x1p-104f, kSplitLeast = 0x1p-112f, kSplitOrdinary = 0x1p16f;
 
@@ -664,7 +666,8 @@ void gemm_conv_split_kernel(GemmArgs g) {
     __shared__ uint4 as[3][BM * 4];
     __shared__ uint4 bs[2][3][BN * 4];
 
-    const int tid = threadIdx.x;
+    int tid = threadIdx.x;
+    asm volatile("" : "+v"(tid));  // (its own register: the census's threadIdx need not hold the lane's number too)
     int lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int wm = wave >> 1, wn = wave & 1;
@@ -675,15 +678,17 @@ void gemm_conv_split_kernel(GemmArgs g) {
     const int nk = (ke - kb + BK - 1) / BK;  // ranges are whole slices, but for the last
 
     // A: thread t reads unit t % 4 of rows t / 4 + 64 i (rows past M repeat
-    // the last one, their sums are dropped; k past the end of a row reads the
-    // next row, or zero past the last, against a zero of B)
+    // the last one, their sums are dropped; k past the end of a row in its last
+    // slice reads the next row, or zero past the last, against a zero of B)
     const __amdgpu_buffer_rsrc_t rw = __builtin_amdgcn_make_buffer_rsrc(
         const_cast<float *>(g.a), 0, static_cast<int>(static_cast<int64_t>(M) * g.lda * 4), kGemmBufferFormat);
     const int arow = tid >> 2, aunit = tid & 3;
     int aoff[UA];
 #pragma unroll
-    for (int i = 0; i < UA; ++i)
+    for (int i = 0; i < UA; ++i) {
         aoff[i] = (min(m0 + arow + 64 * i, M - 1) * static_cast<int>(g.lda) + kb + aunit * 8) * 4;
+        asm volatile("" : "+v"(aoff[i]));  // (one register: taken apart, its terms were two)
+    }
     // B: thread t reads column t % 128, units t / 128 and t / 128 + 2
     // (wave-uniform), through a buffer that starts the padding before x
     const int bcol = tid & 127;
@@ -716,7 +721,7 @@ void gemm_conv_split_kernel(GemmArgs g) {
     auto load_a = [&](int kt) {
 #pragma unroll
         for (int i = 0; i < UA; ++i) {
-            const int off = aoff[i] + kt * (BK * 4);
+            const int off = aoff[i] + (kt < nk ? kt * (BK * 4) : static_cast<int>(0x80000000u));  // past the range: zero
             if constexpr (A_VEC) {
 #pragma unroll
                 for (int h = 0; h < 2; ++h) {
@@ -733,7 +738,7 @@ void gemm_conv_split_kernel(GemmArgs g) {
     };
     // lane e < 16 decodes k number e of the wavefront's two units of a slice:
     // its byte offset from a column's corner, and the shift that brings its
-    // tap's bit of `outside` to the top (bit 31, set, for k past C*R*S)
+    // tap's bit of `outside` to the top (bit 31, set, for k past the range)
     auto load_b = [&](int kt) {
         const int k = kb + kt * BK + (bunit + ((lane >> 3) & 1) * 2) * 8 + (lane & 7);
         const int kc = min(k, Kd - 1);
@@ -742,7 +747,7 @@ void gemm_conv_split_kernel(GemmArgs g) {
         const int rs = kc - c * g.RS;
         const int r = static_cast<int>(__umulhi(static_cast<uint32_t>(rs), g.mS)) + (rs & oneS);
         const int soff = ((c * g.H + r) * g.W + rs - r * g.S) * 4;
-        const int sh = k < Kd ? 31 - rs : 0;
+        const int sh = k < ke ? 31 - rs : 0;
 #pragma unroll
         for (int e = 0; e < UB * 8; ++e) {
             const uint32_t past = (outside << __builtin_amdgcn_readlane(sh, e)) & 0x80000000u;
@@ -750,8 +755,8 @@ void gemm_conv_split_kernel(GemmArgs g) {
                 rx, static_cast<int>(static_cast<uint32_t>(boff) | past), __builtin_amdgcn_readlane(soff, e), 0));
         }
     };
-    float most = 0.0f;  // the largest magnitude this thread cut
-    auto store_units = [&](uint4 *plane0, int plane_units, int row, int unit, const float (&v)[8]) {
+    float most_a[UA] = {}, most_b = 0.0f;  // the largest magnitudes this thread cut, of its rows and of its column
+    auto store_units = [&](uint4 *plane0, int plane_units, int row, int unit, const float (&v)[8], float &most) {
         // (a median with infinity: fmaxf would quieten each value first)
 #pragma unroll
         for (int e = 0; e < 8; ++e) most = __builtin_amdgcn_fmed3f(most, __builtin_fabsf(v[e]), __builtin_inff());
@@ -767,11 +772,11 @@ void gemm_conv_split_kernel(GemmArgs g) {
     };
     auto store_a = [&]() {
 #pragma unroll
-        for (int i = 0; i < UA; ++i) store_units(&as[0][0], BM * 4, arow + 64 * i, aunit, ra[i]);
+        for (int i = 0; i < UA; ++i) store_units(&as[0][0], BM * 4, arow + 64 * i, aunit, ra[i], most_a[i]);
     };
     auto store_b = [&](int buf) {
 #pragma unroll
-        for (int i = 0; i < UB; ++i) store_units(&bs[buf][0][0], BN * 4, bcol, bunit + 2 * i, rb[i]);
+        for (int i = 0; i < UB; ++i) store_units(&bs[buf][0][0], BN * 4, bcol, bunit + 2 * i, rb[i], most_b);
     };
 
     constexpr int MI = 2 * MB, NJ = 4;  // 16 x 16 blocks of a wavefront
@@ -786,7 +791,7 @@ void gemm_conv_split_kernel(GemmArgs g) {
     load_b(0);
     store_a();
     store_b(0);
-    load_a(1);  // past the last slice: in bounds or zero, never used
+    load_a(1);  // past the last slice: zero, never used
     load_b(1);
     for (int kt = 0; kt < nk; ++kt) {
         __syncthreads();  // the slice is in LDS
@@ -841,10 +846,11 @@ void gemm_conv_split_kernel(GemmArgs g) {
     for (int i = 0; i < MI; ++i)
 #pragma unroll
         for (int j = 0; j < NJ; ++j) acc[i][j] += low[i][j];
-    // the lane's number anew, which leaves the loop above no registers to carry
-    uint32_t none;
+    // the lane's number, and the first slice's, anew: nothing of them is carried
+    // through the loop above
+    int none;
     asm volatile("s_mov_b32 %0, 0" : "=s"(none));
-    lane = static_cast<int>(__builtin_amdgcn_mbcnt_hi(~0u, __builtin_amdgcn_mbcnt_lo(~0u, none)));
+    lane = static_cast<int>(__builtin_amdgcn_mbcnt_hi(~0u, __builtin_amdgcn_mbcnt_lo(~0u, static_cast<uint32_t>(none))));
     lrow = lane & 15;
     lq = lane >> 4;
 
@@ -852,51 +858,84 @@ void gemm_conv_split_kernel(GemmArgs g) {
     // of its 16 x 16 block
     // whether a sum may have lost bits: at first against what operands up to
     // kSplitOrdinary lose, one vote of the workgroup
-    float least = __builtin_inff(), finite = 0.0f;  // the least magnitude of a sum; NaN where one is not finite
+    constexpr uint32_t kOdd = 1, kSmall = 2, kLarge = 4;
+    __shared__ uint32_t vote[4];
+    __shared__ float column[2][BN];  // the largest operand of each column, by the two threads that cut it
+    column[bunit][(wave & 1) * 64 + lane] = most_b;
+    float least[NJ], finite = 0.0f, lowest = __builtin_inff();  // magnitudes of sums; NaN where one is not finite
 #pragma unroll
     for (int j = 0; j < NJ; ++j) {
-        float l = __builtin_inff();
+        least[j] = __builtin_inff();
 #pragma unroll
         for (int i = 0; i < MI; ++i)
 #pragma unroll
             for (int v = 0; v < 4; ++v) {
-                l = __builtin_fminf(l, __builtin_fabsf(acc[i][j][v]));
+                least[j] = __builtin_fminf(least[j], __builtin_fabsf(acc[i][j][v]));
                 finite = __builtin_fmaf(acc[i][j][v], 0.0f, finite);
             }
-        if (n0 + (wn * NJ + j) * 16 + lrow < N) least = __builtin_fminf(least, l);  // columns past N hold zeros
+        if (n0 + (wn * NJ + j) * 16 + lrow >= N) least[j] = __builtin_inff();  // no column
+        lowest = __builtin_fminf(lowest, least[j]);
     }
-    __shared__ uint32_t vote[4];
-    const bool doubt = !(finite == 0.0f) || least < kSplitLost * kSplitOrdinary || most > kSplitOrdinary;
-    if (lane == 0) vote[wave] = 0u;
-    if (__any(doubt) && lane == 0) vote[wave] = 1u;
+    float most = __builtin_fmaxf(__builtin_fmaxf(most_a[0], most_a[UA - 1]), most_b);
+    const uint32_t doubts = (__any(!(finite == 0.0f)) ? kOdd : 0u) | (__any(lowest < kSplitLost * kSplitOrdinary) ? kSmall : 0u) |
+                            (__any(most > kSplitOrdinary) ? kLarge : 0u);
+    if (lane == 0) vote[wave] = doubts;
     __syncthreads();
+    const uint32_t doubt = vote[0] | vote[1] | vote[2] | vote[3];
+    __shared__ float red[3][4], row[BM];
+    auto wave_max = [](float v) {
+#pragma unroll
+        for (int off = 32; off > 0; off >>= 1) v = __builtin_fmaxf(v, __shfl_xor(v, off));
+        return v;
+    };
+    float bound = kSplitLost * kSplitOrdinary;
     bool again = false;
-    if (vote[0] | vote[1] | vote[2] | vote[3]) {
-        // the workgroup's largest operand, then the sums one by one
-        __shared__ float red[3][4];
-        auto wave_max = [](float v) {
+    if (doubt) {
+        if (doubt & kLarge) {  // against the workgroup's largest operand
+            most = wave_max(most);
+            if (lane == 0) red[0][wave] = most;
+            __syncthreads();
+            for (int w = 0; w < 4; ++w) most = __builtin_fmaxf(most, red[0][w]);
+            bound = __builtin_fmaxf(kSplitLeast, kSplitLost * most);
+        }
+        // sums of zero are right where their column is zero
+        lowest = __builtin_inff();
 #pragma unroll
-            for (int off = 32; off > 0; off >>= 1) v = __builtin_fmaxf(v, __shfl_xor(v, off));
-            return v;
-        };
-        most = wave_max(most);
-        if (lane == 0) red[0][wave] = most;
-        const bool zero = __syncthreads_or(least == 0.0f);
-        for (int w = 0; w < 4; ++w) most = __builtin_fmaxf(most, red[0][w]);
-        const float bound = __builtin_fmaxf(kSplitLeast, kSplitLost * most);
-        float least_nz = __builtin_inff();
+        for (int j = 0; j < NJ; ++j) {
+            const int c = (wn * NJ + j) * 16 + lrow;
+            if (__builtin_fmaxf(column[0][c], column[1][c]) > 0.0f) lowest = __builtin_fminf(lowest, least[j]);
+        }
 #pragma unroll
-        for (int i = 0; i < MI; ++i)
+        for (int i = 0; i < UA; ++i) {  // four lanes cut a row
+            float r = __builtin_fmaxf(most_a[i], __shfl_xor(most_a[i], 1));
+            r = __builtin_fmaxf(r, __shfl_xor(r, 2));
+            row[wave * 16 + (lane >> 2) + 64 * i] = r;
+        }
+        again = __syncthreads_or(!(finite == 0.0f) || lowest < bound);
+    }
+    if (again) {
+        // and where their row is
+        float least_nz = __builtin_inff(), zero = __builtin_inff();
 #pragma unroll
-            for (int j = 0; j < NJ; ++j)
+        for (int j = 0; j < NJ; ++j) {
+            const int c = (wn * NJ + j) * 16 + lrow;
+            const float column_most = __builtin_fmaxf(column[0][c], column[1][c]);
 #pragma unroll
-                for (int v = 0; v < 4; ++v)
-                    least_nz = __builtin_fminf(least_nz, acc[i][j][v] == 0.0f ? __builtin_inff() : __builtin_fabsf(acc[i][j][v]));
-        again = !(finite == 0.0f) || least_nz < bound;
-        if (zero) {
+            for (int i = 0; i < MI; ++i)
+#pragma unroll
+                for (int v = 0; v < 4; ++v) {
+                    const float m = __builtin_fabsf(acc[i][j][v]);
+                    least_nz = __builtin_fminf(least_nz, m == 0.0f ? __builtin_inff() : m);
+                    // zero where a sum is and neither its row nor its column
+                    zero = __builtin_fminf(zero, __builtin_fminf(row[(wm * MI + i) * 16 + 4 * lq + v], column_most) > 0.0f ? m : 1.0f);
+                }
+        }
+        bool lost = !(finite == 0.0f) || least_nz < bound;
+        if (__syncthreads_or(zero == 0.0f)) {
             // the least nonzero magnitude of the tile's operands, as 2 |v| - 1 so that a zero is the largest
             uint32_t la = ~0u, lb = ~0u;
-            for (int kt = 0; kt < nk; ++kt) {
+#pragma unroll 2
+            for (int kt = none; kt < nk; ++kt) {
                 load_a(kt);
                 load_b(kt);
 #pragma unroll
@@ -919,9 +958,9 @@ void gemm_conv_split_kernel(GemmArgs g) {
                 ma = __builtin_fminf(ma, red[1][w]);
                 mb = __builtin_fminf(mb, red[2][w]);
             }
-            again = again || ma < 0x1p-126f || mb < 0x1p-126f || ma * mb < 0x1p-126f;
+            lost = lost || ma < 0x1p-126f || mb < 0x1p-126f || ma * mb < 0x1p-126f;
         }
-        again = __syncthreads_or(again);
+        again = __syncthreads_or(lost);
     }
     if (again) {
         // the workgroup's tile again in fp32: a slice's operands as they are, in
@@ -934,8 +973,8 @@ void gemm_conv_split_kernel(GemmArgs g) {
         for (int i = 0; i < MI; ++i)
 #pragma unroll
             for (int j = 0; j < NJ; ++j) acc[i][j] = floatx4{0.0f, 0.0f, 0.0f, 0.0f};
-        load_a(0);
-        load_b(0);
+        load_a(none);
+        load_b(none);
 #pragma unroll 1
         for (int kt = 0; kt < nk; ++kt) {
 #pragma unroll

@@ -793,6 +793,14 @@ def test_dense_operand_range(torch, isc, case):
     x = x0.copy()
     x[N - 1] = np.ldexp(x0[N - 1], -138)
     scaled.append(("image", -138, 20, x, np.ldexp(w0, 20)))
+    # sums of zero of every kind: columns without a nonzero input, maps without a
+    # weight, and columns whose only inputs are subnormal
+    x, w = np.zeros_like(x0), w0.copy()
+    keep = rng.random(x0.shape) < 0.02
+    x[keep] = np.ldexp(x0, -140)[keep]
+    x[0, :, : H // 2] = x0[0, :, : H // 2] * (rng.random(x0[0, :, : H // 2].shape) < 0.05)
+    w[::5] = 0.0
+    scaled.append(("zeros", -140, 0, x, w))
     for kind, ex, ew, x, w in scaled:
         note("operand range", case, kind, ex, ew)
         y = isc.isc_conv2d(to_dev(torch, x), to_dev(torch, w), T, P, path="dense").cpu().numpy().astype(np.float64)
