@@ -182,7 +182,10 @@ int isc_conv2d_noalloc(const isc_conv_desc *d, const float *x, const float *w, f
 /* The per-shape crossover AUTO uses under ISC_THRESHOLD_CROSSOVER: the
  * smallest input sparsity (fraction of zero inputs, the definition under
  * Tab. 2) at which it takes the sparse path, from models of both paths'
- * times on this GPU for the plans this descriptor gets; 2.0 when the sparse
+ * times on this GPU for the plans this descriptor gets; 0.0 when every input
+ * goes there (the sparse path is never slower, or the call is so short that
+ * keeping the choice open costs about what an input without zeros would lose:
+ * LeNet conv2, small layers of one image); 2.0 when the sparse
  * path is never expected to win, or only past a sparsity of 0.95, where
  * keeping the choice open (the count and the gated launch of the path not
  * taken, on every call) costs more than it could save (for example 1x1

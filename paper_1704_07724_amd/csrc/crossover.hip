@@ -34,11 +34,13 @@ struct Fit {
 constexpr Fit kResidentFit{0.0105, 1.77078063, 1.41836285};
 
 constexpr double kShortCall = 0.04;       // ms
+constexpr double kShortSlower = 1.2;
 constexpr double kChoiceLaunches = 0.009; // ms: the count's launch and the gated ones
 constexpr double kCountPerInput = 1e-9;  // ms: 4 bytes at 4 TB/s
 
-// The largest count whose density does not exceed dstar.
-long long limit_for(double dstar, int64_t total, double dense) {
+// The largest count whose density does not exceed dstar, where the dense path takes
+// `dense` ms and the sparse path `no_zeros` on an input without any.
+long long limit_for(double dstar, int64_t total, double dense, double no_zeros) {
     // a crossover past 0.95 sparsity counts as none: keeping the choice open
     // (the count, and the gated launch of the path not taken) costs more on
     // every call than the sparse path could save on the rare inputs past it
@@ -46,11 +48,14 @@ long long limit_for(double dstar, int64_t total, double dense) {
     // measured none up to 0.99; AUTO 18 % over the dense path at 0.9 while
     // it kept the choice)
     if (dstar < 0.05) return -1;
-    // and on a short call one below 0.6 counts as every input being sparse:
-    // the dense path's gated launches are a fifth of such a call (inception
-    // 4e.3 at batch 1: 16 us without them, 20 with), a rectified input that
-    // dense is rare
-    if (dstar >= 1.0 || (dstar > 0.4 && dense < kShortCall)) return static_cast<long long>(total);
+    // and on a short call, where the gated launches are a fifth, every input
+    // counts as sparse if one without zeros takes the sparse path at most
+    // kShortSlower times what the open choice costs it (inception 4e.3 at batch
+    // 1: 16 us against 19 at 0.9, 25 against 29 at 0.6, 34 against 28 at 0.3 and 42
+    // against 28 without zeros; 64 -> 192 maps of 56 x 56, 3x3, one image, left
+    // open: 20 against 23, 32 against 31, 44 and 56 against 31)
+    if (dstar >= 1.0 || (dense < kShortCall && no_zeros < kShortSlower * (dense + kChoiceLaunches)))
+        return static_cast<long long>(total);
     // the kernels' models are those of rectified inputs: past a density of
     // 0.69 the two paths are within a tenth of each other where they cross
     return static_cast<long long>(std::floor(std::min(dstar, 0.69) * static_cast<double>(total)));
@@ -84,7 +89,8 @@ long long crossover_nnz_limit(const SparseShape &sh) {
         // much too slow where the largest layer crosses (AlexNet conv2 at 0.6:
         // 720 us measured, 790 modelled)
         const double meet = 1.1 * dense;
-        return limit_for(std::min((meet - rt.base[0]) / rt.slope[0], (meet - rt.base[1]) / rt.slope[1]), total, dense);
+        return limit_for(std::min((meet - rt.base[0]) / rt.slope[0], (meet - rt.base[1]) / rt.slope[1]), total, dense,
+                         std::max(rt.base[0] + rt.slope[0], rt.base[1] + rt.slope[1]));
     }
     const double wc = static_cast<double>(p.workgroups) * p.waves * sh.C / std::max(1, p.phases);
     const int wrows = (p.rows - 1) * sh.T + sh.R, wcols = (p.cols - 1) * sh.T + sh.S;
@@ -98,7 +104,7 @@ long long crossover_nnz_limit(const SparseShape &sh) {
     const double per_density = f.c_nz * wc * pin * (10.0 + taps * std::max(1, p.maps_per_lane)) * 1e-9;
     if (!(per_density > 0.0)) return dense >= fixed ? static_cast<long long>(total) : -1;
     const double dstar = (dense - fixed) / per_density;  // density at which the two meet
-    return limit_for(dstar, total, dense);
+    return limit_for(dstar, total, dense, fixed + per_density);
 }
 
 }  // namespace isc

@@ -351,3 +351,17 @@ def test_crossover_model_orders_shapes():
         assert 0.0 <= s <= 1.0
     # a shape only the list kernels take keeps the paper's 0.9
     assert abs(isc.isc_crossover_sparsity(d(2, 4, 21, 21, 64, 5, 5, 2, 1)) - 0.9) < 1e-3
+
+
+def test_short_calls_keep_the_choice_where_it_matters():
+    """Every input counts as sparse (crossover 0) only where one without zeros
+    loses little: not 64 -> 192 maps of 56 x 56 on one image (56 us sparse, 24
+    dense), 296 -> 58 of 10 x 10 on 31 (76 and 30) or 34 -> 235 of 17 x 17 on 4
+    (58 and 24), whose crossovers lie where their paths were measured to meet;
+    LeNet conv2 and small layers of one image do."""
+    d = isc.make_desc
+    for shape, lo, hi in (((1, 64, 56, 56, 192, 3, 3, 1, 1), 0.5, 0.85), ((31, 296, 10, 10, 58, 3, 3, 1, 1), 0.5, 0.85),
+                          ((4, 34, 17, 17, 235, 5, 5, 1, 2), 0.5, 0.85)):
+        assert lo < isc.isc_crossover_sparsity(d(*shape)) < hi, shape
+    for shape in ((8, 20, 12, 12, 50, 5, 5, 1, 0), (1, 56, 9, 9, 105, 3, 3, 1, 1), (14, 89, 5, 5, 106, 3, 3, 1, 1)):
+        assert isc.isc_crossover_sparsity(d(*shape)) == 0.0, shape
