@@ -71,9 +71,9 @@ constexpr double kPlanDensity = 0.1;  // the paper's layers are 0.9 to 0.95 spar
 // to a caller's phases (1, 2 or 4; 1 where only the tile is named).
 bool choose(const SparseShape &sh, TileChoice *tc, int *phases) {
     if (!(sh.T == 1 || sh.T == 2) || sh.R != sh.S || !(sh.R == 1 || sh.R == 3 || sh.R == 5)) return false;
-    // the kernel addresses a plane and a channel's weights by 31-bit byte offsets
+    // the kernel addresses a channel's weights by 31-bit byte offsets
     const int64_t kp = (sh.K + kLanes - 1) / kLanes * static_cast<int64_t>(kLanes);
-    if (static_cast<int64_t>(sh.H) * sh.W * 4 >= (1ll << 31) || kp * sh.R * sh.S * 4 >= (1ll << 31)) return false;
+    if (kp * sh.R * sh.S * 4 >= (1ll << 31)) return false;
     const TileChoice *tiles;
     const int n = tiles_for(sh.R, sh.T, &tiles);
     for (int pass = 0; pass < 2; ++pass) {

@@ -43,7 +43,10 @@ namespace isc {
 namespace fring {
 
 using tile::kLanes;
-constexpr size_t kLdsMax = 160 * 1024;
+// Range of the buffers a window is read through: past the offsets of every row
+// it spans (at most 13 of 65535 columns); a position outside the map has
+// tile::kPastPlane for an offset and reads zero.
+constexpr int kWindowBytes = 1 << 30;
 
 struct FringArgs {
     const float *x;   // N x C x H x W
@@ -141,13 +144,15 @@ void sparse_conv_fring_kernel(FringArgs a) {
     const int kbase = kg * KW;
     const int C = a.C, H = a.H, W = a.W, P = a.P;
     const size_t HW = static_cast<size_t>(H) * W;
-    const float *x_n = a.x + static_cast<size_t>(n) * C * HW;
+    const int y0 = max(0, oy0 * ST - P);  // the window's first row in the map
+    const float *x_n = a.x + static_cast<size_t>(n) * C * HW + static_cast<size_t>(y0) * W;
     const int ncw = has && phase < C ? (C - 1 - phase) / a.phases + 1 : 0;
     float *slot = slots[wave];
 
-    // byte offset in the channel's plane of position q * CH + lane of the
-    // walk; lanes without one (padding, and lane CH of a ballot, whose bit is
-    // the walk's sentinel) an offset past the plane, which reads as zero
+    // byte offset from row y0 (a plane may exceed 2^31 bytes) of position
+    // q * CH + lane of the walk; lanes without one (padding, and lane CH of a
+    // ballot, whose bit is the walk's sentinel) an offset past the buffer, which
+    // reads as zero
     int xoff[EPL];
 #pragma unroll
     for (int q = 0; q < EPL; ++q) {
@@ -155,7 +160,7 @@ void sparse_conv_fring_kernel(FringArgs a) {
         const int wy = e / Walk::kCols;
         const int y = oy0 * ST - P + wy * Walk::kStep, xx = ox0 * ST - P + (e - wy * Walk::kCols) * Walk::kStep;
         const bool in = lane < CH && e < NQ && y >= 0 && y < H && xx >= 0 && xx < W;
-        xoff[q] = in ? (y * W + xx) * static_cast<int>(sizeof(float)) : tile::kPastPlane;
+        xoff[q] = in ? ((y - y0) * W + xx) * static_cast<int>(sizeof(float)) : tile::kPastPlane;
     }
     // byte offset in a channel's weights of this lane's 16 bytes of block d
     // (blocks past the last tap repeat it)
@@ -166,7 +171,6 @@ void sparse_conv_fring_kernel(FringArgs a) {
         const int tap = min(f / KW, RS2 - 1);
         woff[d] = (tap * a.Kp + min(kbase + f % KW, a.Kp - 4)) * static_cast<int>(sizeof(float));
     }
-    const int plane_bytes = H * W * static_cast<int>(sizeof(float));
     const int chan_bytes = RS2 * a.Kp * static_cast<int>(sizeof(float));
 
     // channel i of this wavefront into its slot
@@ -177,7 +181,7 @@ void sparse_conv_fring_kernel(FringArgs a) {
 #pragma unroll
         for (int d = 0; d < NDW; ++d) tile::buffer_lds16(wres, slot + d * 256, woff[d]);
         const __amdgpu_buffer_rsrc_t xres = __builtin_amdgcn_make_buffer_rsrc(
-            const_cast<float *>(x_n) + static_cast<size_t>(c) * HW, 0, plane_bytes, tile::kBufferFormat);
+            const_cast<float *>(x_n) + static_cast<size_t>(c) * HW, 0, kWindowBytes, tile::kBufferFormat);
 #pragma unroll
         for (int q = 0; q < EPL; ++q) tile::buffer_lds4(xres, slot + NDW * 256 + q * kLanes, xoff[q]);
     };

@@ -365,3 +365,12 @@ def test_short_calls_keep_the_choice_where_it_matters():
         assert lo < isc.isc_crossover_sparsity(d(*shape)) < hi, shape
     for shape in ((8, 20, 12, 12, 50, 5, 5, 1, 0), (1, 56, 9, 9, 105, 3, 3, 1, 1), (14, 89, 5, 5, 106, 3, 3, 1, 1)):
         assert isc.isc_crossover_sparsity(d(*shape)) == 0.0, shape
+
+
+def test_planes_past_two_gigabytes_stay_with_the_ring():
+    """A plane of 2^31 bytes and more is addressed window by window."""
+    d = isc.make_desc
+    for shape in ((1, 1, 32768, 16384, 1, 3, 3, 1, 1), (1, 1, 40000, 50000, 1, 5, 5, 1, 2), (1, 3, 32768, 20000, 1, 1, 1, 1, 0)):
+        assert isc.isc_sparse_kernel(d(*shape)) == "fused_ring", shape
+    # no lists in the workspace: the control block, the counts and the filter
+    assert isc.isc_workspace_size(d(1, 1, 32768, 16384, 1, 3, 3, 1, 1), "sparse") < 1 << 14

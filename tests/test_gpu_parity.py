@@ -650,6 +650,31 @@ def test_ring_phases(torch, isc, R, kpl, th, tw, phases):
         assert isc.isc_census_read(yc) == (z.size, int(np.count_nonzero(z)))
 
 
+def test_ring_plane_past_two_gigabytes(torch, isc):
+    """One map of 32768 x 16640 (2.2 GB): the nonzeros of its corners, of the rows
+    around the byte 2^31 and of a tile's edge give their 3x3 neighbourhoods and
+    nothing else."""
+    H, W = 32768, 16640
+    note("ring large plane", H, W)
+    x = torch.zeros((1, 1, H, W), device="cuda")
+    w = torch.arange(1.0, 10.0, device="cuda").view(1, 1, 3, 3)
+    mid = (1 << 29) // W
+    spots = [(0, 0), (0, W - 1), (6, 13), (7, 14), (mid, 5), (mid, W - 2), (mid + 1, 100), (H - 1, 0), (H - 1, W - 1)]
+    for i, (r, c) in enumerate(spots):
+        x[0, 0, r, c] = float(i + 1)
+    y = isc.isc_sparse_conv_fused(x, isc.isc_repack_filter(w), 1, 1)[0, 0]
+    want = {}
+    for i, (r, c) in enumerate(spots):
+        for dr in range(3):
+            for dc in range(3):
+                o = (r + 1 - dr, c + 1 - dc)
+                if 0 <= o[0] < H and 0 <= o[1] < W:
+                    want[o] = want.get(o, 0.0) + (i + 1) * float(dr * 3 + dc + 1)
+    for o, v in want.items():
+        assert float(y[o]) == v, o
+    assert int(torch.count_nonzero(y)) == len(want)
+
+
 # (C, H, K, R, P, rows, cols): tall tiles of the register-weight kernel, their
 # ragged last bands, maps narrower than the tile and padding other than R/2
 REG_TALL = [(9, 13, 70, 3, 1, 7, 13), (9, 11, 70, 3, 1, 5, 13), (17, 14, 65, 3, 1, 7, 14), (3, 12, 67, 3, 1, 7, 14),
