@@ -555,9 +555,9 @@ def kernel_symbol(isc, desc, R: int) -> str:
     tile (the on-the-fly kernels; the plan's kernel name otherwise)."""
     p = isc.isc_sparse_plan(desc)
     k = p["kernel"]
-    if k == "fused_ring" or (k == "fused" and p["waves"] == 4):
-        return "sparse_conv_fring_kernel<%d, %d, %d, %d, %d, 1>" % (R, p["maps_per_lane"], p["rows"], p["cols"],
-                                                                p["waves"])
+    if k == "fused_ring":
+        return "sparse_conv_fring_kernel<%d, %d, %d, %d, %d, %d>" % (R, p["maps_per_lane"], p["rows"], p["cols"],
+                                                                     p["waves"], desc.stride)
     if k == "fused_reg":
         return "sparse_conv_fused_reg_kernel<%d, %d, %d, ...>" % (R, p["rows"], p["cols"])
     if k == "fused":

@@ -235,9 +235,8 @@ int isc_census_size(const isc_conv_desc *d, size_t *bytes);
  *     counting x.  A census that does not cover exactly N*C*H*W entries
  *     (never written, or written for another shape) leaves the count
  *     unknown and AUTO runs the dense path: y is right either way.  Shapes
- *     whose sparse path runs over compacted lists (isc_sparse_kernel not
- *     FUSED, FUSED_REG or FUSED_RING) count x while listing it and ignore
- *     x_census.
+ *     of the kernels over compacted lists (isc_sparse_kernel not FUSED,
+ *     FUSED_REG or FUSED_RING) count x themselves and ignore x_census.
  *   wt: the repacked filter of isc_repack_filter for K, C, R, S of d
  *     (16-byte aligned), or NULL to repack w into the workspace on every
  *     call.  Used by the on-the-fly sparse kernels.
@@ -322,7 +321,8 @@ int isc_sparse_conv(const isc_conv_desc *d, const int32_t *row_ptr, const isc_nz
  * workgroup per group of 64 output maps: taken there when K > 64, when the
  * filter does not fit in LDS, or when every wavefront of the resident plan
  * would own its channels alone), and streamed through LDS otherwise
- * (ISC_KERNEL_FUSED_RING).  The kernels isc_conv2d's sparse path runs when
+ * (ISC_KERNEL_FUSED_RING; also for ISC_KERNEL_FUSED shapes at stride 1 wider
+ * than 16 columns, unless tuning names the kernel or a part of its plan).  The kernels isc_conv2d's sparse path runs when
  * isc_sparse_kernel reports either (isc_conv2d repacks the filter itself, in
  * the launch that counts the nonzeros); no sparse/dense decision here.
  *   x: device input as for isc_conv2d.
@@ -337,17 +337,20 @@ int isc_sparse_conv(const isc_conv_desc *d, const int32_t *row_ptr, const isc_nz
 int isc_sparse_conv_fused(const isc_conv_desc *d, const float *x, const float *wt, float *y,
                           const isc_tuning *tuning, void *stream);
 
-/* Which kernel isc_conv2d's sparse path runs for this descriptor, reported in
- * *kernel: ISC_KERNEL_FUSED, ISC_KERNEL_FUSED_REG or ISC_KERNEL_FUSED_RING
- * (compaction on the fly, isc_sparse_conv_fused; filter resident in LDS,
- * each wavefront's own channels' weights streamed to registers -- for plans
- * whose wavefronts share no input channel, at stride 1 and at most 16
- * output columns, any K -- or filter streamed through LDS), else
- * the kernel over compacted lists that isc_sparse_conv also runs:
+/* Which kernel's shape this descriptor is on isc_conv2d's sparse path, reported
+ * in *kernel: ISC_KERNEL_FUSED, ISC_KERNEL_FUSED_REG or ISC_KERNEL_FUSED_RING
+ * (compaction on the fly, the shapes isc_sparse_conv_fused takes; filter
+ * resident in LDS, each wavefront's own channels' weights streamed to
+ * registers -- for plans whose wavefronts share no input channel, at stride 1
+ * and at most 16 output columns, any K -- or filter streamed through LDS), else
+ * the kernel over compacted lists that isc_sparse_conv runs:
  * ISC_KERNEL_RESIDENT (filter resident in LDS), ISC_KERNEL_RING (filter
  * streamed through LDS) or ISC_KERNEL_GENERIC (any filter and stride);
- * ISC_KERNEL_NONE if no sparse kernel fits (AUTO then runs dense).
- * Host-only.  Errors: NULL, SHAPE, LIMIT. */
+ * ISC_KERNEL_NONE if no sparse kernel fits (AUTO then runs dense).  In two
+ * cases isc_conv2d runs the filter-ring kernel instead, and isc_sparse_plan
+ * says so: FUSED shapes at stride 1 wider than 16 columns, and GENERIC shapes
+ * with square 1x1, 3x3 and 5x5 filters at stride 2, which it walks straight
+ * from x.  Host-only.  Errors: NULL, SHAPE, LIMIT. */
 enum isc_kernel {
     ISC_KERNEL_NONE = 0,
     ISC_KERNEL_FUSED = 1,
@@ -359,8 +362,8 @@ enum isc_kernel {
 };
 int isc_sparse_kernel(const isc_conv_desc *d, int32_t *kernel);
 
-/* The whole plan of the sparse path for this descriptor under the given
- * overrides (tuning may be NULL): the kernel, its wavefront tile (rows x
+/* The whole plan of isc_conv2d's sparse path for this descriptor under the given
+ * overrides (tuning may be NULL): the kernel that runs, its wavefront tile (rows x
  * cols x 64*maps_per_lane output maps), the channel phases per tile, the
  * wavefronts per workgroup and the workgroups of its launch.  Host-only.
  * Errors: NULL, SHAPE, LIMIT, ARG (nonzero reserved field). */

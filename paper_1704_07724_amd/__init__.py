@@ -489,9 +489,11 @@ KERNEL_NAMES = {0: "none", 1: "fused", 2: "resident", 3: "ring", 4: "generic", 5
 
 
 def isc_sparse_kernel(desc: ConvDesc, tuning=None) -> str:
-    """Which kernel isc_conv2d's sparse path runs for desc (under the given
-    overrides): "fused", "fused_reg", "fused_ring" (on-the-fly compaction),
-    "resident", "ring" or "generic" (over compacted lists), or "none"."""
+    """Which kernel's shape desc is on isc_conv2d's sparse path: "fused",
+    "fused_reg", "fused_ring" (on-the-fly compaction), "resident", "ring" or
+    "generic" (over compacted lists), or "none".  With overrides, the kernel
+    that runs, as isc_sparse_plan reports it: the filter-ring kernel also walks
+    wide "fused" shapes and square "generic" ones at stride 2."""
     if tuning is not None:
         return isc_sparse_plan(desc, tuning)["kernel"]
     which = ctypes.c_int32(-1)

@@ -67,15 +67,15 @@ long long crossover_nnz_limit(const SparseShape &sh) {
     const int64_t total = static_cast<int64_t>(sh.N) * sh.C * sh.H * sh.W;
     isc_plan p{};
     if (!sparse_fused_plan_info(sh, &p)) {
-        // kernels over compacted lists: no model, the paper's 0.9
+        // the kernels over compacted lists have no model, and the filter-ring
+        // kernel's at stride 2 was not held against AUTO: the paper's 0.9
         return static_cast<long long>(std::floor(0.1 * static_cast<double>(total)));
     }
     const double dense = dense_time_model(sh.K, static_cast<int64_t>(sh.N) * sh.Ho * sh.Wo,
                                           static_cast<int64_t>(sh.C) * sh.R * sh.S);
     KernelTime rt;
-    // (a filter-resident plan of four wavefronts is the ring's walk)
-    const bool ring = p.kernel == ISC_KERNEL_FUSED_RING || (p.kernel == ISC_KERNEL_FUSED && p.waves == 4);
-    if (p.kernel == ISC_KERNEL_FUSED_REG ? sparse_reg_time_model(sh, &rt) : ring && sparse_ring_time_model(sh, &rt)) {
+    if (p.kernel == ISC_KERNEL_FUSED_REG ? sparse_reg_time_model(sh, &rt)
+                                         : p.kernel == ISC_KERNEL_FUSED_RING && sparse_ring_time_model(sh, &rt)) {
         // kept open only where the sparse path, with its count, is the faster
         // one on a 0.95 sparse input: the count reads every input (12 us of
         // inception 4a.1's 54 at batch 128), and where the whole call is short

@@ -311,8 +311,7 @@ int conv_impl(const isc_conv_desc *d, const float *x, const float *w, float *y, 
                 dec.nparts = nparts;
             }
             if ((e = isc::launch_sparse_fused(sh, x, wt, y, dec, hs, epi)) != hipSuccess) return hip_status(e);
-        } else if (sh.tu.kernel == 0 && isc::list_kernel_for(sh) == isc::kListGeneric &&
-                   isc::sparse_strided_applies(sh)) {
+        } else if (isc::sparse_strided_applies(sh)) {
             // the general list kernel's shapes at stride 2: the count and the
             // repack, then the walk straight from x (AUTO's limit, the lists'
             // room in the workspace and a census of x are as for the lists)
@@ -591,7 +590,7 @@ int isc_sparse_plan(const isc_conv_desc *d, const isc_tuning *tuning, isc_plan *
     if (!tuning_ok(tuning)) return ISC_ERR_ARG;
     const isc::SparseShape sh = sparse_shape(s, tuning);
     isc_plan p{};
-    if (!isc::sparse_fused_plan_info(sh, &p)) {
+    if (!isc::sparse_fused_plan_info(sh, &p) && !(isc::sparse_strided_applies(sh) && isc::sparse_fring_plan_info(sh, &p))) {
         p = isc_plan{};
         p.kernel = isc::list_kernel_for(sh);
         p.waves = p.kernel == ISC_KERNEL_NONE ? 0 : isc::list_kernel_waves(p.kernel);

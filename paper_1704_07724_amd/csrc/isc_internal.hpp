@@ -216,14 +216,15 @@ hipError_t launch_sparse_fused(const SparseShape &sh, const float *x, const floa
 bool sparse_fring_applies(const SparseShape &sh);
 // The filter-ring kernel at stride 2 (launch_sparse_fring): what isc_conv2d's
 // sparse path runs in place of the general list kernel, straight from x, for
-// square 1x1, 3x3 and 5x5 filters.
+// square 1x1, 3x3 and 5x5 filters, unless the caller names another kernel.
 bool sparse_strided_applies(const SparseShape &sh);
 // 1 (filter-resident), 6 (filter-resident plan with the weights streamed to
 // registers), 5 (filter-ring) or 0 (none): isc_sparse_kernel's ids.
 int sparse_fused_kernel(const SparseShape &sh);
 hipError_t launch_sparse_fring(const SparseShape &sh, const float *x, const float *wt, float *y, const Decision &dec,
                                hipStream_t s, const Epilogue &epi = Epilogue{});
-// The plan the on-the-fly kernels take for a shape (false: none takes it).
+// The plan the on-the-fly kernels take for a shape (false: none takes it), and
+// the filter-ring kernel's (also at stride 2).
 bool sparse_fused_plan_info(const SparseShape &sh, isc_plan *out);
 bool sparse_fring_plan_info(const SparseShape &sh, isc_plan *out);
 int64_t sparse_fring_max_groups(const SparseShape &sh);

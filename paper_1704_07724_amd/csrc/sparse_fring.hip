@@ -145,7 +145,8 @@ bool sparse_fring_applies(const SparseShape &sh) {
 bool sparse_strided_applies(const SparseShape &sh) {
     fring::TileChoice tc;
     int phases;
-    return sh.T == 2 && fring::fring_choose(sh, &tc, &phases);
+    return sh.T == 2 && (sh.tu.kernel == 0 || sh.tu.kernel == ISC_KERNEL_FUSED_RING) &&
+           list_kernel_for(sh) == kListGeneric && fring::fring_choose(sh, &tc, &phases);
 }
 
 int64_t sparse_fring_max_groups(const SparseShape &sh) {
@@ -172,7 +173,7 @@ bool sparse_fring_plan_info(const SparseShape &sh, isc_plan *out) {
     using namespace fring;
     TileChoice tc;
     int phases;
-    if (!sparse_fring_applies(sh) || !fring_choose(sh, &tc, &phases)) return false;
+    if (!fring_choose(sh, &tc, &phases)) return false;
     *out = isc_plan{ISC_KERNEL_FUSED_RING, tc.th, tc.tw, tc.kpl, phases, tc.nw, ring_groups(sh, tc, phases)};
     return true;
 }

@@ -239,11 +239,8 @@ bool sparse_reg_time_model(const SparseShape &sh, KernelTime *t) {
 bool sparse_fused_plan_info(const SparseShape &sh, isc_plan *out) {
     using namespace fused;
     FusedPlan p;
-    if (!fused_plan(sh, &p)) return sparse_fring_plan_info(sh, out);
-    if (fused_walks(sh, p) && sparse_fring_plan_info(sh, out)) {
-        out->kernel = ISC_KERNEL_FUSED;
-        return true;
-    }
+    if (!fused_plan(sh, &p)) return sparse_fring_applies(sh) && sparse_fring_plan_info(sh, out);
+    if (fused_walks(sh, p)) return sparse_fring_plan_info(sh, out);
     const int rg = kWaves / p.cs;
     const int64_t bands = (sh.Ho + rg * p.th - 1) / (rg * p.th);
     const int64_t kgroups = p.wreg ? (sh.K + kLanes - 1) / kLanes : 1;

@@ -320,7 +320,7 @@ def test_sparse_plan_and_overrides():
     assert r["workgroups"] == 128 * 27 // 4 * 2      # 1 x 28 tiles, four to a workgroup, two map groups
     # five maps per lane: no such tile, the library's own choice runs
     assert isc.isc_sparse_plan(conv2, {"kernel": "fused_ring", "maps_per_lane": 5}) == isc.isc_sparse_plan(conv2)
-    assert isc.isc_sparse_plan(d(2, 4, 21, 21, 64, 5, 5, 2, 1))["kernel"] == "generic"
+    assert isc.isc_sparse_plan(d(2, 4, 21, 21, 64, 5, 5, 3, 1))["kernel"] == "generic"
     with pytest.raises(isc.IscError) as e:
         isc.isc_sparse_plan(lenet, isc.Tuning(reserved=3))
     assert e.value.status == 10
@@ -349,7 +349,9 @@ def test_crossover_model_orders_shapes():
     assert one > 0.98 and 0.85 < five < 0.97
     for s in (lenet, conv2, conv3):
         assert 0.0 <= s <= 1.0
-    # a shape only the list kernels take keeps the paper's 0.9
+    # a shape only the list kernels take keeps the paper's 0.9, and so does one
+    # at stride 2
+    assert abs(isc.isc_crossover_sparsity(d(2, 4, 21, 21, 64, 5, 5, 3, 1)) - 0.9) < 1e-3
     assert abs(isc.isc_crossover_sparsity(d(2, 4, 21, 21, 64, 5, 5, 2, 1)) - 0.9) < 1e-3
 
 
@@ -374,3 +376,28 @@ def test_planes_past_two_gigabytes_stay_with_the_ring():
         assert isc.isc_sparse_kernel(d(*shape)) == "fused_ring", shape
     # no lists in the workspace: the control block, the counts and the filter
     assert isc.isc_workspace_size(d(1, 1, 32768, 16384, 1, 3, 3, 1, 1), "sparse") < 1 << 14
+
+
+def test_plan_names_the_kernel_that_runs():
+    """Filter-resident shapes at stride 1 wider than 16 columns, and the general
+    list kernel's square filters at stride 2, are walked by the filter-ring
+    kernel; a caller who names the kernel, or a part of the resident plan, gets
+    it."""
+    d = isc.make_desc
+    wide = d(128, 16, 28, 28, 32, 5, 5, 1, 2)
+    p = isc.isc_sparse_plan(wide)
+    assert (p["kernel"], p["waves"]) == ("fused_ring", 4) and p["workgroups"] > 0
+    q = isc.isc_sparse_plan(wide, {"kernel": "fused"})
+    assert (q["kernel"], q["waves"]) == ("fused", 8)
+    assert isc.isc_sparse_plan(wide, {"phases": 8})["kernel"] == "fused"
+    strided = d(16, 50, 31, 29, 96, 3, 3, 2, 1)
+    p = isc.isc_sparse_plan(strided)
+    assert p["kernel"] == "fused_ring" and (p["rows"], p["cols"]) in ((4, 7), (2, 7)) and p["workgroups"] > 0
+    for t in ((4, 7, 1), (4, 7, 2), (2, 7, 1)):
+        q = isc.isc_sparse_plan(strided, {"kernel": "fused_ring", "rows": t[0], "cols": t[1], "maps_per_lane": t[2]})
+        assert (q["kernel"], q["rows"], q["cols"], q["maps_per_lane"]) == ("fused_ring",) + t
+    assert isc.isc_sparse_plan(strided, {"kernel": "generic"})["kernel"] == "generic"
+    # the filter-resident kernel at stride 2, and shapes no walk takes
+    assert isc.isc_sparse_plan(d(128, 20, 11, 11, 64, 5, 5, 2, 1))["kernel"] == "fused"
+    assert isc.isc_sparse_plan(d(1, 3, 9, 9, 9, 7, 7, 2, 3))["kernel"] == "generic"
+    assert isc.isc_sparse_plan(d(1, 3, 10, 9, 9, 2, 3, 2, 1))["kernel"] == "generic"

@@ -739,6 +739,37 @@ def test_strided_walk(torch, isc, case):
     assert np.array_equal(a, b.cpu().numpy(), equal_nan=True)
 
 
+# each tile of the strided walk, named, with its maps per lane and phases
+STRIDED_TILES = [(R, kpl, th, tw, ph) for R in (1, 3, 5)
+                 for kpl, th, tw in ([(1, 4, 14), (2, 4, 14), (1, 2, 14)] if R == 1 else [(1, 4, 7), (2, 4, 7), (1, 2, 7)])
+                 for ph in (1, 4)]
+
+
+@pytest.mark.parametrize("R,kpl,th,tw,phases", STRIDED_TILES)
+def test_every_strided_tile(torch, isc, R, kpl, th, tw, phases):
+    """Ragged tiles and map groups, few channels, plain and rectified with the
+    census, integers bitwise."""
+    tu = {"kernel": "fused_ring", "maps_per_lane": kpl, "rows": th, "cols": tw, "phases": phases}
+    for case in [(2, 7, 19, 37, 70), (1, 1, 17, 31, 130), (3, 6, 33, 30, 65)]:
+        N, C, H, W, K = case
+        P = R // 2
+        note("strided tile", R, kpl, th, tw, phases, case)
+        desc = isc.make_desc(N, C, H, W, K, R, R, 2, P)
+        plan = isc.isc_sparse_plan(desc, tu)
+        assert [plan[k] for k in ("kernel", "maps_per_lane", "rows", "cols", "phases")] == ["fused_ring", kpl, th, tw, phases]
+        x, w = workloads.make_case(N, C, H, W, K, R, R, 2, P, 0.8, seed=601 + sum(case))
+        xd, wd = to_dev(torch, x), to_dev(torch, w)
+        y = isc.isc_conv2d(xd, wd, 2, P, path="sparse", tuning=tu)
+        assert_conv_close(y.cpu().numpy(), oracle.conv2d_f64(x, w, 2, P), "strided tile %s" % (case,))
+        yc = isc.census(desc)
+        z = isc.isc_conv2d_relu(xd, wd, 2, P, path="sparse", y_census=yc, tuning=tu)
+        assert torch.equal(z, torch.relu(y))
+        assert isc.isc_census_read(yc) == (z.numel(), int((z != 0).sum()))
+        xi, wi = workloads.integer_case(N, C, H, W, K, R, R, seed=11 + sum(case))
+        yi = isc.isc_conv2d(to_dev(torch, xi), to_dev(torch, wi), 2, P, path="sparse", tuning=tu).cpu().numpy()
+        assert np.array_equal(yi.astype(np.float64), oracle.conv2d_f64(xi, wi, 2, P))
+
+
 # N, C, H, W, K, R, S, T, P: edges of the split-operand GEMM's tiles (32 maps is
 # the first size it leaves, 64 and 128 its tile heights), reductions that end
 # inside a slice or are not a multiple of 4, strides, wide padding, 31 taps
