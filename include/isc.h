@@ -146,8 +146,12 @@ int isc_workspace_size(const isc_conv_desc *d, int32_t path, size_t *bytes);
  *     isc_read_decision read it back.
  *   stream: hipStream_t or NULL.
  * A value counts as zero iff its bits with the sign cleared are zero.
- * fp32 throughout; the sparse path accumulates in fp32 in an order of its
- * own, the dense path in MFMA order.  Errors: NULL, SHAPE, LIMIT, WORKSPACE,
+ * fp32 in and out, sums in fp32: the sparse path's in an order of its own, the
+ * dense path's in MFMA order.  The dense path's products are those of fp32
+ * operands; for K > 32, at most 31 taps and at least 16 products per output it
+ * forms each from six of bf16 parts, less than 2^-26 of it left out, and takes
+ * tiles with operands or sums that lose more by it (infinities, NaNs, operands
+ * or products near fp32's lower end) again in fp32.  Errors: NULL, SHAPE, LIMIT, WORKSPACE,
  * ALIAS, PATH, ARG, ALIGN, DEVICE, HIP. */
 int isc_conv2d(const isc_conv_desc *d, const float *x, const float *w, float *y,
                void *ws, size_t ws_bytes, int32_t path, float threshold,

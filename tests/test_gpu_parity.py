@@ -414,9 +414,10 @@ FUSED_CASES = [c for c in CONV_CASES if c[7] == 1 and c[5] == c[6] and c[5] in (
     # N, C, H, W, K, R, S, T, P, sparsity: the fused kernel's plans
     (3, 20, 12, 12, 50, 5, 5, 1, 0, 0.9),     # LeNet conv2: 8 phases (3 or 2 maps each), one 8 x 8 tile
     (2, 24, 11, 11, 33, 5, 5, 1, 1, 0.85),    # 3 input maps per wavefront, ragged 8 x 8 tile
-    (2, 9, 20, 20, 64, 5, 5, 1, 2, 0.9),      # Wo 20: 16-column tiles, several row groups
+    (2, 9, 20, 20, 64, 5, 5, 1, 2, 0.9),      # Wo 20: the ring's walk of a resident shape
     (1, 64, 9, 9, 17, 3, 3, 1, 1, 0.9),       # 3x3: 8 maps per wavefront
-    (2, 13, 30, 30, 64, 3, 3, 1, 0, 0.8),     # Wo 28: single-row tiles, ragged phases
+    (2, 13, 30, 30, 64, 3, 3, 1, 0, 0.8),     # Wo 28: the same, ragged channels
+    (260, 3, 16, 16, 20, 3, 3, 1, 1, 0.8),    # filter resident, several row groups
     (1, 100, 6, 6, 64, 1, 1, 1, 0, 0.9),      # 1x1, many input maps
     (300, 2, 5, 5, 3, 5, 5, 1, 2, 0.5),       # many images, 5 x 5 maps padded
     # filter streamed through LDS (K > 64 or a filter larger than LDS)
@@ -454,6 +455,20 @@ def test_sparse_conv_fused_entry(torch, isc, case):
     xi, wi = workloads.integer_case(N, C, H, W, K, R, S, seed=5 + sum(case[:9]))
     yi = isc.isc_sparse_conv_fused(to_dev(torch, xi), isc.isc_repack_filter(to_dev(torch, wi)), T, P)
     assert np.array_equal(yi.cpu().numpy().astype(np.float64), oracle.conv2d_f64(xi, wi, T, P))
+
+
+@pytest.mark.parametrize("case", [(2, 9, 20, 20, 64, 5, 5, 1, 2, 0.9), (2, 13, 30, 30, 64, 3, 3, 1, 0, 0.8),
+                                  (3, 11, 5, 27, 33, 1, 1, 1, 0, 0.7)])
+def test_resident_kernel_on_wide_maps(torch, isc, case):
+    """The filter-resident kernel on maps of 17 to 28 columns, which a caller
+    still gets by naming it."""
+    N, C, H, W, K, R, S, T, P, sp = case
+    note("resident wide", case)
+    x, w = workloads.make_case(N, C, H, W, K, R, S, T, P, sp, seed=131 + sum(case[:9]))
+    desc = isc.make_desc(N, C, H, W, K, R, S, T, P)
+    assert isc.isc_sparse_plan(desc, {"kernel": "fused"})["kernel"] == "fused"
+    y = isc.isc_sparse_conv_fused(to_dev(torch, x), isc.isc_repack_filter(to_dev(torch, w)), T, P, tuning={"kernel": "fused"})
+    assert_conv_close(y.cpu().numpy(), oracle.conv2d_f64(x, w, T, P), "resident wide %s" % (case,))
 
 
 def test_sparse_conv_fused_rejects_ineligible(torch, isc):
