@@ -247,23 +247,33 @@ class LayerRun:
             res["warm_%s_ms" % name] = round(event_time_ms(torch, fn, max(20, reps)), 6)
         return res
 
+    def weight_grad(self):
+        """The weight gradient of this layer's input and a random output
+        gradient, as a call (isc_conv2d_dw) and that gradient; None when the
+        kernel does not take the shape."""
+        torch, isc, L = self.torch, self.isc, self.layer
+        try:
+            nbytes = isc.isc_conv2d_dw_workspace_size(self.desc)
+        except isc.IscError:
+            return None
+        gen = torch.Generator(device="cuda")
+        gen.manual_seed(self.layer.seed)
+        dy = torch.randn((L.N, L.K, self.Ho, self.Wo), device="cuda", generator=gen)
+        ws = torch.empty(max(nbytes, 1), dtype=torch.uint8, device="cuda")
+        dw = torch.empty((L.K, L.C, L.R, L.S), device="cuda")
+        return lambda: isc.isc_conv2d_dw(self.x, dy, L.R, L.S, L.T, L.P, out=dw, ws=ws), dy
+
     def measure_dw(self, cold, reps, graphs=True):
         """The weight gradient (training) on this layer's input with a random
         output gradient: the zero-skipping kernel (isc_conv2d_dw, graph
         replayed) against torch's GPU weight gradient of the same
         convolution (the vendor library, eager), when the kernel takes the
         shape."""
-        torch, isc, L = self.torch, self.isc, self.layer
-        try:
-            nbytes = isc.isc_conv2d_dw_workspace_size(self.desc)
-        except isc.IscError:
+        torch, L = self.torch, self.layer
+        call = self.weight_grad()
+        if call is None:
             return {}
-        gen = torch.Generator(device="cuda")
-        gen.manual_seed(self.layer.seed)
-        dy = torch.randn((L.N, L.K, self.Ho, self.Wo), device="cuda", generator=gen)
-        ws = torch.empty(max(nbytes, 1), dtype=torch.uint8, device="cuda")
-        dw = torch.empty((L.K, L.C, L.R, L.S), device="cuda")
-        fn = lambda: isc.isc_conv2d_dw(self.x, dy, L.R, L.S, L.T, L.P, out=dw, ws=ws)
+        fn, dy = call
         if graphs:
             fn = graph_of(torch, fn).replay
         res = {"t_dw_sparse_ms": stats(cold.times(fn, reps))["median"]}
@@ -273,7 +283,6 @@ class LayerRun:
         res["speedup_dw_vs_library"] = round(res["t_dw_library_ms"] / res["t_dw_sparse_ms"], 3)
         res["dw_tflops_nonzero"] = round(2 * self.nz_macs / (res["t_dw_sparse_ms"] * 1e-3) / 1e12, 3)
         res["dw_tflops_dense_equiv"] = round(self.flops / (res["t_dw_sparse_ms"] * 1e-3) / 1e12, 3)
-        del dy, ws, dw
         return res
 
     def measure_library(self, cold, reps, t_sparse_ms):
@@ -619,14 +628,17 @@ def probe(torch, isc, layer, n):
     number of bytes (the scale of the HBM counters), then n launches each of
     the sparse kernel alone, the stand-alone compaction, the whole AUTO step
     (count and repack, sparse kernel, the dense kernel that exits on the
-    decision) and the dense path, each launch after the 512 MiB cache-evicting
-    write (so the counters see cold traffic)."""
+    decision), the dense path and the weight gradient, each launch after the
+    512 MiB cache-evicting write (so the counters see cold traffic)."""
     run = LayerRun(torch, isc, layer)
     cold = ColdTimer(torch)
     src = torch.ones(64 << 20, dtype=torch.float32, device="cuda")  # 256 MiB
     dst = torch.empty_like(src)
     steps = [("copy", lambda: torch.mul(src, 1.0, out=dst)), ("sparse_kernel", run.sparse_kernel()),
              ("compact", run.compact()), ("auto", run.conv("auto")), ("dense", run.conv("dense"))]
+    grad = run.weight_grad()
+    if grad:
+        steps.append(("weight_grad", grad[0]))
     for name, fn in steps:
         for _ in range(n):
             cold.flush()
