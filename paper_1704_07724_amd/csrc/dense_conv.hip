@@ -791,9 +791,13 @@ void gemm_conv_split_kernel(GemmArgs g) {
     load_b(0);
     store_a();
     store_b(0);
-    load_a(1);  // past the last slice: zero, never used
-    load_b(1);
-    for (int kt = 0; kt < nk; ++kt) {
+    if (nk > 1) {
+        load_a(1);
+        load_b(1);
+    }
+    // slice kt's products; after the last one nothing is cut
+    auto multiply = [&](int kt, auto lastc) {
+        constexpr bool kLast = decltype(lastc)::value;
         __syncthreads();  // the slice is in LDS
         const int buf = kt & 1;
         bf16x8 a[MI][3], b[2][3];
@@ -810,7 +814,7 @@ void gemm_conv_split_kernel(GemmArgs g) {
                 b[j & 1][p] = __builtin_bit_cast(bf16x8, bs[buf][p][row * 4 + (lq ^ ((row >> 1) & 3))]);
         };
         read_b(0);
-        __syncthreads();  // the slice of A is in everyone's registers
+        if constexpr (!kLast) __syncthreads();  // the slice of A is in everyone's registers
         // its products, with the next slice's cut and stored and the one
         // after that loaded between them: the vector unit works in the matrix
         // unit's shadow
@@ -826,6 +830,7 @@ void gemm_conv_split_kernel(GemmArgs g) {
 #pragma unroll
             for (int i = 0; i < MI; ++i)
                 acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[i][0], b[j & 1][0], acc[i][j], 0, 0, 0);
+            if constexpr (kLast) continue;
             if (j == 0) {
                 store_a();
             } else if (j == 1) {
@@ -841,11 +846,8 @@ void gemm_conv_split_kernel(GemmArgs g) {
             }
             __builtin_amdgcn_sched_barrier(0);
         }
-    }
-#pragma unroll
-    for (int i = 0; i < MI; ++i)
-#pragma unroll
-        for (int j = 0; j < NJ; ++j) acc[i][j] += low[i][j];
+    };
+    for (int kt = 0; kt + 1 < nk; ++kt) multiply(kt, std::false_type{});
     // the lane's number, and the first slice's, anew: nothing of them is carried
     // through the loop above
     int none;
@@ -853,6 +855,11 @@ void gemm_conv_split_kernel(GemmArgs g) {
     lane = static_cast<int>(__builtin_amdgcn_mbcnt_hi(~0u, __builtin_amdgcn_mbcnt_lo(~0u, static_cast<uint32_t>(none))));
     lrow = lane & 15;
     lq = lane >> 4;
+    multiply(nk - 1, std::true_type{});
+#pragma unroll
+    for (int i = 0; i < MI; ++i)
+#pragma unroll
+        for (int j = 0; j < NJ; ++j) acc[i][j] += low[i][j];
 
     // accumulator register v of lane l holds row 4*(l/16) + v and column l%16
     // of its 16 x 16 block
