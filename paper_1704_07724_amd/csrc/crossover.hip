@@ -10,12 +10,7 @@
 // Both paths' times are modelled from the plan the launch would run.  The
 // register-weight and filter-ring kernels' models, which also choose their
 // tiles, are the larger of two lines in the input's density (sparse_fused.hip,
-// sparse_fring.hip); the filter-resident kernel's is one line,
-//   t_sparse(d) = c0 + c2 * d * F_nz + c3 * F_chain
-// with F_nz the nonzeros of its wavefronts' windows times their work (scalar
-// dispatch plus taps in multiply-adds) and F_chain the channels each
-// wavefront walks in sequence, fitted to the sparse path measured at
-// sparsities 0.5 to 0.99.  The
+// sparse_fring.hip); the filter-resident kernel's is one line, below.  The
 // dense path's model is in dense_conv.hip.  The limit handed to the device
 // is the largest nonzero count whose modelled sparse time does not exceed
 // the modelled dense time; the device compares integers only.
@@ -27,15 +22,10 @@
 namespace isc {
 namespace {
 
-struct Fit {
-    double c0, c_nz, c_chain;  // ms; features scaled by 1e-9 (1e-3 for the chain)
-};
-
-constexpr Fit kResidentFit{0.0105, 1.77078063, 1.41836285};
-
 constexpr double kShortCall = 0.04;       // ms
 constexpr double kShortSlower = 1.2;
 constexpr double kChoiceLaunches = 0.009; // ms: the count's launch and the gated ones
+constexpr double kGatedLaunches = 0.004;  // ms: the gated ones alone
 constexpr double kCountPerInput = 1e-9;  // ms: 4 bytes at 4 TB/s
 
 // The largest count whose density does not exceed dstar, where the dense path takes
@@ -92,19 +82,23 @@ long long crossover_nnz_limit(const SparseShape &sh) {
         return limit_for(std::min((meet - rt.base[0]) / rt.slope[0], (meet - rt.base[1]) / rt.slope[1]), total, dense,
                          std::max(rt.base[0] + rt.slope[0], rt.base[1] + rt.slope[1]));
     }
-    const double wc = static_cast<double>(p.workgroups) * p.waves * sh.C / std::max(1, p.phases);
+    // the filter-resident kernel, with the count and repack before it: per round
+    // of workgroups over the CUs and per channel of a wavefront a fixed part, the
+    // static scan of its window and the window's nonzeros, and the filter's copy
+    // into LDS.  Fitted to the sparse path timed on 90 shapes at sparsities 0.3 to
+    // 0.95 (9 % rms, 36 % at most).
     const int wrows = (p.rows - 1) * sh.T + sh.R, wcols = (p.cols - 1) * sh.T + sh.S;
     const double pin = static_cast<double>(std::min(wrows, sh.H)) * std::min(wcols, sh.W);
     const double useful = static_cast<double>(std::min(p.rows, sh.Ho)) * std::min(p.cols, sh.Wo);
     const double taps = std::min<double>(sh.R * sh.S, useful * sh.R * sh.S / pin);
-    // channels each wavefront walks in sequence
-    const double chain = static_cast<double>(sh.C) / std::max(1, p.phases) * 1e-3;
-    const Fit &f = kResidentFit;
-    const double fixed = f.c0 + f.c_chain * chain;
-    const double per_density = f.c_nz * wc * pin * (10.0 + taps * std::max(1, p.maps_per_lane)) * 1e-9;
-    if (!(per_density > 0.0)) return dense >= fixed ? static_cast<long long>(total) : -1;
-    const double dstar = (dense - fixed) / per_density;  // density at which the two meet
-    return limit_for(dstar, total, dense, fixed + per_density);
+    const double rounds = std::ceil(static_cast<double>(p.workgroups) / 256.0);
+    const double channels = (sh.C + std::max(1, p.phases) - 1) / std::max(1, p.phases);
+    const double fixed = 0.00763 + rounds * (channels * (0.000142 + 4.54e-6 * wrows * wcols) + 8.8e-7 * sh.C * sh.R * sh.S);
+    const double per_density = 3.05e-6 * rounds * channels * pin * (10.0 + taps);
+    // as above, the count being in the time
+    if (fixed + per_density <= dense) return static_cast<long long>(total);
+    if (fixed + 0.05 * per_density + (dense < kShortCall ? kGatedLaunches : 0.0) > dense) return -1;
+    return limit_for((dense - fixed) / per_density, total, dense, fixed + per_density);
 }
 
 }  // namespace isc

@@ -401,3 +401,16 @@ def test_plan_names_the_kernel_that_runs():
     assert isc.isc_sparse_plan(d(128, 20, 11, 11, 64, 5, 5, 2, 1))["kernel"] == "fused"
     assert isc.isc_sparse_plan(d(1, 3, 9, 9, 9, 7, 7, 2, 3))["kernel"] == "generic"
     assert isc.isc_sparse_plan(d(1, 3, 10, 9, 9, 2, 3, 2, 1))["kernel"] == "generic"
+
+
+def test_resident_shapes_cross_where_measured():
+    """The filter-resident kernel's model: shapes whose sparse path was measured
+    well ahead of the dense path at 0.9 (14 to 16 us against 18 to 25, 9 against
+    14) are given to it there; one that never catches up (98 us against 21) is
+    not."""
+    d = isc.make_desc
+    for shape in ((13, 36, 12, 14, 40, 3, 3, 2, 0), (92, 26, 9, 7, 57, 3, 3, 2, 1), (20, 17, 8, 8, 16, 3, 3, 2, 0),
+                  (2, 42, 9, 9, 8, 3, 3, 1, 0), (128, 20, 11, 11, 64, 5, 5, 2, 1)):
+        assert isc.isc_sparse_plan(d(*shape))["kernel"] == "fused"
+        assert isc.isc_crossover_sparsity(d(*shape)) <= 0.9, shape
+    assert isc.isc_crossover_sparsity(d(128, 227, 15, 15, 25, 1, 1, 1, 0)) == 2.0
