@@ -599,7 +599,9 @@ void gemm_conv_ring_kernel(GemmArgs g) {
 // slice's 96 MFMAs it cuts and stores the next slice's fp32 values, which it
 // holds in registers, and loads those of the slice after that: the vector unit's share
 // (cutting is 5.5 instructions a value, the largest operand one more) passes in
-// the matrix unit's shadow.
+// the matrix unit's shadow.  After the last slice nothing is cut, which is what
+// the shortest products pay most for (1x1, 16 -> 40 maps of 14 x 14, batch 4: 7.7
+// -> 6.7 us; 16 -> 256 of 28 x 28, batch 128: 41.5 -> 37).
 //
 // The im2col gather takes one k (uniform over a wavefront) of 64 consecutive
 // columns per load: each lane keeps a bit per tap that says whether its
